@@ -247,13 +247,18 @@ hdf_status hdf_krr_create(const double* points, int64_t n, int d, int64_t ld, co
     std::vector<int64_t> fill(start.begin(), start.end() - 1);
     for (int64_t i = 0; i < n; ++i) perm[fill[lab[i]]++] = (int32_t)i;
   }
-  int64_t aoff = 0;
+  int64_t aoff = 0, poff = 0, doff = 0;
+  int max_nt = 1;
   for (int c = 0; c < k; ++c) {
     if (count[c] == 0) continue;
     const int b = (int)h->blocks.size();
-    h->blocks.push_back(Block{start[c], aoff, (int32_t)count[c], 0});
+    const int nt = (int)((count[c] + hdf::krr::kTile - 1) / hdf::krr::kTile);
+    h->blocks.push_back(Block{start[c], aoff, poff, doff, (int32_t)count[c], nt});
     h->block_cluster.push_back(c);
     aoff += count[c] * count[c];
+    poff += (int64_t)nt * nt * hdf::krr::kTile * hdf::krr::kTile;
+    doff += nt;
+    max_nt = std::max(max_nt, nt);
     h->max_n = std::max<int>(h->max_n, (int)count[c]);
     for (int64_t p = start[c]; p < start[c + 1]; ++p) {
       lohi[2 * p] = (int32_t)start[c];
@@ -292,18 +297,18 @@ hdf_status hdf_krr_create(const double* points, int64_t n, int d, int64_t ld, co
     hdf::set_product_timing(h->fac[c], false);
   }
   h->t_factor = now_ms() - t0;
-  // preconditioner: dense blocks, Cholesky, inverses
+  // preconditioner: dense blocks and their inverses
   t0 = now_ms();
   {
-    Buf A, status;
-    KCHK(A.alloc((size_t)aoff * sizeof(double)));
+    Buf M, diag, status;
+    KCHK(M.alloc((size_t)poff * sizeof(double)));
+    KCHK(diag.alloc((size_t)doff * (hdf::krr::kTile + 1) * hdf::krr::kTile * sizeof(double)));
     KCHK(h->ainv.alloc((size_t)aoff * sizeof(double)));
     KCHK(status.alloc((size_t)nb * sizeof(int32_t)));
-    KCHK(hdf::krr::launch_dense_blocks(h->xs.as<double>(), d, h->blocks_dev.as<Block>(), nb, h->max_n, h->kernel,
-                                       lengthscale, lambda, A.as<double>(), s));
-    KCHK(hdf::krr::launch_cholesky(A.as<double>(), h->blocks_dev.as<Block>(), nb, status.as<int32_t>(), s));
-    KCHK(hdf::krr::launch_chol_inverse(A.as<double>(), h->blocks_dev.as<Block>(), nb, h->max_n,
-                                       h->ainv.as<double>(), s));
+    KCHK(hdf::krr::launch_dense_blocks(h->xs.as<double>(), d, h->blocks_dev.as<Block>(), nb, max_nt, h->kernel,
+                                       lengthscale, lambda, M.as<double>(), s));
+    KCHK(hdf::krr::launch_block_inverse(M.as<double>(), diag.as<double>(), h->blocks_dev.as<Block>(), nb, max_nt,
+                                        status.as<int32_t>(), h->ainv.as<double>(), s));
     std::vector<int32_t> stat(nb);
     KCHK(hipMemcpyAsync(stat.data(), status.p, (size_t)nb * sizeof(int32_t), hipMemcpyDeviceToHost, s));
     KCHK(hipStreamSynchronize(s));

@@ -251,89 +251,285 @@ __global__ __launch_bounds__(256) void k_scatter(const double* __restrict__ v, c
 
 // ---------------------------------------------------- preconditioner blocks
 
+// Upper tiles (tile row <= tile column) of lam I + K for each block, in rows of 64 nt; the rows and
+// columns past the block's n are those of the identity.
 template <int D, int KIND>
 __global__ __launch_bounds__(256) void k_dense_blocks(const double* __restrict__ xs, const Block* __restrict__ blocks,
-                                                      double ka, double lam, double* __restrict__ A) {
+                                                      double ka, double lam, double* __restrict__ M) {
   const Block B = blocks[blockIdx.y];
   const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  const int64_t nn = (int64_t)B.n * B.n;
-  if (e >= nn) return;
-  const int64_t i = e / B.n, j = e % B.n;
-  const double* xi = xs + (B.pos + i) * D;
-  const double* xj = xs + (B.pos + j) * D;
-  double r2 = 0.0;
+  const int np = kTile * B.nt;
+  if (e >= (int64_t)np * np) return;
+  const int i = (int)(e / np), j = (int)(e % np);
+  if (i / kTile > j / kTile) return;
+  double v = i == j ? 1.0 : 0.0;
+  if (i < B.n && j < B.n) {
+    const double* xi = xs + (B.pos + i) * D;
+    const double* xj = xs + (B.pos + j) * D;
+    double r2 = 0.0;
 #pragma unroll
-  for (int t = 0; t < D; ++t) {
-    const double u = xi[t] - xj[t];
-    r2 = fma(u, u, r2);
+    for (int t = 0; t < D; ++t) {
+      const double u = xi[t] - xj[t];
+      r2 = fma(u, u, r2);
+    }
+    v = kval<KIND>(r2, ka) + (i == j ? lam : 0.0);
   }
-  A[B.aoff + e] = kval<KIND>(r2, ka) + (i == j ? lam : 0.0);
+  M[B.poff + e] = v;
 }
 
-// Right-looking Cholesky A = U^T U of each block in place, on the upper
-// triangle (row-major): row j of U is finished at step j, then the trailing
-// rows c > j lose U[j][c] * U[j][c..n).  One workgroup per block; the lower
-// triangle is left untouched.  status[b] = 0, or the 1-based step whose pivot
-// was not positive and finite.
-__global__ __launch_bounds__(1024) void k_cholesky(double* __restrict__ A, const Block* __restrict__ blocks,
-                                                   int32_t* __restrict__ status) {
-  __shared__ double piv;
-  __shared__ int bad;
-  const Block B = blocks[blockIdx.x];
-  const int n = B.n;
-  double* U = A + B.aoff;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nw = blockDim.x >> 6;
-  if (tid == 0) bad = 0;
-  for (int j = 0; j < n; ++j) {
-    __syncthreads();
-    if (tid == 0) {
-      const double a = U[(int64_t)j * n + j];
-      const bool ok = a > 0.0 && a < INFINITY;
-      if (!ok && bad == 0) bad = j + 1;
-      piv = ok ? sqrt(a) : 1.0;
-    }
-    __syncthreads();
-    const double pj = piv;
-    for (int i = j + tid; i < n; i += blockDim.x) {
-      double* u = U + (int64_t)j * n + i;
-      *u = (i == j) ? pj : *u / pj;
-    }
-    __syncthreads();
-    for (int c = j + 1 + wave; c < n; c += nw) {
-      const double f = U[(int64_t)j * n + c];
-      double* row = U + (int64_t)c * n;
-      const double* rj = U + (int64_t)j * n;
-      for (int i = c + lane; i < n; i += 64) row[i] = fma(-f, rj[i], row[i]);
-    }
+// Inverses of the preconditioner's blocks: A = U^T U by elimination on [A | I], tile by tile, then
+// A^-1 = L^-T L^-1 with L = U^T.  Work storage of a block (64 nt square): its upper tiles hold A and
+// then the rows of U, its strictly lower tiles L^-1 as the elimination forms it, its diagonal tiles
+// the inverses of the diagonal factors, (L_jj)^-1.  Step j of the elimination, over all blocks at once:
+//   k_inv_panel  M_jt <- (L_jj)^-1 M_jt          for every tile t != j of row j, by substitution
+//   k_inv_trail  M_ci -= M_jc^T M_ji             for c > j and i <= j (L^-1) or i >= c (A), and the
+//                                                workgroup of M_(j+1)(j+1) factorises that tile next
+// so a block of n points costs 2 nt launches of up to nt^2 / 4 workgroups, the bulk of the work (the
+// trail and the final product) on the matrix cores, and the serial 64-step factorisation of a
+// diagonal tile overlaps the other tiles' updates.  What bounds it is that chain of steps.  The
+// preconditioner of 13,760 points in 30 blocks of up to 777 (allocations included): 146.6 ms with one
+// workgroup per block and one thread per column of the inverse, 2.07 ms so.
+// Every entry takes its products one by one in the order of the steps, each subtracted with one
+// rounding: the entries of a kernel matrix shrink as the elimination goes on, and a sum of 64 products
+// formed first, or a panel formed with the explicit inverse of the diagonal factor, is rounded at its
+// own, larger size (z = A^-1 r of 13,760 points in 30 blocks, against extended precision: 4.7e-14 so,
+// 6.4e-15 in this order).
+typedef double doublex2 __attribute__((ext_vector_type(2)));
+typedef double doublex4 __attribute__((ext_vector_type(4)));
+constexpr int kTS = 80;                               // LDS row stride: rows k and k + 1 on different bank halves
+constexpr int kTileLds = kTile * kTS;                 // doubles of a staged tile
+
+// a 64 x 64 tile with row stride ld into LDS (256 threads, 16-byte loads)
+__device__ __forceinline__ void tile_load(const double* __restrict__ src, int64_t ld, double* __restrict__ dst) {
+#pragma unroll
+  for (int it = 0; it < 8; ++it) {
+    const int e = it * 256 + threadIdx.x;
+    const int row = e >> 5, c2 = (e & 31) * 2;
+    *reinterpret_cast<doublex2*>(dst + row * kTS + c2) = *reinterpret_cast<const doublex2*>(src + row * ld + c2);
   }
+}
+
+// acc += SIGN P^T Q: wavefront w forms rows 16 w .. 16 w + 15, four 16 x 16 accumulator tiles
+template <int SIGN>
+__device__ __forceinline__ void tile_product(const double* P, const double* Q, doublex4 (&acc)[4]) {
+  const int lane = threadIdx.x & 63, r = lane & 15, q = lane >> 4, w = threadIdx.x >> 6;
+#pragma unroll
+  for (int k = 0; k < kTile; k += 4) {
+    const double a = SIGN * P[(k + q) * kTS + 16 * w + r];
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+      acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, Q[(k + q) * kTS + 16 * t + r], acc[t], 0, 0, 0);
+  }
+}
+
+constexpr int kDiag = kTile * kTile + kTile;          // a diagonal factor U_jj and its reciprocal diagonal
+
+// Factorisation of the diagonal tile in registers: thread (w, l) holds rows 16 w .. 16 w + 15 of
+// column l of the tile and of the identity.  The wavefront that owns row j scales it and publishes
+// the rows of U and L^-1 in `rows` (LDS, 2 x 192 values); one barrier per step.
+__device__ void tile_factor(double (&a)[16], double* rows, int j0, int32_t* status, double* Mjj, int64_t ld,
+                            double* dj) {
+  const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
+  double b[16];
+#pragma unroll
+  for (int q = 0; q < 16; ++q) b[q] = 16 * w + q == l ? 1.0 : 0.0;
+  int bad = 0;
+  // row j (row q of this wavefront): pivot from lane j by way of LDS, both parts divided by its root
+  auto publish = [&](int j, double& aq, double& bq) {
+    double* next = rows + 192 * (j & 1);
+    next[128 + l] = aq;
+    __builtin_amdgcn_wave_barrier();
+    double p = next[128 + j];
+    if (!(p > 0.0 && p < INFINITY)) {
+      if (!bad) bad = j0 + j + 1;
+      p = 1.0;
+    }
+    const double d = sqrt(p);
+    aq /= d;
+    bq /= d;
+    next[l] = aq;
+    next[64 + l] = bq;
+    if (l == j) dj[kTile * kTile + j] = 1.0 / d;
+  };
+  if (w == 0) publish(0, a[0], b[0]);
   __syncthreads();
-  if (tid == 0) status[blockIdx.x] = bad;
+  for (int wj = 0; wj < 4; ++wj) {
+#pragma unroll
+    for (int jj = 0; jj < 16; ++jj) {
+      const int j = 16 * wj + jj;
+      const double* row = rows + 192 * (j & 1);
+      if (w >= wj) {
+        const double ra = row[l], rb = row[64 + l];
+#pragma unroll
+        for (int q = 0; q < 16; ++q) {
+          if (w > wj || q > jj) {
+            const double m = -row[16 * w + q];
+            a[q] = fma(m, ra, a[q]);
+            b[q] = fma(m, rb, b[q]);
+          }
+        }
+      }
+      if (jj < 15) {
+        if (w == wj) publish(j + 1, a[(jj + 1) & 15], b[(jj + 1) & 15]);
+      } else if (w == wj + 1) {
+        publish(j + 1, a[0], b[0]);
+      }
+      __syncthreads();
+    }
+  }
+  // the wavefronts own consecutive rows: the first bad step is the lowest of theirs
+  int* first = reinterpret_cast<int*>(rows);
+  if (l == 0) first[w] = bad;
+  __syncthreads();
+  if (threadIdx.x == 0 && *status == 0) {
+    for (int v = 3; v >= 0; --v) bad = first[v] ? first[v] : bad;
+    if (bad) *status = bad;
+  }
+#pragma unroll
+  for (int q = 0; q < 16; ++q) {
+    const int row = 16 * w + q;
+    Mjj[row * ld + l] = b[q];
+    dj[row * kTile + l] = a[q];
+  }
 }
 
-// X = A^{-1} = U^{-1} U^{-T} column by column: one thread per column col
-// solves U^T y = e_col, then U x = y, in place in X (row-major, the same
-// layout as A).  Threads are independent: each reads U (the same entry across
-// a wavefront) and its own column of X.
-__global__ __launch_bounds__(256) void k_chol_inverse(const double* __restrict__ Uall, const Block* __restrict__ blocks,
-                                                      double* __restrict__ Xall) {
+__global__ __launch_bounds__(256) void k_inv_first(double* __restrict__ M, double* __restrict__ diag,
+                                                   const Block* __restrict__ blocks, int32_t* __restrict__ status) {
+  __shared__ double rows[384];
+  const Block B = blocks[blockIdx.x];
+  const int64_t ld = (int64_t)kTile * B.nt;
+  double* m = M + B.poff;
+  const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
+  double a[16];
+#pragma unroll
+  for (int q = 0; q < 16; ++q) a[q] = m[(16 * w + q) * ld + l];
+  if (threadIdx.x == 0) status[blockIdx.x] = 0;
+  tile_factor(a, rows, 0, status + blockIdx.x, m, ld, diag + B.doff * kDiag);
+}
+
+// One wavefront per tile, one column per lane: X = (U_jj)^-T M_jt by forward substitution in
+// registers, U_jj read as wavefront-uniform values.  The quotients are formed from the reciprocal
+// diagonal with one correction.
+__global__ __launch_bounds__(64) void k_inv_panel(double* __restrict__ M, const double* __restrict__ diag,
+                                                  const Block* __restrict__ blocks, int j) {
   const Block B = blocks[blockIdx.y];
-  const int n = B.n;
-  if ((int)blockIdx.x * 256 >= n) return;
-  const int col = blockIdx.x * 256 + threadIdx.x;
-  const bool act = col < n;
-  const double* U = Uall + B.aoff;
-  double* X = Xall + B.aoff;
-  // lanes past the last column read the first column of U (valid, read-only) and store nothing
-  const double* xc = act ? X + col : U;
-  for (int i = 0; i < n; ++i) {
-    double s = (i == col) ? 1.0 : 0.0;
-    for (int k = 0; k < i; ++k) s = fma(-U[(int64_t)k * n + i], xc[(int64_t)k * n], s);
-    if (act) X[(int64_t)i * n + col] = s / U[(int64_t)i * n + i];
+  if (j >= B.nt || (int)blockIdx.x >= B.nt - 1) return;
+  const int t = (int)blockIdx.x < j ? blockIdx.x : blockIdx.x + 1;
+  const int64_t ld = (int64_t)kTile * B.nt;
+  double* c = M + B.poff + (int64_t)j * kTile * ld + (int64_t)t * kTile + threadIdx.x;
+  const double* U = diag + (B.doff + j) * kDiag;
+  double x[kTile];
+#pragma unroll
+  for (int r = 0; r < kTile; ++r) x[r] = c[r * ld];
+#pragma unroll
+  for (int r = 0; r < kTile; ++r) {
+    const double inv = U[kTile * kTile + r];
+    double v = x[r] * inv;
+    v = fma(fma(-v, U[r * kTile + r], x[r]), inv, v);
+    c[r * ld] = v;
+#pragma unroll
+    for (int k = r + 1; k < kTile; ++k) x[k] = fma(-U[r * kTile + k], v, x[k]);
   }
-  for (int i = n - 1; i >= 0; --i) {
-    double s = xc[(int64_t)i * n];
-    for (int k = i + 1; k < n; ++k) s = fma(-U[(int64_t)i * n + k], xc[(int64_t)k * n], s);
-    if (act) X[(int64_t)i * n + col] = s / U[(int64_t)i * n + i];
+}
+
+__global__ __launch_bounds__(256) void k_inv_trail(double* __restrict__ M, double* __restrict__ diag,
+                                                   const Block* __restrict__ blocks, int j,
+                                                   int32_t* __restrict__ status) {
+  extern __shared__ unsigned char smem_raw[];
+  double* P = reinterpret_cast<double*>(smem_raw);
+  double* Q = P + kTileLds;
+  const Block B = blocks[blockIdx.y];
+  // tiles of the trailing rows c > j: first the upper ones (row j + 1 first), then the j + 1 columns of L^-1
+  const int nr = B.nt - 1 - j;
+  int x = blockIdx.x, c, i;
+  if (nr < 1) return;
+  const int64_t upper = (int64_t)nr * (nr + 1) / 2;
+  if (x < upper) {
+    c = 0;
+    while (x >= nr - c) x -= nr - c++;
+    i = j + 1 + c + x;
+    c += j + 1;
+  } else {
+    x -= (int)upper;
+    if (x >= nr * (j + 1)) return;
+    c = j + 1 + x / (j + 1);
+    i = x % (j + 1);
+  }
+  const int64_t ld = (int64_t)kTile * B.nt;
+  double* m = M + B.poff;
+  const double* rowj = m + (int64_t)j * kTile * ld;
+  double* out = m + (int64_t)c * kTile * ld + (int64_t)i * kTile;
+  tile_load(rowj + (int64_t)c * kTile, ld, P);
+  if (c != i) tile_load(rowj + (int64_t)i * kTile, ld, Q);
+  const int lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4, w = threadIdx.x >> 6;
+  doublex4 acc[4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) acc[u][e] = i == j ? 0.0 : out[(16 * w + g + 4 * e) * ld + 16 * u + r];
+  __syncthreads();
+  tile_product<-1>(P, c != i ? Q : P, acc);
+  const bool next = c == i && c == j + 1;             // uniform
+#pragma unroll
+  for (int u = 0; u < 4; ++u)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int row = 16 * w + g + 4 * e, col = 16 * u + r;
+      if (next) Q[row * kTS + col] = acc[u][e];
+      else out[row * ld + col] = acc[u][e];
+    }
+  if (!next) return;
+  __syncthreads();
+  const int l = lane;
+  double a[16];
+#pragma unroll
+  for (int q = 0; q < 16; ++q) a[q] = Q[(16 * w + q) * kTS + l];
+  tile_factor(a, P, kTile * c, status + blockIdx.y, out, ld, diag + (B.doff + c) * kDiag);
+}
+
+// X = L^-T L^-1: tile (i, c), i <= c, sums the tiles k >= c of columns i and c of L^-1; the tile is
+// written to both halves of the n x n inverse.
+__global__ __launch_bounds__(256) void k_inv_form(const double* __restrict__ M, const Block* __restrict__ blocks,
+                                                  double* __restrict__ X) {
+  extern __shared__ unsigned char smem_raw[];
+  double* P = reinterpret_cast<double*>(smem_raw);
+  double* Q = P + kTileLds;
+  const Block B = blocks[blockIdx.y];
+  int x = blockIdx.x, i = 0;
+  if (x >= (int64_t)B.nt * (B.nt + 1) / 2) return;
+  while (x >= B.nt - i) x -= B.nt - i++;
+  const int c = i + x;
+  const int64_t ld = (int64_t)kTile * B.nt;
+  const double* m = M + B.poff;
+  doublex4 acc[4] = {{0, 0, 0, 0}, {0, 0, 0, 0}, {0, 0, 0, 0}, {0, 0, 0, 0}};
+  for (int k = c; k < B.nt; ++k) {
+    const double* rowk = m + (int64_t)k * kTile * ld;
+    __syncthreads();
+    tile_load(rowk + (int64_t)i * kTile, ld, P);
+    if (c != i) tile_load(rowk + (int64_t)c * kTile, ld, Q);
+    __syncthreads();
+    tile_product<1>(P, c != i ? Q : P, acc);
+  }
+  const int lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4, w = threadIdx.x >> 6;
+  double* out = X + B.aoff;
+#pragma unroll
+  for (int u = 0; u < 4; ++u)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int row = kTile * i + 16 * w + g + 4 * e, col = kTile * c + 16 * u + r;
+      if (row < B.n && col < B.n) out[(int64_t)row * B.n + col] = acc[u][e];
+    }
+  if (c == i) return;
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < 4; ++u)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) P[(16 * u + r) * kTS + 16 * w + g + 4 * e] = acc[u][e];
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < 16; ++q) {
+    const int row = kTile * c + 16 * w + q, col = kTile * i + lane;
+    if (row < B.n && col < B.n) out[(int64_t)row * B.n + col] = P[(16 * w + q) * kTS + lane];
   }
 }
 
@@ -565,12 +761,12 @@ hipError_t launch_scatter(const double* v, const int32_t* perm, int64_t n, doubl
   return hipGetLastError();
 }
 
-hipError_t launch_dense_blocks(const double* xs, int d, const Block* blocks, int nb, int max_n, int kernel,
-                               double l, double lam, double* A, hipStream_t s) {
+hipError_t launch_dense_blocks(const double* xs, int d, const Block* blocks, int nb, int max_nt, int kernel,
+                               double l, double lam, double* M, hipStream_t s) {
   if (kernel < 0 || kernel > 3 || nb < 1) return hipErrorInvalidValue;
-  const dim3 g(blocks_for((int64_t)max_n * max_n), (unsigned)nb);
+  const dim3 g(blocks_for((int64_t)max_nt * kTile * max_nt * kTile), (unsigned)nb);
   const double ka = kernel_param(kernel, l);
-#define DB_K(D, K) k_dense_blocks<D, K><<<g, 256, 0, s>>>(xs, blocks, ka, lam, A)
+#define DB_K(D, K) k_dense_blocks<D, K><<<g, 256, 0, s>>>(xs, blocks, ka, lam, M)
 #define DB_D(D)                        \
   switch (kernel) {                    \
     case 0: DB_K(D, 0); break;         \
@@ -584,14 +780,19 @@ hipError_t launch_dense_blocks(const double* xs, int d, const Block* blocks, int
   return hipGetLastError();
 }
 
-hipError_t launch_cholesky(double* A, const Block* blocks, int nb, int32_t* status, hipStream_t s) {
-  k_cholesky<<<(unsigned)nb, 1024, 0, s>>>(A, blocks, status);
-  return hipGetLastError();
-}
-
-hipError_t launch_chol_inverse(const double* U, const Block* blocks, int nb, int max_n, double* X, hipStream_t s) {
-  const dim3 g(blocks_for(max_n), (unsigned)nb);
-  k_chol_inverse<<<g, 256, 0, s>>>(U, blocks, X);
+hipError_t launch_block_inverse(double* M, double* diag, const Block* blocks, int nb, int max_nt, int32_t* status,
+                                double* X, hipStream_t s) {
+  if (nb < 1 || max_nt < 1) return hipErrorInvalidValue;
+  const size_t lds = 2 * (size_t)kTileLds * sizeof(double);
+  k_inv_first<<<(unsigned)nb, 256, 0, s>>>(M, diag, blocks, status);
+  for (int j = 0; j < max_nt; ++j) {
+    const unsigned nr = (unsigned)(max_nt - 1 - j);
+    if (max_nt > 1) k_inv_panel<<<dim3((unsigned)max_nt - 1, (unsigned)nb), 64, 0, s>>>(M, diag, blocks, j);
+    if (nr > 0)
+      k_inv_trail<<<dim3(nr * (nr + 1) / 2 + nr * (unsigned)(j + 1), (unsigned)nb), 256, lds, s>>>(M, diag, blocks, j,
+                                                                                                  status);
+  }
+  k_inv_form<<<dim3((unsigned)max_nt * ((unsigned)max_nt + 1) / 2, (unsigned)nb), 256, lds, s>>>(M, blocks, X);
   return hipGetLastError();
 }
 

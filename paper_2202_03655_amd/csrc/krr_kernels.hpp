@@ -19,9 +19,11 @@ constexpr int kDotBlocks = 256;    // partial sums per dot product
 // per-cluster descriptors in cluster order
 struct Block {
   int64_t pos;    // first position of the cluster
-  int64_t aoff;   // offset of its n x n matrix in the block storage
+  int64_t aoff;   // offset of its n x n inverse in the preconditioner's storage
+  int64_t poff;   // offset of its (64 nt) x (64 nt) matrix in the factorisation's work storage
+  int64_t doff;   // first of its nt diagonal tiles (64 x 64) in the tile storage
   int32_t n;      // members
-  int32_t pad;
+  int32_t nt;     // 64-wide tiles: ceil(n / 64)
 };
 
 // k-means
@@ -50,10 +52,13 @@ hipError_t launch_gather(const double* v, const int32_t* perm, int64_t n, double
 hipError_t launch_scatter(const double* v, const int32_t* perm, int64_t n, double* out, hipStream_t s);
 
 // preconditioner blocks
-hipError_t launch_dense_blocks(const double* xs, int d, const Block* blocks, int nb, int max_n, int kernel,
-                               double l, double lam, double* A, hipStream_t s);
-hipError_t launch_cholesky(double* A, const Block* blocks, int nb, int32_t* status, hipStream_t s);
-hipError_t launch_chol_inverse(const double* U, const Block* blocks, int nb, int max_n, double* X, hipStream_t s);
+constexpr int kTile = 64;   // tile edge of the factorisation's work storage
+hipError_t launch_dense_blocks(const double* xs, int d, const Block* blocks, int nb, int max_nt, int kernel,
+                               double l, double lam, double* M, hipStream_t s);
+// inverses of the blocks of M (destroyed) into X at Block::aoff, n x n each; diag: kTile (kTile + 1) values per
+// diagonal tile; status[b] = 0, or the 1-based step whose pivot was not positive and finite
+hipError_t launch_block_inverse(double* M, double* diag, const Block* blocks, int nb, int max_nt, int32_t* status,
+                                double* X, hipStream_t s);
 // z = blockdiag(Ainv) r; part_rz[b] (if not NULL) = block b's share of r . z; skipped when st->done
 hipError_t launch_block_gemv(const double* Ainv, const Block* blocks, const int32_t* row_block, int64_t n,
                              const double* r, double* z, double* part_rz, const CGState* st, hipStream_t s);
