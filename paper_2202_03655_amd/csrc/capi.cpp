@@ -234,7 +234,7 @@ struct hdf_factor {
   // tables of the factor evaluation (in build_tabs) and of the products (in prod_tabs), each
   // set uploaded in one copy
   DevBuf build_tabs, prod_tabs;
-  DevView col_of, chain, q_len, q_off, q_coef, degs_dev, lam_row, tile_tabs, degs_by_k;
+  DevView col_of, chain, q_len, q_off, q_coef, leaves, degs_dev, lam_row, tile_tabs, degs_by_k;
   int n_tiles = 0, tiles_cpl = 0;                 // pass-1 work items for cpl = m16/16
   // tile-major pass 1 (m16 <= 64): wave items and their workgroup groups for each cpl = m16 / 16
   // in 1..4, built with the factor; tile_tabs holds all wave items, then all groups, then the
@@ -333,12 +333,6 @@ void loop_order_columns(int d, int K, const std::unordered_map<uint64_t, int>& c
 // common to the symmetric and the general (X != Y) build.  A general factor
 // evaluates its Y side too, with the Y-side radial coefficients; its diagonal
 // is the identity (sqrt of the singular values is folded into both sides).
-// Zero columns [n, ld) of a rows x ld matrix (the padding of the factor rows).
-static hipError_t clear_padding(void* base, int64_t rows, int64_t n, int64_t ld, size_t el, hipStream_t s) {
-  if (rows <= 0 || ld <= n) return hipSuccess;
-  return hipMemset2DAsync((char*)base + n * el, ld * el, 0, (ld - n) * el, rows, s);
-}
-
 // Wave items of the tile-major pass 1 for cpl = m16 / 16 (1..4): one per 16 harmonics of a kept
 // degree and range of its radial functions (nl * nct accumulator tiles at most), then groups of up
 // to kMvtWavesPerGroup items whose radial rows span at most kMvtMaxNq rows.
@@ -877,6 +871,13 @@ static hdf_status finish_build(hdf_factor* f, double t0, hipStream_t s) {
     if (f->cross) add_typed(f->q_coef2, qc2);
     bt.add(f->q_len, ql.data(), ql.size() * 4);
     bt.add(f->q_off, qo.data(), qo.size() * 4);
+    // harmonics below a chain loop of level lv and base b: C(Kh - b + lv, lv)
+    std::vector<int32_t> leaves((size_t)(d - 1) * (Kh + 1), 1);
+    for (int lv = 1; lv <= d - 2; ++lv)
+      for (int b = Kh; b >= 0; --b)
+        leaves[(size_t)lv * (Kh + 1) + b] =
+            leaves[(size_t)(lv - 1) * (Kh + 1) + b] + (b < Kh ? leaves[(size_t)lv * (Kh + 1) + b + 1] : 0);
+    bt.add(f->leaves, leaves.data(), leaves.size() * 4);
     HIPCHK(upload_batch(f->build_tabs, bt));
     hdf::BuildTables tb{};
     tb.col_of = (const int32_t*)f->col_of.p;
@@ -886,6 +887,8 @@ static hdf_status finish_build(hdf_factor* f, double t0, hipStream_t s) {
     tb.q_coef = f->q_coef.p;
     tb.K = Kh;
     tb.S = (int)f->S;
+    tb.leaves = (const int32_t*)f->leaves.p;
+    tb.n_loop = (int)col_of.size();
     f->tables = tb;
     // tables of the products (not read by the factor evaluation): built and uploaded after its
     // launch in the stored case, so the host work overlaps the evaluation on the device
@@ -943,17 +946,11 @@ static hdf_status finish_build(hdf_factor* f, double t0, hipStream_t s) {
     HIPCHK(hipEventRecord(f->ev_b0, s));
     HIPCHK(hdf::launch_build(f->x_soa.p, dtype, f->ldN, n, d, (const hdf::GeoDev*)f->geo_dev.p,
                              f->u0, f->u1, tb, prec, f->phi.p, f->ldN, f->q.p, f->ldN, s));
-    // rows are padded past N: clear the padding so contraction kernels may
-    // read whole 8-point groups without masking
-    HIPCHK(clear_padding(f->phi.p, f->H, n, f->ldN, f->felem(), s));
-    HIPCHK(clear_padding(f->q.p, f->S, n, f->ldN, f->felem(), s));
     if (f->cross) {
       f->tables2 = tb;
       f->tables2.q_coef = f->q_coef2.p;
       HIPCHK(hdf::launch_build(f->x_soa2.p, dtype, f->ldN2, f->N2, d, (const hdf::GeoDev*)f->geo_dev.p,
                                f->u0, f->u1, f->tables2, prec, f->phi2.p, f->ldN2, f->q2.p, f->ldN2, s));
-      HIPCHK(clear_padding(f->phi2.p, f->H, f->N2, f->ldN2, f->felem(), s));
-      HIPCHK(clear_padding(f->q2.p, f->S, f->N2, f->ldN2, f->felem(), s));
     }
     HIPCHK(hipEventRecord(f->ev_b1, s));
     const hdf_status pst = product_tables();
@@ -1409,14 +1406,12 @@ hdf_status hdf_build_cross(const void* x, int64_t nx, int64_t ldx, const void* y
 // Pass 1 (W = U^T V, binary64) and the scaled copy Wd = D W for pass 2.
 // side 0: the factor's (X) rows; side 1: the Y rows of a general factor.
 // Matrix-free factor: evaluate the harmonics and radial functions of points [c0, c0 + nc) into the
-// chunk scratch (padding columns cleared, as for a stored factor).
+// chunk scratch.
 static hdf_status eval_chunk(hdf_handle h, int64_t c0, int64_t nc, hipStream_t s) {
   const size_t in_el = h->dtype == 0 ? 4 : 8;
   HIPCHK(hdf::launch_build((const char*)h->x_soa.p + c0 * in_el, h->dtype, h->ldN, nc, h->d,
                            (const hdf::GeoDev*)h->geo_dev.p, h->u0, h->u1, h->tables, h->fprec, h->cphi.p, h->ldC,
                            h->cq.p, h->ldC, s));
-  HIPCHK(clear_padding(h->cphi.p, h->H, nc, h->ldC, h->felem(), s));
-  HIPCHK(clear_padding(h->cq.p, h->S, nc, h->ldC, h->felem(), s));
   return HDF_OK;
 }
 
@@ -1881,7 +1876,6 @@ static hdf_status adjoint_dx(hdf_handle h, const double* gv, const double* gw, i
     HIPCHK(hdf::launch_radial(h->x_soa.p, h->dtype, h->ldN, h->N, d, (const hdf::GeoDev*)h->geo_dev.p, h->u0,
                               h->u1, h->tables.q_len, h->tables.q_off, h->dq_coef.p, (int)h->S, 2.0 / (h->u1 - h->u0),
                               h->fprec, h->dq.p, h->ldN, s));
-    HIPCHK(clear_padding(h->dq.p, h->S, h->N, h->ldN, fel, s));
     HIPCHK(hipStreamSynchronize(s));             // the coefficient copy above is read before keep is reused
   }
   // coefficients: C2 = [lambda gv | lambda gw] (rank x 2m), Cs = [G^(j)T C2]_j (shifted rank x 2m d)

@@ -751,13 +751,16 @@ __device__ __forceinline__ void store_row(T* __restrict__ dst, const T (&v)[PPT]
   __builtin_nontemporal_store(w, reinterpret_cast<V*>(dst));
 }
 
-template <typename T, int D, int PPT, int LEVEL>
+// SPLIT: only the harmonics of loop order [t_lo, t_hi) are evaluated; a subtree outside the range is
+// passed over by its number of harmonics, leaves[level (K + 1) + b] below a level-`level` loop of base b.
+template <typename T, int D, int PPT, int LEVEL, bool SPLIT>
 struct Chain {
   typedef typename Vec2<T>::type T2;
   static __device__ __forceinline__ void run(const T (&xt)[PPT][D], const T (&r2)[PPT][D], int b,
                                              const T (&prefix)[PPT], int K,
                                              const T2* __restrict__ chain,
-                                             const int32_t* __restrict__ col_of, int& t,
+                                             const int32_t* __restrict__ col_of,
+                                             const int32_t* __restrict__ leaves, int t_lo, int t_hi, int& t,
                                              T* __restrict__ phi_base, int64_t ld) {
     const T2* cf = chain + ((int64_t)(LEVEL - 1) * (K + 1) + b) * (K + 1);
     T pm1[PPT], p[PPT], pre[PPT];
@@ -776,25 +779,38 @@ struct Chain {
           p[e] = pn;
         }
       }
+      if constexpr (SPLIT) {
+        const int cnt = leaves[(LEVEL - 1) * (K + 1) + b + nn];
+        if (t >= t_hi) return;
+        if (t + cnt <= t_lo) {
+          t += cnt;
+          continue;
+        }
+      }
 #pragma unroll
       for (int e = 0; e < PPT; ++e) pre[e] = prefix[e] * p[e];
-      Chain<T, D, PPT, LEVEL - 1>::run(xt, r2, b + nn, pre, K, chain, col_of, t, phi_base, ld);
+      Chain<T, D, PPT, LEVEL - 1, SPLIT>::run(xt, r2, b + nn, pre, K, chain, col_of, leaves, t_lo, t_hi, t, phi_base,
+                                              ld);
     }
   }
 };
-template <typename T, int D, int PPT>
-struct Chain<T, D, PPT, 0> {
+template <typename T, int D, int PPT, bool SPLIT>
+struct Chain<T, D, PPT, 0, SPLIT> {
   typedef typename Vec2<T>::type T2;
   static __device__ __forceinline__ void run(const T (&)[PPT][D], const T (&)[PPT][D], int,
                                              const T (&prefix)[PPT], int, const T2* __restrict__,
-                                             const int32_t* __restrict__ col_of, int& t,
-                                             T* __restrict__ phi_base, int64_t ld) {
+                                             const int32_t* __restrict__ col_of, const int32_t* __restrict__, int, int,
+                                             int& t, T* __restrict__ phi_base, int64_t ld) {
     const int col = col_of[t++];
     if (col >= 0) store_row<T, PPT>(phi_base + (int64_t)col * ld, prefix);
   }
 };
 
-template <typename Tin, typename T, int D, int PPT>
+// Points of a row that the evaluation writes: the n points and zeros up to the padding the streaming
+// kernels may read (rows are at least that long).
+__host__ __device__ static inline int64_t row_end(int64_t n) { return (n + 63) / 64 * 64 + 64; }
+
+template <typename Tin, typename T, int D, int PPT, bool SPLIT>
 __global__ void __launch_bounds__(256) k_build(const Tin* __restrict__ x_soa, int64_t ldx, int64_t n,
                                                 const GeoDev* __restrict__ geo, double u0, double u1,
                                                 const int32_t* __restrict__ col_of,
@@ -802,10 +818,15 @@ __global__ void __launch_bounds__(256) k_build(const Tin* __restrict__ x_soa, in
                                                 const int32_t* __restrict__ q_len,
                                                 const int32_t* __restrict__ q_off,
                                                 const T* __restrict__ q_coef, int K, int S,
+                                                const int32_t* __restrict__ leaves, int per_group, int q_per_group,
                                                 T* __restrict__ phi, int64_t ld_phi,
                                                 T* __restrict__ q, int64_t ld_q) {
   const int64_t i0 = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * PPT;
-  if (i0 >= n) return;      // whole thread past the end (ld is padded to 64)
+  if (i0 >= row_end(n)) return;      // whole thread past the row's written end (a multiple of 64)
+  // SPLIT: this workgroup's harmonics (loop order) and radial rows
+  const int t_lo = SPLIT ? (int)blockIdx.y * per_group : 0, t_hi = SPLIT ? t_lo + per_group : 0;
+  const int q_lo = SPLIT ? (int)blockIdx.y * q_per_group : 0;
+  const int q_hi = SPLIT ? (q_lo + q_per_group < S ? q_lo + q_per_group : S) : S;
   T xt[PPT][D], r2[PPT][D], tt[PPT];
   {
 #pragma clang fp contract(off)
@@ -836,7 +857,7 @@ __global__ void __launch_bounds__(256) k_build(const Tin* __restrict__ x_soa, in
   int t = 0;
   T cr[PPT], ci[PPT], pre[PPT];
 #pragma unroll
-  for (int e = 0; e < PPT; ++e) { cr[e] = 1; ci[e] = 0; }
+  for (int e = 0; e < PPT; ++e) { cr[e] = i0 + e < n ? 1 : 0; ci[e] = 0; }   // points past n: zero rows
   const T inv_sqrt_2pi = (T)0.39894228040143267794, inv_sqrt_pi = (T)0.56418958354775628695;
   T* phi_base = phi + i0;
   for (int mm = 0; mm <= K; ++mm) {
@@ -850,17 +871,25 @@ __global__ void __launch_bounds__(256) k_build(const Tin* __restrict__ x_soa, in
       }
     }
     const T cm = (mm == 0) ? inv_sqrt_2pi : inv_sqrt_pi;
+    if constexpr (SPLIT) {
+      if (t >= t_hi) break;
+      const int both = (mm > 0 ? 2 : 1) * leaves[(D - 2) * (K + 1) + mm];
+      if (t + both <= t_lo) {
+        t += both;
+        continue;
+      }
+    }
 #pragma unroll
     for (int e = 0; e < PPT; ++e) pre[e] = cm * cr[e];
-    Chain<T, D, PPT, D - 2>::run(xt, r2, mm, pre, K, chain, col_of, t, phi_base, ld_phi);
+    Chain<T, D, PPT, D - 2, SPLIT>::run(xt, r2, mm, pre, K, chain, col_of, leaves, t_lo, t_hi, t, phi_base, ld_phi);
     if (mm > 0) {
 #pragma unroll
       for (int e = 0; e < PPT; ++e) pre[e] = cm * ci[e];
-      Chain<T, D, PPT, D - 2>::run(xt, r2, mm, pre, K, chain, col_of, t, phi_base, ld_phi);
+      Chain<T, D, PPT, D - 2, SPLIT>::run(xt, r2, mm, pre, K, chain, col_of, leaves, t_lo, t_hi, t, phi_base, ld_phi);
     }
   }
   // radial functions: Clenshaw in the basis T_a(t)
-  for (int row = 0; row < S; ++row) {
+  for (int row = q_lo; row < q_hi; ++row) {
     const int L = q_len[row];
     const T* cf = q_coef + q_off[row];
     T b1[PPT], b2[PPT], val[PPT];
@@ -876,24 +905,44 @@ __global__ void __launch_bounds__(256) k_build(const Tin* __restrict__ x_soa, in
       }
     }
 #pragma unroll
-    for (int e = 0; e < PPT; ++e) val[e] = tt[e] * b1[e] - b2[e] + cf[0];
+    for (int e = 0; e < PPT; ++e) val[e] = i0 + e < n ? tt[e] * b1[e] - b2[e] + cf[0] : (T)0;
     store_row<T, PPT>(q + (int64_t)row * ld_q + i0, val);
   }
 }
+
+// Workgroups of the factor evaluation.  One workgroup per 256 PPT points leaves the chip idle for few
+// points (10 workgroups for 10,007 points) and, since a thread then writes all its rows one after the
+// other, keeps too few stores in flight for many: the harmonics (loop order) and radial rows are cut
+// into groups, 16 harmonics or more each, for about kBuildBlocks workgroups in all.  Where that leaves
+// fewer than kBuildFewBlocks, groups go down to two harmonics: the chain of a thread is then shorter
+// than the recurrences that it repeats.  Kernel times before and now: 2,000 points d = 3 binary64 26 ->
+// 7.7 us; 460 points d = 8 binary64 530 -> 14; 10,007 points d = 5 365 -> 24; 1e5 points d = 3 98 -> 27;
+// 2e5 points d = 4 316 -> 177; 250,007 points d = 5 binary64 521 -> 473; 1e6 points d = 5 732 -> 687
+// (655 at best, 5.2 TB/s).  16,384 workgroups: 1e6 points 760 us, 2e5 points 206; 1,024: 711 and 215.
+constexpr int64_t kBuildBlocks = 8192, kBuildFewBlocks = 512;
 
 template <typename Tin, typename T>
 static hipError_t launch_build_t(const void* x_soa, int64_t ldx, int64_t n, int d, const GeoDev* geo,
                                  double u0, double u1, const BuildTables& tb, void* phi,
                                  int64_t ld_phi, void* q, int64_t ld_q, hipStream_t s) {
   constexpr int PPT = 16 / sizeof(T);
-  const dim3 grid((unsigned)((n + 256 * PPT - 1) / (256 * PPT)));
+  if (ld_phi < row_end(n) || ld_q < row_end(n)) return hipErrorInvalidValue;
+  const int64_t blocks = (row_end(n) + 256 * PPT - 1) / (256 * PPT);
+  const int64_t full = std::min<int64_t>((kBuildBlocks + blocks - 1) / blocks, (tb.n_loop + 15) / 16);
+  const int64_t few = std::min<int64_t>((kBuildFewBlocks + blocks - 1) / blocks, (tb.n_loop + 1) / 2);
+  const int groups = (int)std::max<int64_t>(1, std::max(full, few));
+  const int per_group = (tb.n_loop + groups - 1) / groups, q_per_group = (tb.S + groups - 1) / groups;
+  const dim3 grid((unsigned)blocks, (unsigned)groups);
   typedef typename Vec2<T>::type T2;
+#define BUILD_RUN(DD, SPLIT)                                                                  \
+  k_build<Tin, T, DD, PPT, SPLIT><<<grid, 256, 0, s>>>((const Tin*)x_soa, ldx, n, geo, u0, u1, tb.col_of,       \
+                                                       (const T2*)tb.chain, tb.q_len, tb.q_off,                 \
+                                                       (const T*)tb.q_coef, tb.K, tb.S, tb.leaves, per_group,   \
+                                                       q_per_group, (T*)phi, ld_phi, (T*)q, ld_q)
 #define BUILD_CASE(DD)                                                                        \
   case DD:                                                                                    \
-    k_build<Tin, T, DD, PPT><<<grid, 256, 0, s>>>((const Tin*)x_soa, ldx, n, geo, u0, u1,    \
-                                                  tb.col_of, (const T2*)tb.chain, tb.q_len,   \
-                                                  tb.q_off, (const T*)tb.q_coef, tb.K, tb.S,  \
-                                                  (T*)phi, ld_phi, (T*)q, ld_q);              \
+    if (groups > 1) BUILD_RUN(DD, true);                                                      \
+    else BUILD_RUN(DD, false);                                                                \
     break;
   switch (d) {
     BUILD_CASE(3)
@@ -905,6 +954,7 @@ static hipError_t launch_build_t(const void* x_soa, int64_t ldx, int64_t n, int 
     default: return hipErrorInvalidValue;
   }
 #undef BUILD_CASE
+#undef BUILD_RUN
   return hipGetLastError();
 }
 
@@ -942,7 +992,7 @@ __global__ void __launch_bounds__(256) k_radial(const Tin* __restrict__ x_soa, i
                                                  const T* __restrict__ coef, int S, T scale, T* __restrict__ out,
                                                  int64_t ld_out) {
   const int64_t i0 = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * PPT;
-  if (i0 >= n) return;      // whole thread past the end (rows are padded past n)
+  if (i0 >= row_end(n)) return;      // whole thread past the row's written end (a multiple of 64)
   T tt[PPT];
   {
 #pragma clang fp contract(off)
@@ -974,7 +1024,7 @@ __global__ void __launch_bounds__(256) k_radial(const Tin* __restrict__ x_soa, i
       }
     }
 #pragma unroll
-    for (int e = 0; e < PPT; ++e) val[e] = scale * (tt[e] * b1[e] - b2[e] + cf[0]);
+    for (int e = 0; e < PPT; ++e) val[e] = i0 + e < n ? scale * (tt[e] * b1[e] - b2[e] + cf[0]) : (T)0;
     store_row<T, PPT>(out + (int64_t)row * ld_out + i0, val);
   }
 }
@@ -983,10 +1033,11 @@ hipError_t launch_radial(const void* x_soa, int dtype, int64_t ldx, int64_t n, i
                          double u0, double u1, const int32_t* q_len, const int32_t* q_off, const void* coef,
                          int S, double scale, int prec, void* out, int64_t ld_out, hipStream_t s) {
   if (S <= 0 || n <= 0) return hipSuccess;
+  if (ld_out < row_end(n)) return hipErrorInvalidValue;
 #define HDF_RAD(TIN, T)                                                                                      \
   do {                                                                                                       \
     constexpr int PPT = 16 / sizeof(T);                                                                      \
-    const unsigned nb = (unsigned)((n + 256 * PPT - 1) / (256 * PPT));                                      \
+    const unsigned nb = (unsigned)((row_end(n) + 256 * PPT - 1) / (256 * PPT));                             \
     k_radial<TIN, T, PPT><<<nb, 256, 0, s>>>((const TIN*)x_soa, ldx, n, d, geo, u0, u1, q_len, q_off,       \
                                              (const T*)coef, S, (T)scale, (T*)out, ld_out);                  \
   } while (0)

@@ -66,7 +66,10 @@ struct BuildTables {
   const void* q_coef;        // radial coefficients, storage type
   int K;                     // largest kept degree: depth of the harmonic recurrences
   int S;                     // radial rows
+  const int32_t* leaves;     // (level, b) -> harmonics below a chain loop of that level and base, level 0..d-2
+  int n_loop;                // harmonics evaluated (loop order), kept or not
 };
+// rows of phi and q get their n values and zeros up to the next multiple of 64 plus 64
 hipError_t launch_build(const void* x_soa, int dtype, int64_t ldx, int64_t n, int d,
                         const GeoDev* geo, double u0, double u1, const BuildTables& tb,
                         int prec, void* phi, int64_t ld_phi, void* q, int64_t ld_q,
