@@ -220,7 +220,7 @@ struct hdf_factor {
   std::vector<int> kept_k;
   std::vector<int32_t> index_table;               // H x (d-1)
   int64_t H = 0, S = 0, r = 0;
-  int64_t n_wblocks = 0;                          // blocks of pass 2's batch-major copy of D W
+  int64_t n_wblocks = 0;                          // blocks of pass 2's block-ordered copy of D W
   int max_s = 0;
   int n_refined = 0;                              // degrees refined by the second Gram pass
   double t_prep = 0, t_plan = 0, t_gram = 0, t_compress = 0, t_finish = 0, t_build = -1;
@@ -234,7 +234,7 @@ struct hdf_factor {
   // tables of the factor evaluation (in build_tabs) and of the products (in prod_tabs), each
   // set uploaded in one copy
   DevBuf build_tabs, prod_tabs;
-  DevView col_of, chain, q_len, q_off, q_coef, leaves, degs_dev, lam_row, tile_tabs, degs_by_k;
+  DevView col_of, chain, q_len, q_off, q_coef, leaves, degs_dev, lam_row, blk_src, tile_tabs, degs_by_k;
   int n_tiles = 0, tiles_cpl = 0;                 // pass-1 work items for cpl = m16/16
   // tile-major pass 1 (m16 <= 64): wave items and their workgroup groups for each cpl = m16 / 16
   // in 1..4, built with the factor; tile_tabs holds all wave items, then all groups, then the
@@ -247,7 +247,7 @@ struct hdf_factor {
   // host copies of the pass-1 tables: they outlive their asynchronous uploads
   std::vector<hdf::TileDev> tiles_host;
   // matvec / adjoint workspace
-  DevBuf ws_part, ws_W, ws_Wd, ws_Wb, ws_n, bw_GV, bw_GVd, bw_GW, bw_GWd, bw_VW;
+  DevBuf ws_part, ws_Wd, ws_Wb, ws_n, bw_GV, bw_GW, bw_VW;
   DevBuf cphi, cq;                                // matrix-free chunk scratch
   // adjoint (dF/dX by contractions): the loop-order row table, q' = dq/d(rho^2) rows and their
   // coefficients, the shifted-factor degree table (harmonics of k - 1 with radial rows of k), the
@@ -255,7 +255,7 @@ struct hdf_factor {
   std::vector<int32_t> col_of_host;
   DevBuf dq, dq_coef, adj_degs, adj_c2, adj_cs, adj_kv2, adj_kvs;
   std::vector<hdf::DegDev> adj_degs_host;
-  int64_t r_shift = 0;
+  int64_t r_shift = 0, shift_blocks = 0;
   std::vector<char> adj_c2_host, adj_cs_host;
   hdf::BuildTables tables{};
   ~hdf_factor() {
@@ -920,6 +920,13 @@ static hdf_status finish_build(hdf_factor* f, double t0, hipStream_t s) {
         for (int h = 0; h < f->degs[di].nh; ++h)
           for (int l = 0; l < df.s; ++l) lr.push_back(f->cross ? 1.0 : df.lam[l]);
       }
+      // rank row of every row of pass 2's blocks (16 harmonics x one radial function), -1 past a degree
+      std::vector<int32_t> src;
+      src.reserve((size_t)f->n_wblocks * 16);
+      for (const hdf::DegDev& dg : f->degs)
+        for (int h0 = 0; h0 < dg.nh; h0 += 16)
+          for (int l = 0; l < dg.s; ++l)
+            for (int hh = h0; hh < h0 + 16; ++hh) src.push_back(hh < dg.nh ? dg.roff + hh * dg.s + l : -1);
       std::vector<hdf::DegDev> dbk(K + 1);
       for (int k = 0; k <= K; ++k) { dbk[k] = hdf::DegDev{}; }
       for (size_t di = 0; di < f->degs.size(); ++di) dbk[f->kept_k[di]] = f->degs[di];
@@ -927,6 +934,7 @@ static hdf_status finish_build(hdf_factor* f, double t0, hipStream_t s) {
       bp.add(f->degs_dev, f->degs.data(), f->degs.size() * sizeof(hdf::DegDev));
       bp.add(f->tile_tabs, tabs.data(), tabs.size());
       bp.add(f->lam_row, lr.data(), lr.size() * 8);
+      bp.add(f->blk_src, src.data(), src.size() * 4);
       bp.add(f->degs_by_k, dbk.data(), dbk.size() * sizeof(hdf::DegDev));
       HIPCHK(upload_batch(f->prod_tabs, bp));
       return HDF_OK;
@@ -1415,8 +1423,26 @@ static hdf_status eval_chunk(hdf_handle h, int64_t c0, int64_t nc, hipStream_t s
   return HDF_OK;
 }
 
-static hdf_status pass1(hdf_handle h, int side, const void* V, int64_t m, int64_t ldv, int m16, DevBuf& W,
-                        DevBuf& Wd, hipStream_t s, bool timed);
+// What a pass 1 leaves: W = U^T V (binary64, rank rows), Wd = D W in the factor's type (rank rows),
+// Wb = D W in pass 2's block order; a null buffer is not wanted.
+struct PassOut {
+  DevBuf* W = nullptr;
+  DevBuf* Wd = nullptr;
+  DevBuf* Wb = nullptr;
+};
+static hdf_status pass1(hdf_handle h, int side, const void* V, int64_t m, int64_t ldv, int m16, const PassOut& out,
+                        hipStream_t s, bool timed);
+
+// The wanted outputs of a pass 1 from its split partials.
+static hdf_status reduce_splits(hdf_handle h, int n_splits, int m16, const PassOut& out, hipStream_t s) {
+  if (out.W) HIPCHK(out.W->ensure((size_t)h->r * m16 * sizeof(double)));
+  if (out.Wd) HIPCHK(out.Wd->ensure((size_t)h->r * m16 * h->felem()));
+  if (out.Wb) HIPCHK(out.Wb->ensure((size_t)h->n_wblocks * 16 * m16 * h->felem()));
+  HIPCHK(hdf::launch_matvec_reduce((const double*)h->ws_part.p, n_splits, h->r, m16, (const int32_t*)h->blk_src.p,
+                                   h->n_wblocks, (const double*)h->lam_row.p, out.W ? (double*)out.W->p : nullptr,
+                                   out.Wd ? out.Wd->p : nullptr, out.Wb ? out.Wb->p : nullptr, h->fprec, s));
+  return HDF_OK;
+}
 
 // Pass 1 of a matrix-free factor: per chunk, evaluate the factor, then contract it into its own range
 // of split partials; one fixed-order reduction over all chunks' partials gives W.
@@ -1446,13 +1472,13 @@ static void tile_splits(int64_t n, int n_groups, size_t per_split, int* n_splits
 
 // Pass 1 of a matrix-free factor: per chunk, evaluate the factor, then contract it into its own range
 // of split partials; one fixed-order reduction over all chunks' partials gives W.
-static hdf_status pass1_chunked(hdf_handle h, const void* V, int64_t m, int64_t ldv, int m16, DevBuf& W,
-                                DevBuf& Wd, hipStream_t s, bool timed) {
+static hdf_status pass1_chunked(hdf_handle h, const void* V, int64_t m, int64_t ldv, int m16, const PassOut& out,
+                                hipStream_t s, bool timed) {
   const size_t el = h->felem();
   const int cpl = m16 / 16;
   const size_t per_split = (size_t)h->r * m16 * sizeof(double);
   // work items and groups as for a stored factor of chunk points
-  hdf_status st = pass1(h, 2, V, m, ldv, m16, W, Wd, s, false);   // side 2: tables only
+  hdf_status st = pass1(h, 2, V, m, ldv, m16, out, s, false);   // side 2: tables only
   if (st != HDF_OK) return st;
   const bool tile = m16 <= 64;
   std::vector<int> splits;
@@ -1478,8 +1504,6 @@ static hdf_status pass1_chunked(hdf_handle h, const void* V, int64_t m, int64_t 
   if ((double)per_split * total > 1.5e9)
     return fail(HDF_E_INFEASIBLE, "matrix-free pass 1 needs more than 1.5 GB of partial sums: use a larger chunk");
   HIPCHK(h->ws_part.ensure(per_split * total));
-  HIPCHK(W.ensure((size_t)h->r * m16 * sizeof(double)));
-  HIPCHK(Wd.ensure((size_t)h->r * m16 * el));
   if (timed) {
     if (!h->ev_mv[0])
       for (auto& e : h->ev_mv) HIPCHK(hipEventCreate(&e));
@@ -1505,8 +1529,10 @@ static hdf_status pass1_chunked(hdf_handle h, const void* V, int64_t m, int64_t 
     slot += splits[ci];
   }
   if (timed) HIPCHK(hipEventRecord(h->ev_mv[1], s));
-  HIPCHK(hdf::launch_matvec_reduce((const double*)h->ws_part.p, total, h->r, m16, (const double*)h->lam_row.p,
-                                   (double*)W.p, Wd.p, h->fprec, s));
+  {
+    const hdf_status rst = reduce_splits(h, total, m16, out, s);
+    if (rst != HDF_OK) return rst;
+  }
   if (timed) HIPCHK(hipEventRecord(h->ev_mv[2], s));
   return HDF_OK;
 }
@@ -1535,7 +1561,7 @@ static int mf_resident(hdf_handle h, int pass) {
 
 // Pass 1 of a fused matrix-free factor: one launch over splits of the points (one workgroup per
 // resident slot), the split partials reduced as for a stored factor.
-static hdf_status pass1_fused(hdf_handle h, const void* V, int64_t m, int64_t ldv, int m16, DevBuf& W, DevBuf& Wd,
+static hdf_status pass1_fused(hdf_handle h, const void* V, int64_t m, int64_t ldv, int m16, const PassOut& out,
                               hipStream_t s, bool timed) {
   const int cpl = m16 / 16;
   const int64_t n = h->N;
@@ -1547,8 +1573,6 @@ static hdf_status pass1_fused(hdf_handle h, const void* V, int64_t m, int64_t ld
   const int64_t len = ((n + ns - 1) / ns + hdf::kMfP - 1) / hdf::kMfP * hdf::kMfP;
   const int n_splits = (int)((n + len - 1) / len);
   HIPCHK(h->ws_part.ensure(per_split * n_splits));
-  HIPCHK(W.ensure((size_t)h->r * m16 * sizeof(double)));
-  HIPCHK(Wd.ensure((size_t)h->r * m16 * h->felem()));
   if (timed) {
     if (!h->ev_mv[0])
       for (auto& e : h->ev_mv) HIPCHK(hipEventCreate(&e));
@@ -1559,8 +1583,10 @@ static hdf_status pass1_fused(hdf_handle h, const void* V, int64_t m, int64_t ld
                           (const int32_t*)(base + h->mf_o_so1), (const int32_t*)(base + h->mf_o_r1), h->mf_nr1,
                           h->mf_g1, cpl, n_splits, len, V, ldv, (int)m, m16, h->r, (double*)h->ws_part.p, s));
   if (timed) HIPCHK(hipEventRecord(h->ev_mv[1], s));
-  HIPCHK(hdf::launch_matvec_reduce((const double*)h->ws_part.p, n_splits, h->r, m16, (const double*)h->lam_row.p,
-                                   (double*)W.p, Wd.p, h->fprec, s));
+  {
+    const hdf_status rst = reduce_splits(h, n_splits, m16, out, s);
+    if (rst != HDF_OK) return rst;
+  }
   if (timed) HIPCHK(hipEventRecord(h->ev_mv[2], s));
   return HDF_OK;
 }
@@ -1584,11 +1610,11 @@ static hdf_status pass2_fused(hdf_handle h, int64_t m, int m16, void* KV, int64_
 }
 
 // side 2 (matrix-free factors): build the work-item tables only.
-static hdf_status pass1(hdf_handle h, int side, const void* V, int64_t m, int64_t ldv, int m16, DevBuf& W,
-                        DevBuf& Wd, hipStream_t s, bool timed) {
+static hdf_status pass1(hdf_handle h, int side, const void* V, int64_t m, int64_t ldv, int m16, const PassOut& out,
+                        hipStream_t s, bool timed) {
   if (h->storage == HDF_STORE_NONE && side != 2)
-    return h->mf_fused ? pass1_fused(h, V, m, ldv, m16, W, Wd, s, timed)
-                       : pass1_chunked(h, V, m, ldv, m16, W, Wd, s, timed);
+    return h->mf_fused ? pass1_fused(h, V, m, ldv, m16, out, s, timed)
+                       : pass1_chunked(h, V, m, ldv, m16, out, s, timed);
   const int64_t n = side == 1 ? h->N2 : (side == 2 ? h->chunk : h->N);
   const void* phi = side == 1 ? h->phi2.p : h->phi.p;
   const void* qv = side == 1 ? h->q2.p : h->q.p;
@@ -1620,8 +1646,6 @@ static hdf_status pass1(hdf_handle h, int side, const void* V, int64_t m, int64_
     int64_t split_len;
     tile_splits(n, h->n_tgroups[cpl], per_split, &n_splits, &split_len);
     HIPCHK(h->ws_part.ensure(per_split * n_splits));
-    HIPCHK(W.ensure((size_t)h->r * m16 * sizeof(double)));
-    HIPCHK(Wd.ensure((size_t)h->r * m16 * el));
     if (timed) {
       if (!h->ev_mv[0])
         for (auto& e : h->ev_mv) HIPCHK(hipEventCreate(&e));
@@ -1632,8 +1656,10 @@ static hdf_status pass1(hdf_handle h, int side, const void* V, int64_t m, int64_
                                      n_splits, split_len, V, ldv, n, (int)m, m16, h->r, (double*)h->ws_part.p,
                                      h->fprec, h->dtype, s));
     if (timed) HIPCHK(hipEventRecord(h->ev_mv[1], s));
-    HIPCHK(hdf::launch_matvec_reduce((const double*)h->ws_part.p, n_splits, h->r, m16,
-                                     (const double*)h->lam_row.p, (double*)W.p, Wd.p, h->fprec, s));
+    {
+    const hdf_status rst = reduce_splits(h, n_splits, m16, out, s);
+    if (rst != HDF_OK) return rst;
+  }
     if (timed) HIPCHK(hipEventRecord(h->ev_mv[2], s));
     return HDF_OK;
   }
@@ -1647,8 +1673,6 @@ static hdf_status pass1(hdf_handle h, int side, const void* V, int64_t m, int64_
   split_len = (split_len + 15) / 16 * 16;
   n_splits = (int)((n + split_len - 1) / split_len);
   HIPCHK(h->ws_part.ensure(per_split * n_splits));
-  HIPCHK(W.ensure((size_t)h->r * m16 * sizeof(double)));
-  HIPCHK(Wd.ensure((size_t)h->r * m16 * el));
   if (timed) {
     if (!h->ev_mv[0])
       for (auto& e : h->ev_mv) HIPCHK(hipEventCreate(&e));
@@ -1659,38 +1683,37 @@ static hdf_status pass1(hdf_handle h, int side, const void* V, int64_t m, int64_
                               (int)m, m16, n_splits, split_len, h->r, (double*)h->ws_part.p,
                               h->fprec, h->dtype, s));
   if (timed) HIPCHK(hipEventRecord(h->ev_mv[1], s));
-  HIPCHK(hdf::launch_matvec_reduce((const double*)h->ws_part.p, n_splits, h->r, m16,
-                                   (const double*)h->lam_row.p, (double*)W.p, Wd.p, h->fprec, s));
+  {
+    const hdf_status rst = reduce_splits(h, n_splits, m16, out, s);
+    if (rst != HDF_OK) return rst;
+  }
   if (timed) HIPCHK(hipEventRecord(h->ev_mv[2], s));
   return HDF_OK;
 }
 
-// Pass 2 over n points of a factor (phi, q with leading dimension ld): KV = U (D W), W from pass 1.
+// Wavefronts below which pass 2 splits its blocks into shares, and the wavefronts it then aims at.
+// A share costs its part of the sum over shares, so a launch that fills the SIMDs once stays whole
+// (1e5 points, 1,563 wavefronts: 46 us, split 42 + 11 for the sum); below that the chain of blocks is
+// what takes the time (20,000 points of rank 2666: 48 us with 1,024 wavefronts, 35 with 4,096, 32 with
+// 8,192; 10,007 of rank 1413: 23, 17, 16; the sums 4 us each).
+constexpr int64_t kPass2Waves = 1024, kPass2SplitWaves = 4096;
+
+// Pass 2 over n points of a factor (phi, q with leading dimension ld): KV = U (D W), D W from pass 1.
 static hdf_status pass2(hdf_handle h, const void* phi, const void* q, int64_t ld, int64_t n, int64_t m, int m16,
                         void* KV, int64_t ldkv, hipStream_t s) {
-  const size_t el = h->felem();
-  // few points: split the harmonic rows so that pass 2 still has >= 1024 wavefronts
-  const int64_t waves = ((n + 63) / 64) * (m16 / 16);
-  int nz = 1, hchunk = 0;
-  if (waves < 1024 && h->H >= 32) {
-    const int64_t want = std::min<int64_t>((1024 + waves - 1) / waves, h->H / 16);
-    if (want > 1) {
-      hchunk = (int)(((h->H + want - 1) / want + 15) / 16 * 16);
-      nz = (int)((h->H + hchunk - 1) / hchunk);
-    }
+  const int nct = hdf::matvec_n_tiles(n, m16 / 16);
+  const int64_t waves = ((n + 63) / 64) * ((m16 / 16 + nct - 1) / nct);
+  int z_blocks = 0;
+  if (waves < kPass2Waves) {
+    const int64_t want = std::min<int64_t>((kPass2SplitWaves + waves - 1) / waves, h->n_wblocks);
+    if (want > 1) z_blocks = (int)((h->n_wblocks + want - 1) / want);
   }
-  if (nz > 1) HIPCHK(h->ws_n.ensure((size_t)nz * n * m * el));
-  // one pass over the points: D W in batch-major order, four rows per lane in one load
-  const void* Wb = nullptr;
-  if (nz == 1) {
-    HIPCHK(h->ws_Wb.ensure((size_t)h->n_wblocks * 16 * m16 * el));
-    HIPCHK(hdf::launch_wd_batches((const hdf::DegDev*)h->degs_dev.p, (int)h->degs.size(), h->ws_Wd.p, m16,
-                                  h->n_wblocks, h->ws_Wb.p, h->fprec, s));
-    Wb = h->ws_Wb.p;
+  if (z_blocks > 0) {
+    const int64_t nz = (h->n_wblocks + z_blocks - 1) / z_blocks;
+    HIPCHK(h->ws_n.ensure((size_t)nz * n * m * h->felem()));
   }
-  HIPCHK(hdf::launch_matvec_n(phi, ld, q, ld, (const hdf::DegDev*)h->degs_dev.p, (int)h->degs.size(), h->max_s,
-                              h->ws_Wd.p, Wb, m16, KV, ldkv, n, (int)m, h->fprec, h->dtype, nz > 1 ? hchunk : 0, nz,
-                              nz > 1 ? h->ws_n.p : nullptr, s));
+  HIPCHK(hdf::launch_matvec_n(phi, ld, q, ld, (const hdf::DegDev*)h->degs_dev.p, (int)h->degs.size(), h->ws_Wb.p,
+                              h->n_wblocks, m16, KV, ldkv, n, (int)m, h->fprec, h->dtype, z_blocks, h->ws_n.p, s));
   return HDF_OK;
 }
 
@@ -1704,7 +1727,10 @@ static hdf_status matvec_impl(hdf_handle h, const void* V, int64_t m, int64_t ld
   }
   const int m16 = (int)((m + 15) / 16 * 16);
   const bool timed = h->time_products;
-  hdf_status st = pass1(h, h->cross ? 1 : 0, V, m, ldv, m16, h->ws_W, h->ws_Wd, s, timed);
+  PassOut po;
+  if (h->mf_fused) po.Wd = &h->ws_Wd;
+  else po.Wb = &h->ws_Wb;
+  hdf_status st = pass1(h, h->cross ? 1 : 0, V, m, ldv, m16, po, s, timed);
   if (st != HDF_OK) return st;
   if (h->storage == HDF_STORE_NONE && h->mf_fused) {
     st = pass2_fused(h, m, m16, KV, ldkv, s);
@@ -1774,9 +1800,11 @@ hdf_status hdf_matvec_noalloc(hdf_handle h, const void* V, int64_t m, int64_t ld
   const int m16 = (int)((m + 15) / 16 * 16), cpl = m16 / 16;
   const size_t per_split = (size_t)h->r * m16 * sizeof(double);
   auto round256 = [](size_t b) { return (b + 255) / 256 * 256; };
+  // the limit on the rank is that of W, D W and one split; D W in block order takes their place
   const size_t w_bytes = round256((size_t)h->r * m16 * sizeof(double));
   const size_t wd_bytes = round256((size_t)h->r * m16 * h->felem());
-  if (w_bytes + wd_bytes + per_split > hdf::kScratchBytes) {
+  const size_t wb_bytes = round256((size_t)h->n_wblocks * 16 * m16 * h->felem());
+  if (std::max(w_bytes + wd_bytes, wb_bytes) + per_split > hdf::kScratchBytes) {
     char buf[200];
     snprintf(buf, sizeof buf, "rank %lld x %d columns needs %.3g MB of work space, above the %.3g MB scratch",
              (long long)h->r, m16, (double)(w_bytes + wd_bytes + per_split) / 1e6, (double)hdf::kScratchBytes / 1e6);
@@ -1787,22 +1815,22 @@ hdf_status hdf_matvec_noalloc(hdf_handle h, const void* V, int64_t m, int64_t ld
   int n_splits;
   int64_t split_len;
   tile_splits(n1, h->n_tgroups[cpl], per_split, &n_splits, &split_len);
-  const int max_splits = (int)((hdf::kScratchBytes - w_bytes - wd_bytes) / per_split);
+  const int max_splits = (int)((hdf::kScratchBytes - wb_bytes) / per_split);
   if (n_splits > max_splits) {
     split_len = ((n1 + max_splits - 1) / max_splits + 31) / 32 * 32;
     n_splits = (int)((n1 + split_len - 1) / split_len);
   }
-  double* W = (double*)base;
-  void* Wd = (char*)base + w_bytes;
-  double* part = (double*)((char*)base + w_bytes + wd_bytes);
+  void* Wb = base;
+  double* part = (double*)((char*)base + wb_bytes);
   HIPCHK(hdf::launch_matvec_t_tile(side ? h->phi2.p : h->phi.p, side ? h->ldN2 : h->ldN, side ? h->q2.p : h->q.p,
                                    side ? h->ldN2 : h->ldN, tile_waves(h, cpl), tile_rank_rows(h), tile_groups(h, cpl),
                                    h->n_tgroups[cpl], n_splits, split_len, V, ldv, n1, (int)m, m16, h->r, part,
                                    h->fprec, h->dtype, s));
-  HIPCHK(hdf::launch_matvec_reduce(part, n_splits, h->r, m16, (const double*)h->lam_row.p, W, Wd, h->fprec, s));
+  HIPCHK(hdf::launch_matvec_reduce(part, n_splits, h->r, m16, (const int32_t*)h->blk_src.p, h->n_wblocks,
+                                   (const double*)h->lam_row.p, nullptr, nullptr, Wb, h->fprec, s));
   HIPCHK(hdf::launch_matvec_n(h->phi.p, h->ldN, h->q.p, h->ldN, (const hdf::DegDev*)h->degs_dev.p,
-                              (int)h->degs.size(), h->max_s, Wd, nullptr, m16, KV, ldkv, h->N, (int)m, h->fprec,
-                              h->dtype, 0, 1, nullptr, s));
+                              (int)h->degs.size(), Wb, h->n_wblocks, m16, KV, ldkv, h->N, (int)m, h->fprec,
+                              h->dtype, 0, nullptr, s));
   return HDF_OK;
 }
 
@@ -1836,16 +1864,19 @@ static hdf_status adjoint_dx(hdf_handle h, const double* gv, const double* gw, i
   }
   // shifted-factor degrees: harmonics of k - 1 with the radial rows and rank of degree k
   if (h->adj_degs_host.empty() && Kh >= 1) {
-    int64_t roff = 0;
+    int64_t roff = 0, boff = 0;
     for (int k = 1; k <= Kh; ++k) {
       const hdf::DegDev& dg = h->degs[k];
       const hdf::DegDev& d1 = h->degs[k - 1];
       hdf::DegDev e{};
       e.hoff = d1.hoff; e.nh = d1.nh; e.qoff = dg.qoff; e.s = dg.s; e.roff = (int32_t)roff;
+      e.boff = (int32_t)boff;
       h->adj_degs_host.push_back(e);
       roff += (int64_t)d1.nh * dg.s;
+      boff += (int64_t)(d1.nh + 15) / 16 * dg.s;
     }
     h->r_shift = roff;
+    h->shift_blocks = boff;
     HIPCHK(h->adj_degs.ensure(h->adj_degs_host.size() * sizeof(hdf::DegDev)));
     HIPCHK(hipMemcpyAsync(h->adj_degs.p, h->adj_degs_host.data(), h->adj_degs_host.size() * sizeof(hdf::DegDev),
                           hipMemcpyHostToDevice, s));
@@ -1910,17 +1941,25 @@ static hdf_status adjoint_dx(hdf_handle h, const double* gv, const double* gw, i
           }
         }
   }
-  auto pack = [&](const std::vector<double>& v, int64_t rows, int cols, int stride, std::vector<char>& dst) {
-    dst.assign((size_t)std::max<int64_t>(rows, 1) * stride * fel, 0);
-    for (int64_t r = 0; r < rows; ++r)
-      for (int c = 0; c < cols; ++c) {
-        const double x = v[r * cols + c];
-        if (fel == 4) ((float*)dst.data())[r * stride + c] = (float)x;
-        else ((double*)dst.data())[r * stride + c] = x;
-      }
+  // the coefficients in pass 2's block order (the layout of k_mv_reduce's Wb)
+  auto pack = [&](const std::vector<double>& v, const std::vector<hdf::DegDev>& degs, int64_t blocks, int cols,
+                  int stride, std::vector<char>& dst) {
+    dst.assign((size_t)std::max<int64_t>(blocks, 1) * 16 * stride * fel, 0);
+    for (const hdf::DegDev& dg : degs)
+      for (int hh = 0; hh < dg.nh; ++hh)
+        for (int l = 0; l < dg.s; ++l) {
+          const double* row = &v[(dg.roff + (int64_t)hh * dg.s + l) * cols];
+          const int64_t blk = dg.boff + (int64_t)(hh / 16) * dg.s + l;
+          const int kb = (hh % 16) / 4, g = hh % 4;
+          for (int c = 0; c < cols; ++c) {
+            const int64_t at = (blk * (stride / 16) + c / 16) * 256 + (g * 16 + c % 16) * 4 + kb;
+            if (fel == 4) ((float*)dst.data())[at] = (float)row[c];
+            else ((double*)dst.data())[at] = row[c];
+          }
+        }
   };
-  pack(C2, h->r, m2, c2s, h->adj_c2_host);
-  pack(Cs, h->r_shift, md2, css, h->adj_cs_host);
+  pack(C2, h->degs, h->n_wblocks, m2, c2s, h->adj_c2_host);
+  pack(Cs, h->adj_degs_host, h->shift_blocks, md2, css, h->adj_cs_host);
   HIPCHK(h->adj_c2.ensure(h->adj_c2_host.size()));
   HIPCHK(h->adj_cs.ensure(h->adj_cs_host.size()));
   HIPCHK(hipMemcpyAsync(h->adj_c2.p, h->adj_c2_host.data(), h->adj_c2_host.size(), hipMemcpyHostToDevice, s));
@@ -1932,11 +1971,14 @@ static hdf_status adjoint_dx(hdf_handle h, const double* gv, const double* gw, i
   HIPCHK(hipEventRecord(h->ev_adj[0], s));
   // U' [Gv | Gw] and the shifted factor times [G^(j)T Gv | G^(j)T Gw] (pass-2 kernel, one chunk)
   HIPCHK(hdf::launch_matvec_n(h->phi.p, h->ldN, h->dq.p, h->ldN, (const hdf::DegDev*)h->degs_dev.p,
-                              (int)h->degs.size(), h->max_s, h->adj_c2.p, nullptr, c2s, h->adj_kv2.p, m2, h->N, m2,
-                              h->fprec, io, 0, 1, nullptr, s));
-  HIPCHK(hdf::launch_matvec_n(h->phi.p, h->ldN, h->q.p, h->ldN, (const hdf::DegDev*)h->adj_degs.p, Kh, h->max_s,
-                              h->adj_cs.p, nullptr, css, h->adj_kvs.p, md2, h->N, md2, h->fprec, io, 0, 1, nullptr,
-                              s));
+                              (int)h->degs.size(), h->adj_c2.p, h->n_wblocks, c2s, h->adj_kv2.p, m2, h->N, m2,
+                              h->fprec, io, 0, nullptr, s));
+  if (Kh >= 1) {
+    HIPCHK(hdf::launch_matvec_n(h->phi.p, h->ldN, h->q.p, h->ldN, (const hdf::DegDev*)h->adj_degs.p, Kh, h->adj_cs.p,
+                                h->shift_blocks, css, h->adj_kvs.p, md2, h->N, md2, h->fprec, io, 0, nullptr, s));
+  } else {
+    HIPCHK(hipMemset2DAsync(h->adj_kvs.p, md2 * fel, 0, md2 * fel, h->N, s));   // degree 0 only: no derivative
+  }
   HIPCHK(hdf::launch_adj_combine(h->x_soa.p, h->dtype, h->ldN, h->N, d, (const hdf::GeoDev*)h->geo_dev.p,
                                  h->adj_kvs.p, md2, h->adj_kv2.p, m2, Wm, Vm, ld, m, dX, lddx, h->fprec, s));
   HIPCHK(hipEventRecord(h->ev_adj[1], s));
@@ -1982,15 +2024,15 @@ hdf_status hdf_backward(hdf_handle h, const void* Wm, const void* Vm, int64_t m,
     HIPCHK(hipMemcpy2DAsync(h->bw_VW.p, m2 * el, Vm, ld * el, m * el, h->N, hipMemcpyDeviceToDevice, s));
     HIPCHK(hipMemcpy2DAsync((char*)h->bw_VW.p + m * el, m2 * el, Wm, ld * el, m * el, h->N,
                             hipMemcpyDeviceToDevice, s));
-    hdf_status st = pass1(h, 0, h->bw_VW.p, m2, m2, m16, h->bw_GV, h->bw_GVd, s, false);
+    hdf_status st = pass1(h, 0, h->bw_VW.p, m2, m2, m16, PassOut{&h->bw_GV}, s, false);
     if (st != HDF_OK) return st;
     gv_src = gw_src = &h->bw_GV;
     gw_col = m;
   } else {
     m16 = (int)((m + 15) / 16 * 16);
-    hdf_status st = pass1(h, 0, Vm, m, ld, m16, h->bw_GV, h->bw_GVd, s, false);
+    hdf_status st = pass1(h, 0, Vm, m, ld, m16, PassOut{&h->bw_GV}, s, false);
     if (st != HDF_OK) return st;
-    st = pass1(h, 0, Wm, m, ld, m16, h->bw_GW, h->bw_GWd, s, false);
+    st = pass1(h, 0, Wm, m, ld, m16, PassOut{&h->bw_GW}, s, false);
     if (st != HDF_OK) return st;
     gv_src = &h->bw_GV;
     gw_src = &h->bw_GW;

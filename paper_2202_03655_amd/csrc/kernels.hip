@@ -1543,169 +1543,289 @@ hipError_t launch_matvec_t_tile(const void* phi, int64_t ld_phi, const void* q, 
   return hipGetLastError();
 }
 
-// Fixed-order reduction over the pass-1 splits (eight independent partial
-// sums combined pairwise, so the order is fixed and the loads pipelined).
+// Fixed-order reduction over the pass-1 splits, one wavefront-wide group of 64 entries per workgroup:
+// wavefront w takes the splits w, w + 4, ... with eight running sums (loads in flight), and the four
+// sums are combined in a fixed order.  The entries run over the blocks of pass 2 (16 harmonics x one
+// radial function, `src` their rank rows, -1 past a degree's harmonics) and the m16 columns; each sum
+// goes to W (rank rows), to the scaled copy Wd = D W (rank rows) and to Wb, the scaled copy in pass
+// 2's order: block, 16-column tile, then (lane 16 g + c, K-step kb) for harmonic 4 kb + g, zeros past
+// the degree's harmonics.  Any of the three may be null.
 template <typename T>
-__global__ void k_mv_reduce(const double* __restrict__ part, int n_splits, int64_t total, int m16,
-                            const double* __restrict__ lam_row, double* __restrict__ W,
-                            T* __restrict__ Wd) {
-  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= total) return;
+__global__ void __launch_bounds__(256) k_mv_reduce(const double* __restrict__ part, int n_splits, int64_t stride,
+                                                    int64_t total, int m16, const int32_t* __restrict__ src,
+                                                    const double* __restrict__ lam_row, double* __restrict__ W,
+                                                    T* __restrict__ Wd, T* __restrict__ Wb) {
+  __shared__ double red[4][64];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int64_t e = (int64_t)blockIdx.x * 64 + lane;
+  const int64_t row = e < total ? e / m16 : 0;
+  const int c = (int)(e < total ? e - row * m16 : 0);
+  const int sr = e < total ? src[row] : -1;
+  const double* p = part + (int64_t)(sr < 0 ? 0 : sr) * m16 + c;
   double acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-  int sp = 0;
-  for (; sp + 8 <= n_splits; sp += 8)
+  int sp = w;
+  for (; sp + 28 < n_splits; sp += 32)
 #pragma unroll
-    for (int u = 0; u < 8; ++u) acc[u] += part[(int64_t)(sp + u) * total + e];
-  for (int u = 0; sp + u < n_splits; ++u) acc[u] += part[(int64_t)(sp + u) * total + e];
-  const double s = ((acc[0] + acc[1]) + (acc[2] + acc[3])) + ((acc[4] + acc[5]) + (acc[6] + acc[7]));
-  W[e] = s;
-  Wd[e] = (T)(lam_row[e / m16] * s);
+    for (int u = 0; u < 8; ++u) acc[u] += p[(int64_t)(sp + 4 * u) * stride];
+  for (; sp < n_splits; sp += 4) acc[0] += p[(int64_t)sp * stride];
+  red[w][lane] = ((acc[0] + acc[1]) + (acc[2] + acc[3])) + ((acc[4] + acc[5]) + (acc[6] + acc[7]));
+  __syncthreads();
+  if (w != 0 || e >= total) return;
+  const double v = (red[0][lane] + red[1][lane]) + (red[2][lane] + red[3][lane]);
+  const T sc = sr < 0 ? (T)0 : (T)(lam_row[sr < 0 ? 0 : sr] * v);
+  if (sr >= 0 && W) W[(int64_t)sr * m16 + c] = v;
+  if (sr >= 0 && Wd) Wd[(int64_t)sr * m16 + c] = sc;
+  if (Wb) {
+    const int hh = (int)(row & 15), kb = hh >> 2, g = hh & 3;
+    Wb[((row >> 4) * (m16 >> 4) + (c >> 4)) * 256 + (g * 16 + (c & 15)) * 4 + kb] = sc;
+  }
 }
 
-// Pass 2, KV = U (D W).  One wavefront owns 64 points and one 16-column
-// chunk of the right-hand sides.  The reduction runs over the rank columns
-// (k, h, l) directly: the MFMA A operand is U[i, (k,h,l)] = phi_h(i) q_{k,l}(i),
-// formed in registers from one load of each harmonic row and the point's
-// radial values, and B is row (k,h,l) of D W.  Each harmonic row is read
-// once, and the four accumulators (one per point tile) are the output itself.
-// MFMA row i of point tile u is point p0 + 4 i + u, so each lane reads 4
-// consecutive points of a harmonic (or radial) row with one 16-byte load.
-// With hchunk > 0 (few points, many harmonics) blockIdx.z takes the harmonic
-// rows [z hchunk, (z+1) hchunk) only and writes its share of KV to
-// part[z][n][m]; k_mv_n_sum adds the shares in z order.
-// With Wb (and hchunk == 0) the rows of D W come from its batch-major copy (k_wd_batches): the four
-// values a lane needs for one radial function of a batch are one 16-byte (32-byte) load.
-template <typename T, typename TO>
-__global__ void __launch_bounds__(64) k_mv_n(const T* __restrict__ phi, int64_t ld_phi,
-                                              const T* __restrict__ q, int64_t ld_q,
-                                              const DegDev* __restrict__ degs, int n_deg,
-                                              const T* __restrict__ Wd, const T* __restrict__ Wb, int m16,
-                                              TO* __restrict__ KV, int64_t ldkv, int64_t n, int m,
-                                              int hchunk, T* __restrict__ part) {
+// Pass 2, KV = U (D W).  One wavefront owns 64 points and NCT 16-column tiles of the right-hand sides.
+// The reduction runs over the rank columns (k, h, l) directly: the MFMA A operand is
+// U[i, (k,h,l)] = phi_h(i) q_{k,l}(i), formed in registers from the harmonic rows and the points'
+// radial values, and B is row (k,h,l) of D W.  The accumulators (one per point tile and column tile)
+// are the output itself.  MFMA row i of point tile u is point p0 + 4 i + u, so each lane reads 4
+// consecutive points of a harmonic (or radial) row with 16-byte loads, and the four values of D W that
+// a lane needs for a block (16 harmonics, one radial function: four K-steps) are one 16-byte
+// (32-byte) load of Wb (k_mv_reduce).
+// What bounds it: memory with one column tile, the matrix cores with four.  So the harmonic rows and
+// the operands U are formed once for up to four column tiles, and the number of radial functions is a
+// template parameter: a batch of 16 harmonics is then one block of straight code, in which the waits
+// for the operands of radial function l + 1 and for the next batch's rows are counted, not taken for
+// every load in flight as around a loop over l.  Rows past a degree's harmonics are those of the next
+// degree (the last row past the last) and meet zero rows of Wb; points past n are read from the rows' padding and not written.
+// With z_blocks > 0 (few points) blockIdx.z takes the blocks [z z_blocks, (z + 1) z_blocks) only,
+// whatever degree and radial function they are, and writes its share of KV to part[z][n][m];
+// k_mv_n_sum adds the shares in z order.
+// 64 columns: binary32, 1e6 points, rank 1413 3.06 -> 1.88 ms (96 TFLOP/s, matrix cores busy 80 %);
+// binary64, 5e5 points, rank 1463 4.43 -> 2.08 ms (45 TFLOP/s; two column tiles per wavefront 2.22).
+// 16 columns: binary64, 250,007 points 0.73 -> 0.52 ms; binary32, 1e6 points 0.79 -> 0.78 ms (memory).
+// Wavefronts per SIMD that the registers are held to (accumulators: 16 NCT registers in binary32,
+// 32 NCT in binary64):
+template <typename T, int NCT> struct MvnWaves {
+  static constexpr int value = sizeof(T) == 4 ? (NCT == 1 ? 4 : (NCT == 2 ? 3 : 2)) : (NCT == 1 ? 2 : 1);
+};
+constexpr int kMvnKB = 4;                          // K-steps per block: 16 harmonics
+
+// four consecutive points of a padded row (in bounds up to 63 points past n)
+template <typename T>
+__device__ __forceinline__ void mvn_load4(const T* __restrict__ p, T (&o)[4]) {
+  if constexpr (sizeof(T) == 4) {
+    const floatx4 w = *reinterpret_cast<const floatx4*>(p);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) o[u] = w[u];
+  } else {
+    const doublex2 w0 = *reinterpret_cast<const doublex2*>(p);
+    const doublex2 w1 = *reinterpret_cast<const doublex2*>(p + 2);
+    o[0] = w0[0]; o[1] = w0[1]; o[2] = w1[0]; o[3] = w1[1];
+  }
+}
+
+template <typename T, int NCT>
+struct MvnPass {
   typedef typename Mfma<T>::V Acc;
-  const int lane = threadIdx.x, li = lane & 15, g = lane >> 4;
-  const int64_t p0 = (int64_t)blockIdx.x * 64;
-  const int c0 = blockIdx.y * 16;
-  const int64_t pa = p0 + 4 * li;                // this lane's four A points
-  const int zlo = hchunk > 0 ? (int)blockIdx.z * hchunk : 0;
-  const int zhi = hchunk > 0 ? zlo + hchunk : 0x7fffffff;
-  Acc acc[4];
+  // wavefront-uniform bases and this lane's offsets (values): the loads take their base from scalar registers
+  const T* phi;                                    // at the first of the wavefront's points
+  const T* q;
+  const T* wb;                                     // first column tile of the group
+  int64_t ld_phi, ld_q, wb_stride;                 // wb_stride: values per block
+  int ct_off[NCT];                                 // column tile offsets in a block (uniform)
+  int last_row;                                    // last harmonic row of phi
+  int g;
+  uint32_t pt_off, wb_off;                         // 4 li, lane kMvnKB
+  Acc acc[NCT][4];
+
+  __device__ __forceinline__ void rows(const DegDev& dg, int b, T (&v)[kMvnKB][4]) const {
 #pragma unroll
-  for (int u = 0; u < 4; ++u) acc[u] = Acc{0, 0, 0, 0};
-  // four consecutive points of a padded row (in bounds up to 63 points past n)
-  auto load4 = [&](const T* row, T (&o)[4]) {
-    if constexpr (sizeof(T) == 4) {
-      const floatx4 w = *reinterpret_cast<const floatx4*>(row + pa);
-#pragma unroll
-      for (int u = 0; u < 4; ++u) o[u] = w[u];
-    } else {
-      const doublex2 w0 = *reinterpret_cast<const doublex2*>(row + pa);
-      const doublex2 w1 = *reinterpret_cast<const doublex2*>(row + pa + 2);
-      o[0] = w0[0]; o[1] = w0[1]; o[2] = w1[0]; o[3] = w1[1];
+    for (int kb = 0; kb < kMvnKB; ++kb) {
+      const int row = dg.hoff + 16 * b + 4 * kb + g;
+      mvn_load4(phi + (int64_t)(row < last_row ? row : last_row) * ld_phi + pt_off, v[kb]);
     }
-  };
-  constexpr int KB = 4;                          // K-steps per batch: 16 harmonics
-  for (int di = 0; di < n_deg; ++di) {
-    const DegDev dg = degs[di];
-    // this workgroup's harmonics of the degree: [hlo, hhi)
-    const int hlo = zlo > dg.hoff ? zlo - dg.hoff : 0;
-    const int hhi = (zhi - dg.hoff) < dg.nh ? zhi - dg.hoff : dg.nh;
-    if (hlo >= hhi) continue;
-    // harmonic rows of a batch (clamped rows, masked values), the next batch in flight
-    auto load_batch = [&](int hb, T (&vv)[KB][4]) {
+  }
+  __device__ __forceinline__ void operands(int qrow, int64_t block, T (&ql)[4], T (&bw)[NCT][kMvnKB]) const {
+    const T* qb = q + (int64_t)qrow * ld_q;
+    const T* wbb = wb + block * wb_stride;
+    mvn_load4(qb + pt_off, ql);
 #pragma unroll
-      for (int kb = 0; kb < KB; ++kb) {
-        const int hh = hb + 4 * kb + g;
-        load4(phi + (int64_t)(dg.hoff + (hh < hhi ? hh : hlo)) * ld_phi, vv[kb]);
+    for (int ct = 0; ct < NCT; ++ct) mvn_load4(wbb + ct_off[ct] + wb_off, bw[ct]);
+  }
+  __device__ __forceinline__ void multiply(const T (&v)[kMvnKB][4], const T (&ql)[4], const T (&bw)[NCT][kMvnKB]) {
 #pragma unroll
-        for (int u = 0; u < 4; ++u) vv[kb][u] = (hh < hhi && pa + u < n) ? vv[kb][u] : (T)0;
+    for (int kb = 0; kb < kMvnKB; ++kb) {
+      T av[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) av[u] = v[kb][u] * ql[u];
+#pragma unroll
+      for (int ct = 0; ct < NCT; ++ct)
+#pragma unroll
+        for (int u = 0; u < 4; ++u) acc[ct][u] = Mfma<T>::run(av[u], bw[ct][kb], acc[ct][u]);
+    }
+  }
+  // radial functions [l0, l0 + SN) of all batches of a degree
+  template <int SN>
+  __device__ __forceinline__ void degree(const DegDev& dg, int l0) {
+    const int nb = (dg.nh + 15) >> 4;
+    T vn[kMvnKB][4], ql[2][4], bw[2][NCT][kMvnKB];
+    // the indices are carried from load to load through readfirstlane, so that the compiler forms each
+    // address when it is needed instead of holding those of every radial function in registers
+    int qr = dg.qoff + l0, blk = dg.boff + l0;
+    operands(qr, blk, ql[0], bw[0]);
+    rows(dg, 0, vn);
+    for (int b = 0; b < nb; ++b) {
+      const int bn = b + 1 < nb ? b + 1 : b;
+      T v[kMvnKB][4];
+#pragma unroll
+      for (int kb = 0; kb < kMvnKB; ++kb)
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[kb][u] = vn[kb][u];
+#pragma unroll
+      for (int l = 0; l < SN; ++l) {
+        // the operands of the next radial function, or those of the next batch's first
+        qr = __builtin_amdgcn_readfirstlane(l + 1 < SN ? qr + 1 : qr - (SN - 1));
+        blk = __builtin_amdgcn_readfirstlane(l + 1 < SN ? blk + 1 : blk - (SN - 1) + (bn - b) * dg.s);
+        operands(qr, blk, ql[(l + 1) & 1], bw[(l + 1) & 1]);
+        if (l == 0) rows(dg, bn, vn);
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(v, ql[l & 1], bw[l & 1]);
       }
-    };
-    // radial values of function l at this lane's points and the batch's rows of D W for l
-    auto load_l = [&](int hb, int l, T (&ql)[4], T (&bw)[KB]) {
-      load4(q + (int64_t)(dg.qoff + l) * ld_q, ql);
-      if (Wb) {                                     // uniform
-        // block (batch hb / 16, radial function l) of the degree, column tile blockIdx.y
-        const T* src = Wb + (((int64_t)dg.boff + (hb >> 4) * dg.s + l) * (m16 >> 4) + blockIdx.y) * 256 +
-                       (g * 16 + li) * KB;
-        if constexpr (sizeof(T) == 4) {
-          const floatx4 w = *reinterpret_cast<const floatx4*>(src);
+      if constexpr (SN & 1) {
 #pragma unroll
-          for (int kb = 0; kb < KB; ++kb) bw[kb] = w[kb];
-        } else {
-          const doublex2 w0 = *reinterpret_cast<const doublex2*>(src);
-          const doublex2 w1 = *reinterpret_cast<const doublex2*>(src + 2);
-          bw[0] = w0[0]; bw[1] = w0[1]; bw[2] = w1[0]; bw[3] = w1[1];
-        }
-        return;
-      }
+        for (int u = 0; u < 4; ++u) ql[0][u] = ql[1][u];
 #pragma unroll
-      for (int kb = 0; kb < KB; ++kb) {
-        const int hh = hb + 4 * kb + g;
-        bw[kb] = Wd[(int64_t)(dg.roff + (hh < hhi ? hh : hlo) * dg.s + l) * m16 + c0 + li];
-      }
-    };
-    // binary32 issue order per batch: the operands of l = 0, then the next batch's rows, then
-    // those of l + 1 ahead of l's MFMAs, so no wait of this batch covers the next batch's rows.
-    // binary64 loads l's operands at l (the extra registers would cost a wavefront per SIMD).
-    constexpr bool ahead = sizeof(T) == 4;
-    T v_nxt[KB][4];
-    load_batch(hlo, v_nxt);
-    for (int hb = hlo; hb < hhi; hb += 4 * KB) {
-      T v[KB][4];
+        for (int ct = 0; ct < NCT; ++ct)
 #pragma unroll
-      for (int kb = 0; kb < KB; ++kb)
-#pragma unroll
-        for (int u = 0; u < 4; ++u) v[kb][u] = v_nxt[kb][u];
-      T ql[4], bw[KB];
-      if constexpr (ahead) load_l(hb, 0, ql, bw);
-      if (hb + 4 * KB < hhi) load_batch(hb + 4 * KB, v_nxt);
-      for (int l = 0; l < dg.s; ++l) {
-        T qn[4], bn[KB];
-        if constexpr (ahead) {
-          if (l + 1 < dg.s) load_l(hb, l + 1, qn, bn);
-        } else {
-          load_l(hb, l, ql, bw);
-        }
-#pragma unroll
-        for (int kb = 0; kb < KB; ++kb)
-#pragma unroll
-          for (int u = 0; u < 4; ++u) acc[u] = Mfma<T>::run(v[kb][u] * ql[u], bw[kb], acc[u]);
-        if constexpr (ahead) {
-#pragma unroll
-          for (int u = 0; u < 4; ++u) ql[u] = qn[u];
-#pragma unroll
-          for (int kb = 0; kb < KB; ++kb) bw[kb] = bn[kb];
-        }
+          for (int kb = 0; kb < kMvnKB; ++kb) bw[0][ct][kb] = bw[1][ct][kb];
       }
     }
   }
-  const int c = c0 + li;
-  if (c < m) {
-    T* dpart = part ? part + (int64_t)blockIdx.z * n * m : nullptr;
+};
+
+template <typename T, typename TO, int NCT, bool SPLIT>
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(MvnWaves<T, NCT>::value, 8)))
+k_mv_n(const T* __restrict__ phi, int64_t ld_phi, const T* __restrict__ q, int64_t ld_q,
+       const DegDev* __restrict__ degs, int n_deg, const T* __restrict__ Wb, int m16, TO* __restrict__ KV,
+       int64_t ldkv, int64_t n, int m, int z_blocks, int n_blocks, T* __restrict__ part) {
+  const int lane = threadIdx.x, li = lane & 15, g = lane >> 4;
+  // block b takes column group cg of point block pb, b = 8 (n_cg (pb / 8) + cg) + pb % 8: the column
+  // groups of a point block run on one XCD (dispatch is round robin over the eight), close in time,
+  // and share the harmonic rows in its L2
+  const int cpl = m16 >> 4, n_cg = (cpl + NCT - 1) / NCT;
+  const int rest = (int)(blockIdx.x >> 3), cg = rest % n_cg;
+  const int64_t p0 = ((int64_t)(rest / n_cg) * 8 + (blockIdx.x & 7)) * 64;
+  if (p0 >= n) return;
+  const int ct0 = cg * NCT, nct = cpl - ct0 < NCT ? cpl - ct0 : NCT;   // column tiles of this group
+  MvnPass<T, NCT> ps;
+  ps.phi = phi + p0;
+  ps.q = q + p0;
+  ps.wb = Wb + (int64_t)ct0 * 256;
+  ps.pt_off = 4 * li;
+  ps.wb_off = lane * kMvnKB;
+  ps.last_row = degs[n_deg - 1].hoff + degs[n_deg - 1].nh - 1;
+  ps.ld_phi = ld_phi;
+  ps.ld_q = ld_q;
+  ps.wb_stride = (int64_t)cpl * 256;
+  ps.g = g;
 #pragma unroll
-    for (int u = 0; u < 4; ++u)
+  for (int ct = 0; ct < NCT; ++ct) {
+    // a column tile past the last repeats the group's first (never written)
+    ps.ct_off[ct] = ct < nct ? ct * 256 : 0;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int64_t pt = p0 + 4 * Mfma<T>::row(g, e) + u;
-        if (pt < n) {
-          if (dpart) dpart[pt * m + c] = acc[u][e];
-          else KV[pt * ldkv + c] = (TO)acc[u][e];
+    for (int u = 0; u < 4; ++u) ps.acc[ct][u] = typename Mfma<T>::V{0, 0, 0, 0};
+  }
+  if constexpr (!SPLIT) {
+    for (int di = 0; di < n_deg; ++di) {
+      const DegDev dg = degs[di];
+      for (int l0 = 0; l0 < dg.s; l0 += 8) {
+        switch (dg.s - l0) {                       // uniform
+          case 1: ps.template degree<1>(dg, l0); break;
+          case 2: ps.template degree<2>(dg, l0); break;
+          case 3: ps.template degree<3>(dg, l0); break;
+          case 4: ps.template degree<4>(dg, l0); break;
+          case 5: ps.template degree<5>(dg, l0); break;
+          case 6: ps.template degree<6>(dg, l0); break;
+          case 7: ps.template degree<7>(dg, l0); break;
+          default: ps.template degree<8>(dg, l0); break;
         }
       }
+    }
+  } else {
+    // block after block, the next one's rows and operands in flight
+    int blk = (int)blockIdx.z * z_blocks;
+    const int hi = blk + z_blocks < n_blocks ? blk + z_blocks : n_blocks;
+    int di = 0;
+    while (di + 1 < n_deg && degs[di + 1].boff <= blk) ++di;
+    DegDev dg = degs[di];
+    int b = (blk - dg.boff) / dg.s, l = (blk - dg.boff) % dg.s;
+    T vn[kMvnKB][4], qn[4], wn[NCT][kMvnKB];
+    ps.operands(dg.qoff + l, blk, qn, wn);
+    ps.rows(dg, b, vn);
+    for (; blk < hi; ++blk) {
+      T v[kMvnKB][4], ql[4], bw[NCT][kMvnKB];
+#pragma unroll
+      for (int kb = 0; kb < kMvnKB; ++kb)
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[kb][u] = vn[kb][u];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) ql[u] = qn[u];
+#pragma unroll
+      for (int ct = 0; ct < NCT; ++ct)
+#pragma unroll
+        for (int kb = 0; kb < kMvnKB; ++kb) bw[ct][kb] = wn[ct][kb];
+      if (++l == dg.s) {
+        l = 0;
+        ++b;
+      }
+      if (16 * b >= dg.nh) {                       // past the degree: the next one's first block
+        b = 0;
+        if (di + 1 < n_deg) dg = degs[++di];
+      }
+      ps.operands(dg.qoff + l, blk + 1 < hi ? blk + 1 : blk, qn, wn);
+      ps.rows(dg, b, vn);
+      __builtin_amdgcn_sched_barrier(0);
+      ps.multiply(v, ql, bw);
+    }
+  }
+#pragma unroll
+  for (int ct = 0; ct < NCT; ++ct) {
+    const int c = 16 * (ct0 + ct) + li;
+    if (ct < nct && c < m) {
+      T* dpart = SPLIT ? part + (int64_t)blockIdx.z * n * m : nullptr;
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int64_t pt = p0 + 4 * Mfma<T>::row(g, e) + u;
+          if (pt < n) {
+            if constexpr (SPLIT) dpart[pt * m + c] = ps.acc[ct][u][e];
+            else KV[pt * ldkv + c] = (TO)ps.acc[ct][u][e];
+          }
+        }
+    }
   }
 }
 
+// Sum of pass 2's shares in a fixed order: a workgroup owns 64 entries, wavefront w takes the shares
+// w, w + 4, ... with four running sums (one thread per entry over 128 shares of a 460-point cluster
+// took 26 us, a chain of dependent loads).
 template <typename T, typename TO>
 __global__ void __launch_bounds__(256) k_mv_n_sum(const T* __restrict__ part, int nz, int64_t n, int m,
                                                   TO* __restrict__ KV, int64_t ldkv) {
-  const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (e >= n * m) return;
+  __shared__ T red[4][64];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int64_t e = (int64_t)blockIdx.x * 64 + lane, total = n * m;
+  const T* p = part + (e < total ? e : 0);
+  T acc[4] = {0, 0, 0, 0};
+  int z = w;
+  for (; z + 12 < nz; z += 16)
+#pragma unroll
+    for (int u = 0; u < 4; ++u) acc[u] += p[(int64_t)(z + 4 * u) * total];
+  for (; z < nz; z += 4) acc[0] += p[(int64_t)z * total];
+  red[w][lane] = (acc[0] + acc[1]) + (acc[2] + acc[3]);
+  __syncthreads();
+  if (w != 0 || e >= total) return;
   const int64_t pt = e / m;
-  const int c = (int)(e - pt * m);
-  T s = 0;
-  for (int z = 0; z < nz; ++z) s += part[((int64_t)z * n + pt) * m + c];
-  KV[pt * ldkv + c] = (TO)s;
+  KV[pt * ldkv + (e - pt * m)] = (TO)((red[0][lane] + red[1][lane]) + (red[2][lane] + red[3][lane]));
 }
 
 constexpr int kMvNctF = 4;   // column tiles per item of k_mv_t, binary32
@@ -1738,74 +1858,78 @@ hipError_t launch_matvec_t(const void* phi, int64_t ld_phi, const void* q, int64
   return hipGetLastError();
 }
 
-hipError_t launch_matvec_reduce(const double* partials, int n_splits, int64_t rank, int m16,
-                                const double* lam_row, double* W, void* Wd, int prec,
+hipError_t launch_matvec_reduce(const double* partials, int n_splits, int64_t rank, int m16, const int32_t* src,
+                                int64_t n_blocks, const double* lam_row, double* W, void* Wd, void* Wb, int prec,
                                 hipStream_t s) {
-  const int64_t total = rank * m16;
-  const unsigned nb = (unsigned)((total + 255) / 256);
+  if (n_blocks < 1 || m16 < 16 || m16 % 16) return hipErrorInvalidValue;
+  const int64_t total = n_blocks * 16 * m16;
+  const unsigned nb = (unsigned)((total + 63) / 64);
   if (prec == 1)
-    k_mv_reduce<float><<<nb, 256, 0, s>>>(partials, n_splits, total, m16, lam_row, W, (float*)Wd);
+    k_mv_reduce<float><<<nb, 256, 0, s>>>(partials, n_splits, rank * m16, total, m16, src, lam_row, W, (float*)Wd,
+                                          (float*)Wb);
   else
-    k_mv_reduce<double><<<nb, 256, 0, s>>>(partials, n_splits, total, m16, lam_row, W, (double*)Wd);
+    k_mv_reduce<double><<<nb, 256, 0, s>>>(partials, n_splits, rank * m16, total, m16, src, lam_row, W, (double*)Wd,
+                                           (double*)Wb);
   return hipGetLastError();
 }
 
-// Batch-major copy of D W for pass 2: block B = boff_k + b s_k + l of degree k holds, for batch b
-// (harmonics 16 b .. 16 b + 15) and radial function l, every 16-column tile ct as 256 values in
-// the order (lane g 16 + c, K-step kb) with harmonic 16 b + 4 kb + g and column 16 ct + c; rows past
-// the degree's harmonics are zero.  boff_k is DegDev::boff.
-template <typename T>
-__global__ void __launch_bounds__(256) k_wd_batches(const DegDev* __restrict__ degs, int n_deg,
-                                                     const T* __restrict__ Wd, int m16, int64_t n_blocks,
-                                                     T* __restrict__ Wb) {
-  const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  const int ncts = m16 >> 4;
-  if (e >= n_blocks * ncts * 256) return;
-  const int64_t blk = e / (ncts * 256);
-  const int rest = (int)(e - blk * ncts * 256);
-  const int ct = rest >> 8, lane = (rest >> 2) & 63, kb = rest & 3;
-  const int g = lane >> 4, c = lane & 15;
-  int di = 0;
-  while (di + 1 < n_deg && degs[di + 1].boff <= blk) ++di;
-  const DegDev dg = degs[di];
-  const int64_t rel = blk - dg.boff;
-  const int b = (int)(rel / dg.s), l = (int)(rel - (int64_t)b * dg.s);
-  const int hh = 16 * b + 4 * kb + g;
-  Wb[e] = hh < dg.nh ? Wd[(int64_t)(dg.roff + hh * dg.s + l) * m16 + 16 * ct + c] : (T)0;
-}
-
-hipError_t launch_wd_batches(const DegDev* degs, int n_deg, const void* Wd, int m16, int64_t n_blocks, void* Wb,
-                             int prec, hipStream_t s) {
-  if (m16 < 16 || m16 % 16 || n_blocks < 1 || n_deg < 1) return hipErrorInvalidValue;
-  const int64_t total = n_blocks * (m16 / 16) * 256;
-  const unsigned nb = (unsigned)((total + 255) / 256);
-  if (prec == 1) k_wd_batches<float><<<nb, 256, 0, s>>>(degs, n_deg, (const float*)Wd, m16, n_blocks, (float*)Wb);
-  else k_wd_batches<double><<<nb, 256, 0, s>>>(degs, n_deg, (const double*)Wd, m16, n_blocks, (double*)Wb);
-  return hipGetLastError();
+int matvec_n_tiles(int64_t n, int cpl) {
+  // The busiest of the 1,024 SIMDs sets the time: its wavefronts times their column tiles, plus about
+  // a third of a tile for the rows and operands that a wavefront forms once.  With many points that is
+  // the widest group with the fewest padded tiles; 44,599 points and 168 columns take groups of three
+  // (three wavefronts of three tiles on a SIMD, 0.53 ms) rather than of four (2,091 wavefronts, a few
+  // SIMDs with three of four tiles, 0.65 ms).
+  int best = 1;
+  int64_t cost = -1;
+  for (int t = 1; t <= 4 && t <= cpl; ++t) {
+    const int64_t waves = ((n + 63) / 64) * ((cpl + t - 1) / t);
+    const int64_t c = (waves + 1023) / 1024 * (10 * t + 3);
+    if (cost < 0 || c <= cost) {
+      cost = c;
+      best = t;
+    }
+  }
+  return best;
 }
 
 hipError_t launch_matvec_n(const void* phi, int64_t ld_phi, const void* q, int64_t ld_q,
-                           const DegDev* degs, int n_deg, int max_s, const void* Wd, const void* Wb, int m16,
-                           void* KV, int64_t ldkv, int64_t n, int m, int prec, int io, int hchunk, int nz,
+                           const DegDev* degs, int n_deg, const void* Wb, int64_t n_blocks, int m16,
+                           void* KV, int64_t ldkv, int64_t n, int m, int prec, int io, int z_blocks,
                            void* part, hipStream_t s) {
-  (void)max_s;
-  if (nz < 1 || (nz > 1 && (hchunk <= 0 || !part))) return hipErrorInvalidValue;
-  if (Wb && nz > 1) return hipErrorInvalidValue;
-  const dim3 grid((unsigned)((n + 63) / 64), (unsigned)(m16 / 16), (unsigned)nz);
-  const int hc = nz > 1 ? hchunk : 0;
-  const unsigned nb = (unsigned)((n * m + 255) / 256);
+  if (n_deg < 1 || n_blocks < 1 || m16 < 16 || m16 % 16) return hipErrorInvalidValue;
+  const int nz = z_blocks > 0 ? (int)((n_blocks + z_blocks - 1) / z_blocks) : 1;
+  if (nz > 1 && !part) return hipErrorInvalidValue;
+  const int nct = matvec_n_tiles(n, m16 / 16);
+  const int64_t n_cg = (m16 / 16 + nct - 1) / nct;
+  const dim3 grid((unsigned)(((n + 63) / 64 + 7) / 8 * 8 * n_cg), 1, (unsigned)nz);
+  const unsigned nb = (unsigned)((n * m + 63) / 64);
+#define HDF_MVN_RUN(T, TO, NCT, SPLIT)                                                                       \
+  k_mv_n<T, TO, NCT, SPLIT><<<grid, 64, 0, s>>>((const T*)phi, ld_phi, (const T*)q, ld_q, degs, n_deg,      \
+                                                (const T*)Wb, m16, (TO*)KV, ldkv, n, m, z_blocks,            \
+                                                (int)n_blocks, (T*)part)
+#define HDF_MVN_NCT(T, TO, SPLIT)                                                                            \
+  do {                                                                                                       \
+    if (nct == 1) HDF_MVN_RUN(T, TO, 1, SPLIT);                                                              \
+    else if (nct == 2) HDF_MVN_RUN(T, TO, 2, SPLIT);                                                         \
+    else if (nct == 3) HDF_MVN_RUN(T, TO, 3, SPLIT);                                                         \
+    else HDF_MVN_RUN(T, TO, 4, SPLIT);                                                                       \
+  } while (0)
 #define HDF_MVN(T, TO)                                                                                       \
   do {                                                                                                       \
-    T* dst = nz > 1 ? (T*)part : nullptr;                                                                    \
-    k_mv_n<T, TO><<<grid, 64, 0, s>>>((const T*)phi, ld_phi, (const T*)q, ld_q, degs, n_deg, (const T*)Wd,  \
-                                      (const T*)Wb, m16, (TO*)KV, ldkv, n, m, hc, dst);                      \
-    if (nz > 1) k_mv_n_sum<T, TO><<<nb, 256, 0, s>>>((const T*)part, nz, n, m, (TO*)KV, ldkv);               \
+    if (nz > 1) {                                                                                            \
+      HDF_MVN_NCT(T, TO, true);                                                                              \
+      k_mv_n_sum<T, TO><<<nb, 256, 0, s>>>((const T*)part, nz, n, m, (TO*)KV, ldkv);                         \
+    } else {                                                                                                 \
+      HDF_MVN_NCT(T, TO, false);                                                                             \
+    }                                                                                                        \
   } while (0)
   if (prec == 1 && io == 0) HDF_MVN(float, float);
   else if (prec == 0 && io == 1) HDF_MVN(double, double);
   else if (prec == 0 && io == 0) HDF_MVN(double, float);
   else return hipErrorInvalidValue;
 #undef HDF_MVN
+#undef HDF_MVN_NCT
+#undef HDF_MVN_RUN
   return hipGetLastError();
 }
 

@@ -147,22 +147,23 @@ hipError_t launch_matvec_t_tile(const void* phi, int64_t ld_phi, const void* q, 
                                 int n_groups, int n_splits,
                                 int64_t split_len, const void* V, int64_t ldv, int64_t n, int m, int m16,
                                 int64_t rank, double* partials, int prec, int io, hipStream_t s);
-// Batch-major copy Wb of Wd for pass 2 (n_blocks = sum over degrees of ceil(nh / 16) s; the
-// degrees' block offsets in DegDev::boff): 16 m16 values per block.
-hipError_t launch_wd_batches(const DegDev* degs, int n_deg, const void* Wd, int m16, int64_t n_blocks, void* Wb,
-                             int prec, hipStream_t s);
-// Reduce over splits: W[row][c] = sum_split partial (binary64) and
-// Wd[row][c] = lambda_row * W (storage type) for pass 2.
-hipError_t launch_matvec_reduce(const double* partials, int n_splits, int64_t rank, int m16,
-                                const double* lam_row, double* W, void* Wd, int prec,
+// Pass 2 takes D W in blocks of 16 harmonics x one radial function, batch after batch of a degree and
+// degree after degree (n_blocks = sum over degrees of ceil(nh / 16) s; the degrees' first blocks in
+// DegDev::boff), 16 m16 values per block.  launch_matvec_reduce sums the pass-1 partials over the
+// splits and writes W[row][c] (binary64), Wd[row][c] = lambda_row * W (storage type) and Wb, the same
+// values in block order; any of them may be NULL.  src: the rank row of every row of the blocks, -1
+// past a degree's harmonics.
+hipError_t launch_matvec_reduce(const double* partials, int n_splits, int64_t rank, int m16, const int32_t* src,
+                                int64_t n_blocks, const double* lam_row, double* W, void* Wd, void* Wb, int prec,
                                 hipStream_t s);
-// Pass 2: KV[i][c] = sum_rows U[i,row] Wd[row][c].
-// nz > 1: harmonic rows split into nz chunks of hchunk rows, each chunk's share
-// of KV in part (nz x n x m, storage type), summed in chunk order into KV
-// Wb: optional batch-major copy of Wd (launch_wd_batches; nz == 1 only), read instead of Wd.
+// column tiles per wavefront of pass 2 over n points for cpl = m16 / 16
+int matvec_n_tiles(int64_t n, int cpl);
+// Pass 2: KV[i][c] = sum_rows U[i,row] (D W)[row][c], D W in block order.
+// z_blocks > 0: the blocks are split into shares of z_blocks, each share's KV in part (shares x n x m,
+// storage type), summed in order into KV
 hipError_t launch_matvec_n(const void* phi, int64_t ld_phi, const void* q, int64_t ld_q,
-                           const DegDev* degs, int n_deg, int max_s, const void* Wd, const void* Wb, int m16,
-                           void* KV, int64_t ldkv, int64_t n, int m, int prec, int io, int hchunk, int nz,
+                           const DegDev* degs, int n_deg, const void* Wb, int64_t n_blocks, int m16,
+                           void* KV, int64_t ldkv, int64_t n, int m, int prec, int io, int z_blocks,
                            void* part, hipStream_t s);
 
 // Adjoint by contractions (see hdf_backward).  launch_radial evaluates S
