@@ -2289,3 +2289,93 @@ hdf_status hdf_plan_index_set(int d, int k, int32_t* table, int64_t* count) {
 }
 
 }  // extern "C"
+
+// ------------------------------------------------------------------ batched products
+namespace hdf {
+
+struct ProductBatch {
+  std::vector<MvBatch> host;     // outlives its upload
+  MvBatchGrid grid{};
+  DevBuf desc, ws;
+  ~ProductBatch() { (void)hipDeviceSynchronize(); }
+};
+
+hdf_status batch_create(const std::vector<hdf_handle>& factors, const std::vector<int64_t>& pos, hipStream_t s,
+                        ProductBatch** out) {
+  std::unique_ptr<ProductBatch> b(new ProductBatch);
+  int live = 0;
+  for (hdf_handle h : factors) {
+    if (!h || h->storage != HDF_STORE_FACTOR || h->cross || h->fprec != 0 || h->dtype != 1)
+      return fail(HDF_E_ARG, "internal: a batched product takes stored symmetric binary64 factors");
+    live += h->r > 0;
+  }
+  size_t at = 0;
+  auto room = [&](size_t values) {
+    const size_t o = at;
+    at += (values + 31) / 32 * 32;
+    return o;
+  };
+  std::vector<size_t> o_part, o_wb, o_sh;
+  for (size_t i = 0; i < factors.size(); ++i) {
+    const hdf_handle h = factors[i];
+    if (h->r == 0) continue;                       // contributes zeros
+    MvBatch f{};
+    f.phi = (const double*)h->phi.p;
+    f.q = (const double*)h->q.p;
+    f.ld = h->ldN;
+    f.n = h->N;
+    f.pos = pos[i];
+    f.rank = h->r;
+    f.n_blocks = h->n_wblocks;
+    f.waves = tile_waves(h, 1);
+    f.rank_rows = tile_rank_rows(h);
+    f.groups = tile_groups(h, 1);
+    f.n_groups = h->n_tgroups[1];
+    f.degs = (const DegDev*)h->degs_dev.p;
+    f.n_deg = (int)h->degs.size();
+    f.src = (const int32_t*)h->blk_src.p;
+    f.lam = (const double*)h->lam_row.p;
+    // the launches of all factors together aim at what one factor's aim at alone (tile_splits, pass2),
+    // twice as many pass-1 workgroups since the factors differ in size
+    int64_t ns = std::max<int64_t>(1, 2048 / std::max(1, live * f.n_groups));
+    ns = std::min<int64_t>(ns, (f.n + 127) / 128);
+    f.split_len = ((f.n + ns - 1) / ns + 127) / 128 * 128;
+    f.n_splits = (int)((f.n + f.split_len - 1) / f.split_len);
+    const int64_t waves = (f.n + 63) / 64;
+    const int64_t want = std::min<int64_t>(std::max<int64_t>(1, kPass2SplitWaves / (waves * live)), f.n_blocks);
+    f.z_blocks = (int)((f.n_blocks + want - 1) / want);
+    f.nz = (int)((f.n_blocks + f.z_blocks - 1) / f.z_blocks);
+    o_part.push_back(room((size_t)f.n_splits * f.rank * 16));
+    o_wb.push_back(room((size_t)f.n_blocks * 256));
+    o_sh.push_back(room((size_t)f.nz * f.n));
+    b->host.push_back(f);
+    MvBatchGrid& g = b->grid;
+    g.t_blocks = std::max(g.t_blocks, (f.n_splits + 7) / 8 * 8 * f.n_groups);
+    g.r_blocks = std::max(g.r_blocks, (int)(f.n_blocks * 4));
+    g.n_blocks = std::max(g.n_blocks, (int)waves);
+    g.shares = std::max(g.shares, f.nz);
+  }
+  b->grid.factors = (int)b->host.size();
+  if (b->grid.factors > 0) {
+    HIPCHK(b->ws.ensure(at * sizeof(double)));
+    HIPCHK(b->desc.ensure(b->host.size() * sizeof(MvBatch)));
+    for (size_t i = 0; i < b->host.size(); ++i) {
+      b->host[i].part = (double*)b->ws.p + o_part[i];
+      b->host[i].Wb = (double*)b->ws.p + o_wb[i];
+      b->host[i].shares = (double*)b->ws.p + o_sh[i];
+    }
+    HIPCHK(hipMemcpyAsync(b->desc.p, b->host.data(), b->host.size() * sizeof(MvBatch), hipMemcpyHostToDevice, s));
+  }
+  *out = b.release();
+  return HDF_OK;
+}
+
+hdf_status batch_run(const ProductBatch* b, const double* v, double* out, hipStream_t s) {
+  if (b->grid.factors == 0) return HDF_OK;
+  HIPCHK(launch_matvec_batch((const MvBatch*)b->desc.p, b->grid, v, out, s));
+  return HDF_OK;
+}
+
+void batch_free(ProductBatch* b) { delete b; }
+
+}  // namespace hdf

@@ -1268,15 +1268,12 @@ constexpr int kMvtVS = kMvtSpan + 4;       // padded staged row (LDS bank spread
 
 
 template <typename T, typename TV, int NCT>
-__global__ void __launch_bounds__(kMvtThreads) __attribute__((amdgpu_waves_per_eu(MvtWaves<T, NCT>::value, 8)))
-k_mv_t_tile(const T* __restrict__ phi, int64_t ld_phi,
-                                                    const T* __restrict__ q, int64_t ld_q,
-                                                    const MvtWave* __restrict__ waves,
-                                                    const MvtRankRow* __restrict__ rrows,
-                                                    const MvtGroup* __restrict__ groups, int n_groups,
-                                                    int n_splits, int64_t split_len,
-                                                    const TV* __restrict__ V, int64_t ldv, int64_t n, int m,
-                                                    int m16, int64_t rank, double* __restrict__ part) {
+__device__ __forceinline__ void mvt_tile(int b, const T* __restrict__ phi, int64_t ld_phi,
+                                         const T* __restrict__ q, int64_t ld_q, const MvtWave* __restrict__ waves,
+                                         const MvtRankRow* __restrict__ rrows, const MvtGroup* __restrict__ groups,
+                                         int n_groups, int n_splits, int64_t split_len, const TV* __restrict__ V,
+                                         int64_t ldv, int64_t n, int m, int m16, int64_t rank,
+                                         double* __restrict__ part) {
   typedef typename Mfma<T>::V Acc;
   constexpr int PF = MvtPF<T, NCT>::value;
   static_assert(PF % 2 == 0, "the LDS buffer of a chunk is its slot's parity");
@@ -1289,7 +1286,6 @@ k_mv_t_tile(const T* __restrict__ phi, int64_t ld_phi,
   // block b runs group gi over split sp with b = 8 (G (sp / 8) + gi) + sp % 8: the workgroups of
   // all groups over one range of points land on one XCD (dispatch is round robin over the eight),
   // close together in time, so V and the radial rows of the range are fetched into its L2 once
-  const int b = blockIdx.x;
   const int rest = b >> 3;
   const int gi = rest % n_groups;
   const int split = ((rest / n_groups) << 3) + (b & 7);
@@ -1503,6 +1499,16 @@ k_mv_t_tile(const T* __restrict__ phi, int64_t ld_phi,
   }
 }
 
+template <typename T, typename TV, int NCT>
+__global__ void __launch_bounds__(kMvtThreads) __attribute__((amdgpu_waves_per_eu(MvtWaves<T, NCT>::value, 8)))
+k_mv_t_tile(const T* __restrict__ phi, int64_t ld_phi, const T* __restrict__ q, int64_t ld_q,
+            const MvtWave* __restrict__ waves, const MvtRankRow* __restrict__ rrows,
+            const MvtGroup* __restrict__ groups, int n_groups, int n_splits, int64_t split_len,
+            const TV* __restrict__ V, int64_t ldv, int64_t n, int m, int m16, int64_t rank, double* __restrict__ part) {
+  mvt_tile<T, TV, NCT>(blockIdx.x, phi, ld_phi, q, ld_q, waves, rrows, groups, n_groups, n_splits, split_len, V, ldv, n,
+                       m, m16, rank, part);
+}
+
 int matvec_tile_nl(int prec, int nct) {
   if (prec == 1) return nct == 1 ? MvtNL<float, 1>::value : (nct == 2 ? MvtNL<float, 2>::value : MvtNL<float, 4>::value);
   return nct == 1 ? MvtNL<double, 1>::value : (nct == 2 ? MvtNL<double, 2>::value : MvtNL<double, 4>::value);
@@ -1551,13 +1557,13 @@ hipError_t launch_matvec_t_tile(const void* phi, int64_t ld_phi, const void* q, 
 // 2's order: block, 16-column tile, then (lane 16 g + c, K-step kb) for harmonic 4 kb + g, zeros past
 // the degree's harmonics.  Any of the three may be null.
 template <typename T>
-__global__ void __launch_bounds__(256) k_mv_reduce(const double* __restrict__ part, int n_splits, int64_t stride,
-                                                    int64_t total, int m16, const int32_t* __restrict__ src,
-                                                    const double* __restrict__ lam_row, double* __restrict__ W,
-                                                    T* __restrict__ Wd, T* __restrict__ Wb) {
+__device__ __forceinline__ void mv_reduce(int bx, const double* __restrict__ part, int n_splits, int64_t stride,
+                                          int64_t total, int m16, const int32_t* __restrict__ src,
+                                          const double* __restrict__ lam_row, double* __restrict__ W,
+                                          T* __restrict__ Wd, T* __restrict__ Wb) {
   __shared__ double red[4][64];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int64_t e = (int64_t)blockIdx.x * 64 + lane;
+  const int64_t e = (int64_t)bx * 64 + lane;
   const int64_t row = e < total ? e / m16 : 0;
   const int c = (int)(e < total ? e - row * m16 : 0);
   const int sr = e < total ? src[row] : -1;
@@ -1579,6 +1585,14 @@ __global__ void __launch_bounds__(256) k_mv_reduce(const double* __restrict__ pa
     const int hh = (int)(row & 15), kb = hh >> 2, g = hh & 3;
     Wb[((row >> 4) * (m16 >> 4) + (c >> 4)) * 256 + (g * 16 + (c & 15)) * 4 + kb] = sc;
   }
+}
+
+template <typename T>
+__global__ void __launch_bounds__(256) k_mv_reduce(const double* __restrict__ part, int n_splits, int64_t stride,
+                                                    int64_t total, int m16, const int32_t* __restrict__ src,
+                                                    const double* __restrict__ lam_row, double* __restrict__ W,
+                                                    T* __restrict__ Wd, T* __restrict__ Wb) {
+  mv_reduce(blockIdx.x, part, n_splits, stride, total, m16, src, lam_row, W, Wd, Wb);
 }
 
 // Pass 2, KV = U (D W).  One wavefront owns 64 points and NCT 16-column tiles of the right-hand sides.
@@ -1702,17 +1716,17 @@ struct MvnPass {
 };
 
 template <typename T, typename TO, int NCT, bool SPLIT>
-__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(MvnWaves<T, NCT>::value, 8)))
-k_mv_n(const T* __restrict__ phi, int64_t ld_phi, const T* __restrict__ q, int64_t ld_q,
-       const DegDev* __restrict__ degs, int n_deg, const T* __restrict__ Wb, int m16, TO* __restrict__ KV,
-       int64_t ldkv, int64_t n, int m, int z_blocks, int n_blocks, T* __restrict__ part) {
+__device__ __forceinline__ void mv_n(unsigned bx, int bz, const T* __restrict__ phi, int64_t ld_phi,
+                                     const T* __restrict__ q, int64_t ld_q, const DegDev* __restrict__ degs, int n_deg,
+                                     const T* __restrict__ Wb, int m16, TO* __restrict__ KV, int64_t ldkv, int64_t n,
+                                     int m, int z_blocks, int n_blocks, T* __restrict__ part) {
   const int lane = threadIdx.x, li = lane & 15, g = lane >> 4;
   // block b takes column group cg of point block pb, b = 8 (n_cg (pb / 8) + cg) + pb % 8: the column
   // groups of a point block run on one XCD (dispatch is round robin over the eight), close in time,
   // and share the harmonic rows in its L2
   const int cpl = m16 >> 4, n_cg = (cpl + NCT - 1) / NCT;
-  const int rest = (int)(blockIdx.x >> 3), cg = rest % n_cg;
-  const int64_t p0 = ((int64_t)(rest / n_cg) * 8 + (blockIdx.x & 7)) * 64;
+  const int rest = (int)(bx >> 3), cg = rest % n_cg;
+  const int64_t p0 = ((int64_t)(rest / n_cg) * 8 + (bx & 7)) * 64;
   if (p0 >= n) return;
   const int ct0 = cg * NCT, nct = cpl - ct0 < NCT ? cpl - ct0 : NCT;   // column tiles of this group
   MvnPass<T, NCT> ps;
@@ -1751,7 +1765,7 @@ k_mv_n(const T* __restrict__ phi, int64_t ld_phi, const T* __restrict__ q, int64
     }
   } else {
     // block after block, the next one's rows and operands in flight
-    int blk = (int)blockIdx.z * z_blocks;
+    int blk = bz * z_blocks;
     const int hi = blk + z_blocks < n_blocks ? blk + z_blocks : n_blocks;
     int di = 0;
     while (di + 1 < n_deg && degs[di + 1].boff <= blk) ++di;
@@ -1790,7 +1804,7 @@ k_mv_n(const T* __restrict__ phi, int64_t ld_phi, const T* __restrict__ q, int64
   for (int ct = 0; ct < NCT; ++ct) {
     const int c = 16 * (ct0 + ct) + li;
     if (ct < nct && c < m) {
-      T* dpart = SPLIT ? part + (int64_t)blockIdx.z * n * m : nullptr;
+      T* dpart = SPLIT ? part + (int64_t)bz * n * m : nullptr;
 #pragma unroll
       for (int u = 0; u < 4; ++u)
 #pragma unroll
@@ -1805,15 +1819,24 @@ k_mv_n(const T* __restrict__ phi, int64_t ld_phi, const T* __restrict__ q, int64
   }
 }
 
+template <typename T, typename TO, int NCT, bool SPLIT>
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(MvnWaves<T, NCT>::value, 8)))
+k_mv_n(const T* __restrict__ phi, int64_t ld_phi, const T* __restrict__ q, int64_t ld_q,
+       const DegDev* __restrict__ degs, int n_deg, const T* __restrict__ Wb, int m16, TO* __restrict__ KV,
+       int64_t ldkv, int64_t n, int m, int z_blocks, int n_blocks, T* __restrict__ part) {
+  mv_n<T, TO, NCT, SPLIT>(blockIdx.x, blockIdx.z, phi, ld_phi, q, ld_q, degs, n_deg, Wb, m16, KV, ldkv, n, m, z_blocks,
+                          n_blocks, part);
+}
+
 // Sum of pass 2's shares in a fixed order: a workgroup owns 64 entries, wavefront w takes the shares
 // w, w + 4, ... with four running sums (one thread per entry over 128 shares of a 460-point cluster
 // took 26 us, a chain of dependent loads).
 template <typename T, typename TO>
-__global__ void __launch_bounds__(256) k_mv_n_sum(const T* __restrict__ part, int nz, int64_t n, int m,
-                                                  TO* __restrict__ KV, int64_t ldkv) {
+__device__ __forceinline__ void mv_n_sum(int bx, const T* __restrict__ part, int nz, int64_t n, int m,
+                                         TO* __restrict__ KV, int64_t ldkv) {
   __shared__ T red[4][64];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int64_t e = (int64_t)blockIdx.x * 64 + lane, total = n * m;
+  const int64_t e = (int64_t)bx * 64 + lane, total = n * m;
   const T* p = part + (e < total ? e : 0);
   T acc[4] = {0, 0, 0, 0};
   int z = w;
@@ -1826,6 +1849,56 @@ __global__ void __launch_bounds__(256) k_mv_n_sum(const T* __restrict__ part, in
   if (w != 0 || e >= total) return;
   const int64_t pt = e / m;
   KV[pt * ldkv + (e - pt * m)] = (TO)((red[0][lane] + red[1][lane]) + (red[2][lane] + red[3][lane]));
+}
+
+template <typename T, typename TO>
+__global__ void __launch_bounds__(256) k_mv_n_sum(const T* __restrict__ part, int nz, int64_t n, int m,
+                                                  TO* __restrict__ KV, int64_t ldkv) {
+  mv_n_sum(blockIdx.x, part, nz, n, m, KV, ldkv);
+}
+
+// The products of many binary64 factors with one right-hand side each, a launch per phase over all of
+// them (blockIdx.y: the factor).  Launched one by one, thirty factors of 460 points and rank 1,290 took
+// 120 launches of a few workgroups, and the host's enqueueing bounded the KRR operator: 0.69 ms with
+// them on four streams, 0.45 ms so (0.30 of it the off-diagonal kernel beside them).
+__global__ void __launch_bounds__(kMvtThreads) __attribute__((amdgpu_waves_per_eu(MvtWaves<double, 1>::value, 8)))
+k_mvb_t(const MvBatch* __restrict__ batch, const double* __restrict__ v) {
+  const MvBatch f = batch[blockIdx.y];
+  if ((int)blockIdx.x >= (f.n_splits + 7) / 8 * 8 * f.n_groups) return;
+  mvt_tile<double, double, 1>(blockIdx.x, f.phi, f.ld, f.q, f.ld, f.waves, f.rank_rows, f.groups, f.n_groups,
+                              f.n_splits, f.split_len, v + f.pos, 1, f.n, 1, 16, f.rank, f.part);
+}
+
+__global__ void __launch_bounds__(256) k_mvb_reduce(const MvBatch* __restrict__ batch) {
+  const MvBatch f = batch[blockIdx.y];
+  if ((int64_t)blockIdx.x * 64 >= f.n_blocks * 256) return;
+  mv_reduce<double>(blockIdx.x, f.part, f.n_splits, f.rank * 16, f.n_blocks * 256, 16, f.src, f.lam, nullptr, nullptr,
+                    f.Wb);
+}
+
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(MvnWaves<double, 1>::value, 8)))
+k_mvb_n(const MvBatch* __restrict__ batch) {
+  const MvBatch f = batch[blockIdx.y];
+  if ((int)blockIdx.z >= f.nz) return;
+  mv_n<double, double, 1, true>(blockIdx.x, blockIdx.z, f.phi, f.ld, f.q, f.ld, f.degs, f.n_deg, f.Wb, 16, nullptr, 1,
+                                f.n, 1, f.z_blocks, (int)f.n_blocks, f.shares);
+}
+
+__global__ void __launch_bounds__(256) k_mvb_sum(const MvBatch* __restrict__ batch, double* __restrict__ out) {
+  const MvBatch f = batch[blockIdx.y];
+  if ((int64_t)blockIdx.x * 64 >= f.n) return;
+  mv_n_sum<double, double>(blockIdx.x, f.shares, f.nz, f.n, 1, out + f.pos, 1);
+}
+
+hipError_t launch_matvec_batch(const MvBatch* batch_dev, const MvBatchGrid& g, const double* v, double* out,
+                               hipStream_t s) {
+  if (g.factors < 1 || g.t_blocks < 1 || g.r_blocks < 1 || g.n_blocks < 1 || g.shares < 1) return hipErrorInvalidValue;
+  const unsigned nf = (unsigned)g.factors;
+  k_mvb_t<<<dim3((unsigned)g.t_blocks, nf), kMvtThreads, matvec_tile_lds_bytes(16, 0), s>>>(batch_dev, v);
+  k_mvb_reduce<<<dim3((unsigned)g.r_blocks, nf), 256, 0, s>>>(batch_dev);
+  k_mvb_n<<<dim3((unsigned)((g.n_blocks + 7) / 8 * 8), nf, (unsigned)g.shares), 64, 0, s>>>(batch_dev);
+  k_mvb_sum<<<dim3((unsigned)g.n_blocks, nf), 256, 0, s>>>(batch_dev, out);
+  return hipGetLastError();
 }
 
 constexpr int kMvNctF = 4;   // column tiles per item of k_mv_t, binary32

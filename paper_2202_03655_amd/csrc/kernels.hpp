@@ -82,7 +82,7 @@ struct DegDev {
   int32_t qoff;   // first radial row in q
   int32_t s;      // s_k
   int32_t roff;   // first rank row (k, h=0, l=0)
-  int32_t boff;   // first block of the degree in pass 2's batch-major copy of D W
+  int32_t boff;   // first block of the degree in pass 2's block-ordered copy of D W
   int32_t pad[2];
 };
 struct TileDev {
@@ -165,6 +165,29 @@ hipError_t launch_matvec_n(const void* phi, int64_t ld_phi, const void* q, int64
                            const DegDev* degs, int n_deg, const void* Wb, int64_t n_blocks, int m16,
                            void* KV, int64_t ldkv, int64_t n, int m, int prec, int io, int z_blocks,
                            void* part, hipStream_t s);
+
+// Products of several binary64 factors, one right-hand side each (entries [pos, pos + n) of v and out).
+struct MvBatch {
+  const double *phi, *q;
+  int64_t ld, n, pos, rank, n_blocks, split_len;
+  const MvtWave* waves;
+  const MvtRankRow* rank_rows;
+  const MvtGroup* groups;
+  const DegDev* degs;
+  const int32_t* src;
+  const double* lam;
+  double *part, *Wb, *shares;
+  int32_t n_groups, n_splits, n_deg, z_blocks, nz, pad;
+};
+struct MvBatchGrid {
+  int factors;      // descriptors
+  int t_blocks;     // largest number of pass-1 workgroups, ...
+  int r_blocks;     // ... of 64-entry groups of the reduction,
+  int n_blocks;     // ... of 64-point groups
+  int shares;       // ... and of shares of pass 2
+};
+hipError_t launch_matvec_batch(const MvBatch* batch_dev, const MvBatchGrid& g, const double* v, double* out,
+                               hipStream_t s);
 
 // Adjoint by contractions (see hdf_backward).  launch_radial evaluates S
 // Chebyshev series of t(rho^2) at every point: out[row][i] = scale * sum_a

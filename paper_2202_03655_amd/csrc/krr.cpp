@@ -23,7 +23,6 @@ namespace {
 
 constexpr int kMaxBlock = 16384;   // largest cluster: its dense block is 2 GiB
 constexpr int kBatch = 8;          // CG iterations enqueued per convergence check
-constexpr int kSide = 4;           // streams the per-cluster factor products are spread over
 
 struct Buf {
   void* p = nullptr;
@@ -75,31 +74,31 @@ struct hdf_krr {
   std::vector<hdf_handle> fac;            // per cluster, NULL when empty
   std::vector<int> block_cluster;         // non-empty block -> cluster
   std::vector<Block> blocks;              // non-empty blocks in cluster order
-  int max_n = 0, splits = 1, nrz = 1;
+  int max_n = 0, splits = 1, nrz = 1, npq = 1;
   int64_t precond_elems = 0;
   double t_factor = 0, t_precond = 0;
   int last_it = 0;
   double last_relres = 0;
   bool od_timed = false, s_timed = false;
   hipEvent_t ev[4] = {nullptr, nullptr, nullptr, nullptr};   // off-diagonal kernel, solve
-  // the cluster factors are small (few points, many harmonics): their products run on side streams,
-  // concurrently with each other and with the off-diagonal kernel
-  hipStream_t side[kSide] = {};
-  hipEvent_t fork = nullptr, join[kSide] = {};
+  // the cluster factors are small (few points, many harmonics): their products run in one launch per
+  // phase over all of them, on a side stream beside the off-diagonal kernel
+  hdf::ProductBatch* batch = nullptr;
+  hipStream_t side = nullptr;
+  hipEvent_t fork = nullptr, join = nullptr;
   // device: points in cluster order, permutation, exclusion ranges, row -> block, descriptors
   Buf xs, perm, lohi, row_block, blocks_dev, ainv;
   // work vectors (cluster order), partial sums, CG state
   Buf vs, outs, qb, part, x, r, z, p, q, st, part_pq, part_rr, part_bb, part_rz;
   ~hdf_krr() {
+    if (batch) hdf::batch_free(batch);
     for (hdf_handle h : fac)
       if (h) hdf_free(h);
     for (auto& e : ev)
       if (e) hipEventDestroy(e);
-    for (auto& e : join)
-      if (e) hipEventDestroy(e);
+    if (join) hipEventDestroy(join);
     if (fork) hipEventDestroy(fork);
-    for (auto& t : side)
-      if (t) hipStreamDestroy(t);
+    if (side) hipStreamDestroy(side);
   }
 };
 
@@ -167,7 +166,7 @@ hdf_status hdf_kernel_matvec(const double* x, int64_t nx, int64_t ldx, const dou
   KCHK(part.alloc((size_t)splits * nx * sizeof(double)));
   KCHK(hdf::krr::launch_kmv(x, ldx, nx, y, ldy, ny, d, (int)kernel, lengthscale, w, nullptr, part.as<double>(),
                             splits, s));
-  KCHK(hdf::krr::launch_kmv_finish(part.as<double>(), splits, nx, nullptr, nullptr, 0.0, out, s));
+  KCHK(hdf::krr::launch_kmv_finish(part.as<double>(), splits, nx, nullptr, nullptr, 0.0, out, nullptr, s));
   // the workspace is released on return
   KCHK(hipStreamSynchronize(s));
   return HDF_OK;
@@ -176,17 +175,14 @@ hdf_status hdf_kernel_matvec(const double* x, int64_t nx, int64_t ldx, const dou
 // ------------------------------------------------------------ KRR system
 
 // out = lam v + blockdiag(factors) v + offdiag(K) v.  The cluster factors' products (into qb) run on the
-// side streams after a fork from s; the off-diagonal kernel runs on s meanwhile; s waits for every side
-// stream before the final sum.
-static hdf_status krr_operator(hdf_krr* h, const double* v, double* out, hipStream_t s, bool timed) {
+// side stream after a fork from s; the off-diagonal kernel runs on s meanwhile; s waits for the side
+// stream before the final sum, which leaves the partial sums of v . out in part_vq if that is not NULL.
+static hdf_status krr_operator(hdf_krr* h, const double* v, double* out, double* part_vq, hipStream_t s, bool timed) {
   KCHK(hipEventRecord(h->fork, s));
-  for (int j = 0; j < kSide; ++j) KCHK(hipStreamWaitEvent(h->side[j], h->fork, 0));
-  for (size_t b = 0; b < h->blocks.size(); ++b) {
-    const Block& B = h->blocks[b];
-    hdf_status st = hdf_matvec(h->fac[h->block_cluster[b]], v + B.pos, 1, 1, h->qb.as<double>() + B.pos, 1,
-                               h->side[b % kSide]);
-    if (st != HDF_OK) return st;
-  }
+  KCHK(hipStreamWaitEvent(h->side, h->fork, 0));
+  hdf_status st = hdf::batch_run(h->batch, v, h->qb.as<double>(), h->side);
+  if (st != HDF_OK) return st;
+  KCHK(hipEventRecord(h->join, h->side));
   if (timed) KCHK(hipEventRecord(h->ev[0], s));
   KCHK(hdf::krr::launch_kmv(h->xs.as<double>(), h->d, h->n, h->xs.as<double>(), h->d, h->n, h->d, h->kernel, h->l,
                             v, h->lohi.as<int32_t>(), h->part.as<double>(), h->splits, s));
@@ -194,11 +190,9 @@ static hdf_status krr_operator(hdf_krr* h, const double* v, double* out, hipStre
     KCHK(hipEventRecord(h->ev[1], s));
     h->od_timed = true;
   }
-  for (int j = 0; j < kSide; ++j) {
-    KCHK(hipEventRecord(h->join[j], h->side[j]));
-    KCHK(hipStreamWaitEvent(s, h->join[j], 0));
-  }
-  KCHK(hdf::krr::launch_kmv_finish(h->part.as<double>(), h->splits, h->n, h->qb.as<double>(), v, h->lam, out, s));
+  KCHK(hipStreamWaitEvent(s, h->join, 0));
+  KCHK(hdf::krr::launch_kmv_finish(h->part.as<double>(), h->splits, h->n, h->qb.as<double>(), v, h->lam, out, part_vq,
+                                   s));
   return HDF_OK;
 }
 
@@ -325,12 +319,26 @@ hdf_status hdf_krr_create(const double* points, int64_t n, int d, int64_t ld, co
   for (Buf* b : {&h->vs, &h->outs, &h->qb, &h->x, &h->r, &h->z, &h->p, &h->q}) KCHK(b->alloc((size_t)n * 8));
   KCHK(h->part.alloc((size_t)h->splits * n * 8));
   KCHK(h->st.alloc(sizeof(CGState)));
-  for (Buf* b : {&h->part_pq, &h->part_rr, &h->part_bb}) KCHK(b->alloc((size_t)hdf::krr::kDotBlocks * 8));
+  for (Buf* b : {&h->part_rr, &h->part_bb}) KCHK(b->alloc((size_t)hdf::krr::kDotBlocks * 8));
+  h->npq = hdf::krr::kmv_finish_blocks(n);
+  KCHK(h->part_pq.alloc((size_t)h->npq * 8));
   KCHK(h->part_rz.alloc((size_t)h->nrz * 8));
   for (auto& e : h->ev) KCHK(hipEventCreate(&e));
   KCHK(hipEventCreateWithFlags(&h->fork, hipEventDisableTiming));
-  for (auto& e : h->join) KCHK(hipEventCreateWithFlags(&e, hipEventDisableTiming));
-  for (auto& t : h->side) KCHK(hipStreamCreateWithFlags(&t, hipStreamNonBlocking));
+  KCHK(hipEventCreateWithFlags(&h->join, hipEventDisableTiming));
+  KCHK(hipStreamCreateWithFlags(&h->side, hipStreamNonBlocking));
+  {
+    std::vector<hdf_handle> factors;
+    std::vector<int64_t> pos;
+    for (int b = 0; b < nb; ++b) {
+      factors.push_back(h->fac[h->block_cluster[b]]);
+      pos.push_back(h->blocks[b].pos);
+    }
+    // factors of rank zero write nothing: their entries of qb stay zero
+    KCHK(hipMemsetAsync(h->qb.p, 0, (size_t)n * 8, s));
+    hdf_status st = hdf::batch_create(factors, pos, s, &h->batch);
+    if (st != HDF_OK) return st;
+  }
   *out = h.release();
   return HDF_OK;
 }
@@ -341,7 +349,7 @@ hdf_status hdf_krr_apply(hdf_krr_handle h, const double* v, double* out, void* h
   if (overlap(v, h->n * 8, out, h->n * 8)) return hdf::set_error(HDF_E_ARG, "v and out overlap");
   hipStream_t s = (hipStream_t)hip_stream;
   KCHK(hdf::krr::launch_gather(v, h->perm.as<int32_t>(), h->n, h->vs.as<double>(), s));
-  hdf_status st = krr_operator(h, h->vs.as<double>(), h->outs.as<double>(), s, true);
+  hdf_status st = krr_operator(h, h->vs.as<double>(), h->outs.as<double>(), nullptr, s, true);
   if (st != HDF_OK) return st;
   KCHK(hdf::krr::launch_scatter(h->outs.as<double>(), h->perm.as<int32_t>(), h->n, out, s));
   return HDF_OK;
@@ -385,15 +393,12 @@ hdf_status hdf_krr_solve(hdf_krr_handle h, const double* y, double* w, int max_i
   for (int it0 = 0;; it0 += kBatch) {
     const int cnt = std::min(kBatch, max_iter - it0);
     for (int i = 0; i < cnt; ++i) {
-      hdf_status e = krr_operator(h, p, q, s, first);
+      hdf_status e = krr_operator(h, p, q, h->part_pq.as<double>(), s, first);
       if (e != HDF_OK) return e;
       first = false;
-      KCHK(hdf::krr::launch_dot_partial(p, q, n, h->part_pq.as<double>(), s));
-      KCHK(hdf::krr::launch_cg_alpha(st, h->part_pq.as<double>(), s));
-      KCHK(hdf::krr::launch_cg_xr(x, r, p, q, n, st, h->part_rr.as<double>(), s));
-      KCHK(hdf::krr::launch_cg_check(st, h->part_rr.as<double>(), s));
+      KCHK(hdf::krr::launch_cg_xr(x, r, p, q, n, st, h->part_pq.as<double>(), h->npq, h->part_rr.as<double>(), s));
       KCHK(hdf::krr::launch_block_gemv(h->ainv.as<double>(), blocks, rb, n, r, z, h->part_rz.as<double>(), st, s));
-      KCHK(hdf::krr::launch_cg_beta(st, h->part_rz.as<double>(), h->nrz, s));
+      KCHK(hdf::krr::launch_cg_step(st, h->part_rr.as<double>(), h->part_rz.as<double>(), h->nrz, s));
       KCHK(hdf::krr::launch_cg_p(p, z, n, st, s));
     }
     KCHK(hipMemcpyAsync(&hs, st, sizeof(CGState), hipMemcpyDeviceToHost, s));

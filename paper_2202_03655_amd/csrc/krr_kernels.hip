@@ -219,15 +219,40 @@ __global__ __launch_bounds__(256) void k_kmv(const double* __restrict__ x, int64
   if (i < nx) part[(int64_t)blockIdx.y * nx + i] = acc;
 }
 
+// 64 entries per workgroup, wavefront w takes the partial sums w, w + 4, ... (a fixed order)
 __global__ __launch_bounds__(256) void k_kmv_finish(const double* __restrict__ part, int splits, int64_t n,
                                                     const double* __restrict__ base, const double* __restrict__ v,
-                                                    double lam, double* __restrict__ out) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= n) return;
-  double s = base ? base[i] : 0.0;
-  if (v) s = fma(lam, v[i], s);
-  for (int k = 0; k < splits; ++k) s += part[(int64_t)k * n + i];
-  out[i] = s;
+                                                    double lam, double* __restrict__ out,
+                                                    double* __restrict__ part_dot) {
+  __shared__ double red[4][64];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int64_t i = (int64_t)blockIdx.x * 64 + lane;
+  double acc[4] = {0, 0, 0, 0};
+  if (i < n) {
+    int k = w;
+    for (; k + 12 < splits; k += 16)
+#pragma unroll
+      for (int u = 0; u < 4; ++u) acc[u] += part[(int64_t)(k + 4 * u) * n + i];
+    for (; k < splits; k += 4) acc[0] += part[(int64_t)k * n + i];
+  }
+  red[w][lane] = (acc[0] + acc[1]) + (acc[2] + acc[3]);
+  __syncthreads();
+  if (w != 0) return;
+  double dot = 0.0;
+  if (i < n) {
+    double s = (red[0][lane] + red[1][lane]) + (red[2][lane] + red[3][lane]);
+    if (base) s += base[i];
+    if (v) {
+      s = fma(lam, v[i], s);
+      dot = v[i] * s;
+    }
+    out[i] = s;
+  }
+  if (part_dot) {
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) dot += __shfl_xor(dot, off);
+    if (lane == 0) part_dot[blockIdx.x] = dot;
+  }
 }
 
 __global__ __launch_bounds__(256) void k_pack_rows(const double* __restrict__ x, int64_t n, int d, int64_t ld,
@@ -590,29 +615,21 @@ __global__ __launch_bounds__(256) void k_cg_init(CGState* __restrict__ st, const
     st->rz = rz;
     st->rr = bb;
     st->rtol2 = rtol2;
-    st->alpha = st->beta = st->pq = 0.0;
+    st->beta = 0.0;
     st->it = 0;
     st->max_it = max_it;
     st->done = bb == 0.0 ? 1 : (max_it <= 0 ? 2 : 0);
   }
 }
 
-__global__ __launch_bounds__(256) void k_cg_alpha(CGState* __restrict__ st, const double* __restrict__ part_pq) {
-  if (st->done) return;
-  __shared__ double sh[256];
-  const double pq = block_sum(part_pq, kDotBlocks, sh);
-  if (threadIdx.x == 0) {
-    st->pq = pq;
-    st->alpha = st->rz / pq;
-  }
-}
-
+// every workgroup sums the partial p . q for itself: a launch less than a scalar kernel before it
 __global__ __launch_bounds__(256) void k_cg_xr(double* __restrict__ x, double* __restrict__ r,
                                                const double* __restrict__ p, const double* __restrict__ q, int64_t n,
-                                               const CGState* __restrict__ st, double* __restrict__ part_rr) {
+                                               const CGState* __restrict__ st, const double* __restrict__ part_pq,
+                                               int npq, double* __restrict__ part_rr) {
   if (st->done) return;
   __shared__ double sh[256];
-  const double a = st->alpha;
+  const double a = st->rz / block_sum(part_pq, npq, sh);
   double s = 0.0;
   for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)kDotBlocks * 256) {
     x[i] = fma(a, p[i], x[i]);
@@ -623,26 +640,22 @@ __global__ __launch_bounds__(256) void k_cg_xr(double* __restrict__ x, double* _
   block_store(s, sh, part_rr + blockIdx.x);
 }
 
-__global__ __launch_bounds__(256) void k_cg_check(CGState* __restrict__ st, const double* __restrict__ part_rr) {
+__global__ __launch_bounds__(256) void k_cg_step(CGState* __restrict__ st, const double* __restrict__ part_rr,
+                                                 const double* __restrict__ part_rz, int nrz) {
   if (st->done) return;
   __shared__ double sh[256];
   const double rr = block_sum(part_rr, kDotBlocks, sh);
+  const double rz = block_sum(part_rz, nrz, sh);
   if (threadIdx.x == 0) {
     st->rr = rr;
     const int it = st->it + 1;
     st->it = it;
     if (rr <= st->rtol2 * st->bb) st->done = 1;
     else if (it >= st->max_it) st->done = 2;
-  }
-}
-
-__global__ __launch_bounds__(256) void k_cg_beta(CGState* __restrict__ st, const double* __restrict__ part_rz, int nrz) {
-  if (st->done) return;
-  __shared__ double sh[256];
-  const double rz = block_sum(part_rz, nrz, sh);
-  if (threadIdx.x == 0) {
-    st->beta = rz / st->rz;
-    st->rz = rz;
+    if (!st->done) {
+      st->beta = rz / st->rz;
+      st->rz = rz;
+    }
   }
 }
 
@@ -740,9 +753,11 @@ hipError_t launch_kmv(const double* x, int64_t ldx, int64_t nx, const double* y,
   return hipGetLastError();
 }
 
+int kmv_finish_blocks(int64_t n) { return (int)std::max<int64_t>(1, (n + 63) / 64); }
+
 hipError_t launch_kmv_finish(const double* part, int splits, int64_t n, const double* base, const double* v,
-                             double lam, double* out, hipStream_t s) {
-  k_kmv_finish<<<blocks_for(n), 256, 0, s>>>(part, splits, n, base, v, lam, out);
+                             double lam, double* out, double* part_dot, hipStream_t s) {
+  k_kmv_finish<<<(unsigned)kmv_finish_blocks(n), 256, 0, s>>>(part, splits, n, base, v, lam, out, part_dot);
   return hipGetLastError();
 }
 
@@ -822,24 +837,14 @@ hipError_t launch_cg_init(CGState* st, const double* part_bb, const double* part
   return hipMemcpyAsync(p, z, (size_t)n * sizeof(double), hipMemcpyDeviceToDevice, s);
 }
 
-hipError_t launch_cg_alpha(CGState* st, const double* part_pq, hipStream_t s) {
-  k_cg_alpha<<<1, 256, 0, s>>>(st, part_pq);
-  return hipGetLastError();
-}
-
 hipError_t launch_cg_xr(double* x, double* r, const double* p, const double* q, int64_t n, const CGState* st,
-                        double* part_rr, hipStream_t s) {
-  k_cg_xr<<<kDotBlocks, 256, 0, s>>>(x, r, p, q, n, st, part_rr);
+                        const double* part_pq, int npq, double* part_rr, hipStream_t s) {
+  k_cg_xr<<<kDotBlocks, 256, 0, s>>>(x, r, p, q, n, st, part_pq, npq, part_rr);
   return hipGetLastError();
 }
 
-hipError_t launch_cg_check(CGState* st, const double* part_rr, hipStream_t s) {
-  k_cg_check<<<1, 256, 0, s>>>(st, part_rr);
-  return hipGetLastError();
-}
-
-hipError_t launch_cg_beta(CGState* st, const double* part_rz, int nrz, hipStream_t s) {
-  k_cg_beta<<<1, 256, 0, s>>>(st, part_rz, nrz);
+hipError_t launch_cg_step(CGState* st, const double* part_rr, const double* part_rz, int nrz, hipStream_t s) {
+  k_cg_step<<<1, 256, 0, s>>>(st, part_rr, part_rz, nrz);
   return hipGetLastError();
 }
 

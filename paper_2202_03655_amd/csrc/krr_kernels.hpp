@@ -10,7 +10,7 @@ namespace krr {
 // Device-resident conjugate-gradient scalars.  done: 0 running, 1 converged,
 // 2 iteration limit reached.
 struct CGState {
-  double rz, pq, rr, bb, alpha, beta, rtol2;
+  double rz, rr, bb, beta, rtol2;
   int32_t it, done, max_it, pad;
 };
 
@@ -41,9 +41,11 @@ int kmv_splits(int64_t nx, int64_t ny);
 hipError_t launch_kmv(const double* x, int64_t ldx, int64_t nx, const double* y, int64_t ldy, int64_t ny, int d,
                       int kernel, double l, const double* w, const int32_t* lohi, double* part, int splits,
                       hipStream_t s);
-// out[i] = (base ? base[i] : 0) + lam * (v ? v[i] : 0) + sum_s part[s][i]
+// out[i] = (base ? base[i] : 0) + lam * (v ? v[i] : 0) + sum_s part[s][i]; part_dot (if not NULL, with
+// v): kmv_finish_blocks(n) partial sums of v . out
+int kmv_finish_blocks(int64_t n);
 hipError_t launch_kmv_finish(const double* part, int splits, int64_t n, const double* base, const double* v,
-                             double lam, double* out, hipStream_t s);
+                             double lam, double* out, double* part_dot, hipStream_t s);
 // contiguous n x d copy of a strided array
 hipError_t launch_pack_rows(const double* x, int64_t n, int d, int64_t ld, double* out, hipStream_t s);
 
@@ -69,11 +71,11 @@ hipError_t launch_dot_partial(const double* a, const double* b, int64_t n, doubl
 hipError_t launch_cg_start(const double* y, int64_t n, double* x, double* r, hipStream_t s);
 hipError_t launch_cg_init(CGState* st, const double* part_bb, const double* part_rz, int nrz, double rtol2,
                           int max_it, const double* z, double* p, int64_t n, hipStream_t s);
-hipError_t launch_cg_alpha(CGState* st, const double* part_pq, hipStream_t s);
+// alpha = rz / sum(part_pq); x += alpha p, r -= alpha q, partial sums of r . r
 hipError_t launch_cg_xr(double* x, double* r, const double* p, const double* q, int64_t n, const CGState* st,
-                        double* part_rr, hipStream_t s);
-hipError_t launch_cg_check(CGState* st, const double* part_rr, hipStream_t s);
-hipError_t launch_cg_beta(CGState* st, const double* part_rz, int nrz, hipStream_t s);
+                        const double* part_pq, int npq, double* part_rr, hipStream_t s);
+// the iteration's count and stopping decision, then beta from the new r . z unless it has stopped
+hipError_t launch_cg_step(CGState* st, const double* part_rr, const double* part_rz, int nrz, hipStream_t s);
 hipError_t launch_cg_p(double* p, const double* z, int64_t n, const CGState* st, hipStream_t s);
 
 }  // namespace krr

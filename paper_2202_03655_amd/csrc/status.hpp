@@ -1,7 +1,11 @@
 // Shared by the C ABI translation units: the reason of the last failure, kept
 // per thread and returned by hdf_last_error(), and the product-timing switch.
 #pragma once
+#include <hip/hip_runtime_api.h>
+
+#include <cstdint>
 #include <string>
+#include <vector>
 
 #include "../../include/hdf.h"
 
@@ -11,4 +15,11 @@ void clear_error();
 // Switch the HIP events around a factor's products on or off (hdf_info then
 // reports no kernel times for them).  Products on many small factors use off.
 void set_product_timing(hdf_handle h, bool on);
+// Products of several stored binary64 factors with one right-hand side each: the entries
+// [pos, pos + n) of v and out belong to the factor at pos.  The factors outlive the batch.
+struct ProductBatch;
+hdf_status batch_create(const std::vector<hdf_handle>& factors, const std::vector<int64_t>& pos, hipStream_t s,
+                        ProductBatch** out);
+hdf_status batch_run(const ProductBatch* b, const double* v, double* out, hipStream_t s);
+void batch_free(ProductBatch* b);
 }  // namespace hdf
