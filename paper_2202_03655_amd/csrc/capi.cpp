@@ -176,6 +176,8 @@ double now_ms() {
 namespace hdf {
 hdf_status set_error(hdf_status s, const std::string& msg) { return fail(s, msg); }
 void clear_error() { g_err.clear(); }
+hipError_t pool_alloc(void** p, size_t b, size_t* got, int* dev) { return pool::alloc(p, b, got, dev); }
+void pool_release(void* p, size_t bytes, int dev) { pool::release(p, bytes, dev); }
 }  // namespace hdf
 
 
@@ -1423,12 +1425,16 @@ static hdf_status eval_chunk(hdf_handle h, int64_t c0, int64_t nc, hipStream_t s
   return HDF_OK;
 }
 
+// Products of a stored factor with up to kNwMax right-hand sides take the narrow passes.
+static bool narrow(hdf_handle h, int64_t m) { return h->storage == HDF_STORE_FACTOR && m <= hdf::kNwMax; }
+
 // What a pass 1 leaves: W = U^T V (binary64, rank rows), Wd = D W in the factor's type (rank rows),
 // Wb = D W in pass 2's block order; a null buffer is not wanted.
 struct PassOut {
   DevBuf* W = nullptr;
   DevBuf* Wd = nullptr;
   DevBuf* Wb = nullptr;
+  DevBuf* Wn = nullptr;          // D W in the factor's type, rank rows of m values (narrow products only)
 };
 static hdf_status pass1(hdf_handle h, int side, const void* V, int64_t m, int64_t ldv, int m16, const PassOut& out,
                         hipStream_t s, bool timed);
@@ -1609,12 +1615,59 @@ static hdf_status pass2_fused(hdf_handle h, int64_t m, int m16, void* KV, int64_
   return HDF_OK;
 }
 
+// Pass 1 of a narrow product: W (stride m16) and Wn, the splits summed where there are several.
+static hdf_status pass1_narrow(hdf_handle h, int side, const void* V, int64_t m, int64_t ldv, int m16,
+                               const PassOut& out, hipStream_t s, bool timed) {
+  const int64_t n = side == 1 ? h->N2 : h->N, ldn = side == 1 ? h->ldN2 : h->ldN;
+  const int items = hdf::narrow_items(h->degs.data(), (int)h->degs.size(), h->fprec, (int)m);
+  const int64_t per_split = h->r * m * (int64_t)sizeof(double);
+  int n_splits;
+  int64_t split_len;
+  hdf::narrow_splits(n, items, h->fprec, per_split, (int64_t)96e6, &n_splits, &split_len);
+  if (n_splits > 1) HIPCHK(h->ws_part.ensure((size_t)per_split * n_splits));
+  if (out.W) HIPCHK(out.W->ensure((size_t)h->r * m16 * sizeof(double)));
+  if (out.Wn) HIPCHK(out.Wn->ensure((size_t)h->r * m * h->felem()));
+  if (timed) {
+    if (!h->ev_mv[0])
+      for (auto& e : h->ev_mv) HIPCHK(hipEventCreate(&e));
+    HIPCHK(hipEventRecord(h->ev_mv[0], s));
+  }
+  HIPCHK(hdf::launch_narrow_t(side == 1 ? h->phi2.p : h->phi.p, ldn, side == 1 ? h->q2.p : h->q.p, ldn,
+                              (const hdf::DegDev*)h->degs_dev.p, (int)h->degs.size(), items, n_splits, split_len, V, ldv,
+                              n, (int)m, h->r, (const double*)h->lam_row.p, out.Wn ? out.Wn->p : nullptr,
+                              out.W ? (double*)out.W->p : nullptr, m16, (double*)h->ws_part.p, h->fprec, h->dtype, s));
+  if (timed) {
+    HIPCHK(hipEventRecord(h->ev_mv[1], s));
+    HIPCHK(hipEventRecord(h->ev_mv[2], s));
+  }
+  return HDF_OK;
+}
+
+// Wavefronts below which the narrow pass 2 splits the harmonic rows, and at which its shares aim.
+constexpr int64_t kNarrowWaves = 4096;
+
+// Pass 2 of a narrow product.
+static hdf_status pass2_narrow(hdf_handle h, int64_t m, void* KV, int64_t ldkv, hipStream_t s) {
+  const int64_t step = 64 * 16 / h->felem(), waves = (h->N + step - 1) / step;
+  int z_rows = 0;
+  if (waves < kNarrowWaves / 2) {
+    const int64_t want = std::min<int64_t>((kNarrowWaves + waves - 1) / waves, (h->H + 7) / 8);
+    if (want > 1) z_rows = (int)((h->H + want - 1) / want);
+  }
+  if (z_rows > 0) HIPCHK(h->ws_n.ensure((size_t)((h->H + z_rows - 1) / z_rows) * h->N * m * h->felem()));
+  HIPCHK(hdf::launch_narrow_n(h->phi.p, h->ldN, h->q.p, h->ldN, (const hdf::DegDev*)h->degs_dev.p,
+                              (int)h->degs.size(), h->ws_Wd.p, KV, ldkv, h->N, (int)m, (int)h->H, z_rows, h->ws_n.p,
+                              h->fprec, h->dtype, s));
+  return HDF_OK;
+}
+
 // side 2 (matrix-free factors): build the work-item tables only.
 static hdf_status pass1(hdf_handle h, int side, const void* V, int64_t m, int64_t ldv, int m16, const PassOut& out,
                         hipStream_t s, bool timed) {
   if (h->storage == HDF_STORE_NONE && side != 2)
     return h->mf_fused ? pass1_fused(h, V, m, ldv, m16, out, s, timed)
                        : pass1_chunked(h, V, m, ldv, m16, out, s, timed);
+  if (narrow(h, m)) return pass1_narrow(h, side, V, m, ldv, m16, out, s, timed);
   const int64_t n = side == 1 ? h->N2 : (side == 2 ? h->chunk : h->N);
   const void* phi = side == 1 ? h->phi2.p : h->phi.p;
   const void* qv = side == 1 ? h->q2.p : h->q.p;
@@ -1728,7 +1781,8 @@ static hdf_status matvec_impl(hdf_handle h, const void* V, int64_t m, int64_t ld
   const int m16 = (int)((m + 15) / 16 * 16);
   const bool timed = h->time_products;
   PassOut po;
-  if (h->mf_fused) po.Wd = &h->ws_Wd;
+  if (narrow(h, m)) po.Wn = &h->ws_Wd;
+  else if (h->mf_fused) po.Wd = &h->ws_Wd;
   else po.Wb = &h->ws_Wb;
   hdf_status st = pass1(h, h->cross ? 1 : 0, V, m, ldv, m16, po, s, timed);
   if (st != HDF_OK) return st;
@@ -1743,6 +1797,9 @@ static hdf_status matvec_impl(hdf_handle h, const void* V, int64_t m, int64_t ld
       st = pass2(h, h->cphi.p, h->cq.p, h->ldC, nc, m, m16, (char*)KV + c0 * ldkv * el, ldkv, s);
       if (st != HDF_OK) return st;
     }
+  } else if (narrow(h, m)) {
+    st = pass2_narrow(h, m, KV, ldkv, s);
+    if (st != HDF_OK) return st;
   } else {
     st = pass2(h, h->phi.p, h->q.p, h->ldN, n, m, m16, KV, ldkv, s);
     if (st != HDF_OK) return st;
@@ -1814,6 +1871,18 @@ hdf_status hdf_matvec_noalloc(hdf_handle h, const void* V, int64_t m, int64_t ld
   const int64_t n1 = side ? h->N2 : h->N;
   int n_splits;
   int64_t split_len;
+  if (narrow(h, m)) {
+    const int nd = (int)h->degs.size(), items = hdf::narrow_items(h->degs.data(), nd, h->fprec, (int)m);
+    const int64_t wn_bytes = (int64_t)round256((size_t)h->r * m * h->felem());
+    hdf::narrow_splits(n1, items, h->fprec, h->r * m * 8, (int64_t)hdf::kScratchBytes - wn_bytes, &n_splits, &split_len);
+    HIPCHK(hdf::launch_narrow_t(side ? h->phi2.p : h->phi.p, side ? h->ldN2 : h->ldN, side ? h->q2.p : h->q.p,
+                                side ? h->ldN2 : h->ldN, (const hdf::DegDev*)h->degs_dev.p, nd, items, n_splits,
+                                split_len, V, ldv, n1, (int)m, h->r, (const double*)h->lam_row.p, base, nullptr, 1,
+                                (double*)((char*)base + wn_bytes), h->fprec, h->dtype, s));
+    HIPCHK(hdf::launch_narrow_n(h->phi.p, h->ldN, h->q.p, h->ldN, (const hdf::DegDev*)h->degs_dev.p, nd, base, KV, ldkv,
+                                h->N, (int)m, (int)h->H, 0, nullptr, h->fprec, h->dtype, s));
+    return HDF_OK;
+  }
   tile_splits(n1, h->n_tgroups[cpl], per_split, &n_splits, &split_len);
   const int max_splits = (int)((hdf::kScratchBytes - wb_bytes) / per_split);
   if (n_splits > max_splits) {
@@ -2315,7 +2384,7 @@ hdf_status batch_create(const std::vector<hdf_handle>& factors, const std::vecto
     at += (values + 31) / 32 * 32;
     return o;
   };
-  std::vector<size_t> o_part, o_wb, o_sh;
+  std::vector<size_t> o_part, o_wn, o_sh;
   for (size_t i = 0; i < factors.size(); ++i) {
     const hdf_handle h = factors[i];
     if (h->r == 0) continue;                       // contributes zeros
@@ -2326,33 +2395,24 @@ hdf_status batch_create(const std::vector<hdf_handle>& factors, const std::vecto
     f.n = h->N;
     f.pos = pos[i];
     f.rank = h->r;
-    f.n_blocks = h->n_wblocks;
-    f.waves = tile_waves(h, 1);
-    f.rank_rows = tile_rank_rows(h);
-    f.groups = tile_groups(h, 1);
-    f.n_groups = h->n_tgroups[1];
     f.degs = (const DegDev*)h->degs_dev.p;
     f.n_deg = (int)h->degs.size();
-    f.src = (const int32_t*)h->blk_src.p;
     f.lam = (const double*)h->lam_row.p;
-    // the launches of all factors together aim at what one factor's aim at alone (tile_splits, pass2),
-    // twice as many pass-1 workgroups since the factors differ in size
-    int64_t ns = std::max<int64_t>(1, 2048 / std::max(1, live * f.n_groups));
-    ns = std::min<int64_t>(ns, (f.n + 127) / 128);
-    f.split_len = ((f.n + ns - 1) / ns + 127) / 128 * 128;
-    f.n_splits = (int)((f.n + f.split_len - 1) / f.split_len);
-    const int64_t waves = (f.n + 63) / 64;
-    const int64_t want = std::min<int64_t>(std::max<int64_t>(1, kPass2SplitWaves / (waves * live)), f.n_blocks);
-    f.z_blocks = (int)((f.n_blocks + want - 1) / want);
-    f.nz = (int)((f.n_blocks + f.z_blocks - 1) / f.z_blocks);
-    o_part.push_back(room((size_t)f.n_splits * f.rank * 16));
-    o_wb.push_back(room((size_t)f.n_blocks * 256));
+    f.n_items = narrow_items(h->degs.data(), f.n_deg, 0, 1);
+    // the launches of all factors together aim at what one factor's aim at alone
+    narrow_splits(f.n, f.n_items * live, 0, f.rank * 8, (int64_t)96e6 / live, &f.n_splits, &f.split_len);
+    const int64_t waves = (f.n + 127) / 128;
+    const int64_t want = std::min<int64_t>(std::max<int64_t>(1, kNarrowWaves / (waves * live)), (h->H + 7) / 8);
+    f.z_rows = (int)((h->H + want - 1) / want);
+    f.nz = (int)((h->H + f.z_rows - 1) / f.z_rows);
+    o_part.push_back(room(f.n_splits > 1 ? (size_t)f.n_splits * f.rank : 0));
+    o_wn.push_back(room((size_t)f.rank));
     o_sh.push_back(room((size_t)f.nz * f.n));
     b->host.push_back(f);
     MvBatchGrid& g = b->grid;
-    g.t_blocks = std::max(g.t_blocks, (f.n_splits + 7) / 8 * 8 * f.n_groups);
-    g.r_blocks = std::max(g.r_blocks, (int)(f.n_blocks * 4));
-    g.n_blocks = std::max(g.n_blocks, (int)waves);
+    g.t_blocks = std::max(g.t_blocks, (f.n_items + 3) / 4 * f.n_splits);
+    if (f.n_splits > 1) g.r_blocks = std::max(g.r_blocks, (int)((f.rank + 63) / 64));
+    g.n_blocks = std::max(g.n_blocks, (int)((f.n + 63) / 64));
     g.shares = std::max(g.shares, f.nz);
   }
   b->grid.factors = (int)b->host.size();
@@ -2361,7 +2421,7 @@ hdf_status batch_create(const std::vector<hdf_handle>& factors, const std::vecto
     HIPCHK(b->desc.ensure(b->host.size() * sizeof(MvBatch)));
     for (size_t i = 0; i < b->host.size(); ++i) {
       b->host[i].part = (double*)b->ws.p + o_part[i];
-      b->host[i].Wb = (double*)b->ws.p + o_wb[i];
+      b->host[i].Wn = (double*)b->ws.p + o_wn[i];
       b->host[i].shares = (double*)b->ws.p + o_sh[i];
     }
     HIPCHK(hipMemcpyAsync(b->desc.p, b->host.data(), b->host.size() * sizeof(MvBatch), hipMemcpyHostToDevice, s));

@@ -1857,34 +1857,346 @@ __global__ void __launch_bounds__(256) k_mv_n_sum(const T* __restrict__ part, in
   mv_n_sum(blockIdx.x, part, nz, n, m, KV, ldkv);
 }
 
+// ------------------------------------------------------------------ narrow products
+// Products with up to kNwMax right-hand sides, on the vector units: the matrix instructions would spend
+// 12 of 16 columns or more on padding, and their operand layouts read 128- and 256-byte pieces of a row
+// where a lane per 16 bytes of one row streams a kilobyte.  Both passes are bound by reading the factor
+// once (pass 2 at 6.0 TB/s, 1e6 points binary32).  Where the line lies, measured per pass against the
+// matrix-core passes (four right-hand sides, then five to eight computed as eight): pass 1, 1e6 points
+// binary32 0.72 against 0.86 ms, 250,007 points binary64 0.59 against 0.69, 2e5 points of rank 2666 0.22
+// against 0.36; pass 2 0.59, 0.44 and 0.18 against 0.76, 0.51 and 0.30; with eight columns pass 2 takes
+// 0.75, 0.50 and 0.27, no longer worth a second layout of D W, and pass 1 is bound by its arithmetic.
+// One right-hand side: both passes 0.77 + 0.78 -> 0.63 + 0.58 ms, 0.66 + 0.73 -> 0.45 + 0.41, 0.32 + 0.34
+// -> 0.17 + 0.17.
+//
+// Pass 1: a wavefront takes RB harmonics of one degree, up to four of its radial functions and a range
+// of points; every lane keeps its own sums of PPL points a step (one 16-byte load per row), formed with
+// z_{l,c}(i) = q_l(i) v_c(i), and the sums over the lanes are taken in binary64 at the end, halving the
+// number of values with the number of lanes.
+template <typename T>
+__device__ __forceinline__ void nw_load(const T* __restrict__ p, T (&o)[16 / sizeof(T)]) {
+  typedef typename PVec<T, 16 / sizeof(T)>::type V;
+  const V w = *reinterpret_cast<const V*>(p);
+#pragma unroll
+  for (int e = 0; e < (int)(16 / sizeof(T)); ++e) o[e] = w[e];
+}
+__device__ __forceinline__ float nw_fma(float a, float b, float c) { return fmaf(a, b, c); }
+__device__ __forceinline__ double nw_fma(double a, double b, double c) { return fma(a, b, c); }
+constexpr int kNwSteps = 4;                        // least number of steps (64 PPL points) per split
+__host__ __device__ constexpr int nw_rows(int bytes, int sn, int m) {
+  return bytes == 4 ? (sn * m <= 8 ? 8 : 4) : (sn * m <= 4 ? 8 : (sn * m <= 8 ? 4 : 2));
+}
+
+// Sums over the 64 lanes of N values: the lanes with bit OFF set go on with the upper half of the values,
+// the others with the lower, each taking its half from the lane across; `first` is the index of the sum
+// that a lane ends with (64 / N lanes hold the same one).
+template <int OFF, int N>
+__device__ __forceinline__ double nw_fold(const double (&s)[N], int lane, int& first) {
+  if constexpr (OFF == 0) {
+    return s[0];
+  } else if constexpr (N == 1) {
+    const double t[1] = {s[0] + __shfl_xor(s[0], OFF)};
+    return nw_fold<OFF / 2>(t, lane, first);
+  } else {
+    // bit masks instead of selects: every lane reaches the shuffles by one path
+    const uint64_t up = 0 - (uint64_t)((lane / OFF) & 1);
+    double t[N / 2];
+#pragma unroll
+    for (int j = 0; j < N / 2; ++j) {
+      const uint64_t a = __builtin_bit_cast(uint64_t, s[j]), b = __builtin_bit_cast(uint64_t, s[j + N / 2]);
+      const double give = __builtin_bit_cast(double, (a & up) | (b & ~up));
+      t[j] = __builtin_bit_cast(double, (b & up) | (a & ~up)) + __shfl_xor(give, OFF);
+    }
+    first += (int)up & (N / 2);
+    return nw_fold<OFF / 2>(t, lane, first);
+  }
+}
+
+template <typename T, typename TV, int SN, int M>
+__device__ __forceinline__ void nw_t_item(const T* __restrict__ phi, int64_t ld_phi, const T* __restrict__ q,
+                                          int64_t ld_q, const DegDev& dg, int rb, int l0,
+                                          const TV* __restrict__ V, int64_t ldv, int64_t n, int64_t p_begin,
+                                          int64_t p_end, const double* __restrict__ lam, T* __restrict__ Wn,
+                                          double* __restrict__ W, int64_t w_ld, double* __restrict__ part) {
+  constexpr int PPL = 16 / sizeof(T), RB = nw_rows(sizeof(T), SN, M), NV = RB * SN * M;
+  const int lane = threadIdx.x & 63;
+  const int h0 = rb * RB;
+  T acc[RB][SN][M];
+#pragma unroll
+  for (int r = 0; r < RB; ++r)
+#pragma unroll
+    for (int l = 0; l < SN; ++l)
+#pragma unroll
+      for (int c = 0; c < M; ++c) acc[r][l][c] = 0;
+  for (int64_t p = p_begin; p < p_end; p += 64 * PPL) {
+    const int64_t pl = p + (int64_t)lane * PPL;
+    const int64_t pc = pl < n ? pl : 0;            // lanes past the points read the first ones, times zero
+    T a[RB][PPL], z[SN][PPL];
+    TV v[M][PPL];
+#pragma unroll
+    for (int r = 0; r < RB; ++r) {
+      const int h = h0 + r < dg.nh ? h0 + r : dg.nh - 1;
+      nw_load(phi + (int64_t)(dg.hoff + h) * ld_phi + pc, a[r]);
+    }
+#pragma unroll
+    for (int l = 0; l < SN; ++l) nw_load(q + (int64_t)(dg.qoff + l0 + l) * ld_q + pc, z[l]);
+#pragma unroll
+    for (int e = 0; e < PPL; ++e)
+#pragma unroll
+      for (int c = 0; c < M; ++c) v[c][e] = V[(pl + e < n ? pl + e : 0) * ldv + c];
+#pragma unroll
+    for (int e = 0; e < PPL; ++e) {
+      const bool ok = pl + e < p_end;
+#pragma unroll
+      for (int c = 0; c < M; ++c) {
+        const T vv = ok ? (T)v[c][e] : (T)0;
+#pragma unroll
+        for (int l = 0; l < SN; ++l) {
+          const T zz = z[l][e] * vv;
+#pragma unroll
+          for (int r = 0; r < RB; ++r) acc[r][l][c] = nw_fma(a[r][e], zz, acc[r][l][c]);
+        }
+      }
+    }
+  }
+  // value j = (r SN + l) M + c; padded to a power of two
+  constexpr int NP = NV <= 1 ? 1 : NV <= 2 ? 2 : NV <= 4 ? 4 : NV <= 8 ? 8 : NV <= 16 ? 16 : NV <= 32 ? 32 : 64;
+  static_assert(NV <= 64, "one value per lane at the end");
+  double s[NP];
+#pragma unroll
+  for (int j = 0; j < NP; ++j) s[j] = j < NV ? (double)acc[j / (SN * M) % RB][j / M % SN][j % M] : 0.0;
+  int first = 0;                                   // index of the value this lane ends with
+  s[0] = nw_fold<32>(s, lane, first);
+  const int r = first / (SN * M), l = first / M % SN, c = first % M;
+  constexpr int REP = 64 / NP;                     // lanes with the same value
+  if (first < NV && h0 + r < dg.nh && lane % REP == 0) {
+    const int64_t row = dg.roff + (int64_t)(h0 + r) * dg.s + l0 + l;
+    if (part) {
+      part[row * M + c] = s[0];
+    } else {
+      if (Wn) Wn[row * M + c] = (T)(lam[row] * s[0]);
+      if (W) W[row * w_ld + c] = s[0];
+    }
+  }
+}
+
+// Items of pass 1 over the degrees: row blocks of each group of up to four radial functions.
+template <typename T, typename TV, int M>
+__device__ __forceinline__ void nw_t(int item, int split, const T* __restrict__ phi, int64_t ld_phi,
+                                     const T* __restrict__ q, int64_t ld_q, const DegDev* __restrict__ degs, int n_deg,
+                                     const TV* __restrict__ V, int64_t ldv, int64_t n, int64_t split_len,
+                                     int64_t rank, const double* __restrict__ lam, T* __restrict__ Wn,
+                                     double* __restrict__ W, int64_t w_ld, double* __restrict__ part) {
+  DegDev dg = degs[0];
+  int l0 = 0, sn = 0;
+  for (int di = 0; di < n_deg; ++di) {
+    dg = degs[di];
+    bool here = false;
+    for (l0 = 0; l0 < dg.s; l0 += 4) {
+      sn = dg.s - l0 < 4 ? dg.s - l0 : 4;
+      const int rows = nw_rows(sizeof(T), sn, M), nrb = (dg.nh + rows - 1) / rows;
+      if (item < nrb) {
+        here = true;
+        break;
+      }
+      item -= nrb;
+    }
+    if (here) break;
+  }
+  const int64_t p_begin = (int64_t)split * split_len;
+  const int64_t p_end = p_begin + split_len < n ? p_begin + split_len : n;
+  double* out = part ? part + (int64_t)split * rank * M : nullptr;
+  switch (sn) {                                    // uniform
+    case 1: nw_t_item<T, TV, 1, M>(phi, ld_phi, q, ld_q, dg, item, l0, V, ldv, n, p_begin, p_end, lam, Wn, W, w_ld, out); break;
+    case 2: nw_t_item<T, TV, 2, M>(phi, ld_phi, q, ld_q, dg, item, l0, V, ldv, n, p_begin, p_end, lam, Wn, W, w_ld, out); break;
+    case 3: nw_t_item<T, TV, 3, M>(phi, ld_phi, q, ld_q, dg, item, l0, V, ldv, n, p_begin, p_end, lam, Wn, W, w_ld, out); break;
+    default: nw_t_item<T, TV, 4, M>(phi, ld_phi, q, ld_q, dg, item, l0, V, ldv, n, p_begin, p_end, lam, Wn, W, w_ld, out); break;
+  }
+}
+
+// Wavefront w of block b takes item 4 gi + w of split sp, b = 8 (G (sp / 8) + gi) + sp % 8: the items of
+// one range of points run on one XCD, close in time, and share V and the radial rows in its L2.
+template <typename T, typename TV, int M>
+__global__ void __launch_bounds__(256) k_nw_t(const T* __restrict__ phi, int64_t ld_phi, const T* __restrict__ q,
+                                              int64_t ld_q, const DegDev* __restrict__ degs, int n_deg, int n_items,
+                                              int n_splits, int64_t split_len, const TV* __restrict__ V, int64_t ldv,
+                                              int64_t n, int64_t rank, const double* __restrict__ lam,
+                                              T* __restrict__ Wn, double* __restrict__ W, int64_t w_ld,
+                                              double* __restrict__ part) {
+  const int groups = (n_items + 3) / 4;
+  const int rest = (int)(blockIdx.x >> 3), gi = rest % groups, split = ((rest / groups) << 3) + (blockIdx.x & 7);
+  const int item = 4 * gi + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  if (split >= n_splits || item >= n_items) return;
+  nw_t<T, TV, M>(item, split, phi, ld_phi, q, ld_q, degs, n_deg, V, ldv, n, split_len, rank, lam, Wn, W, w_ld, part);
+}
+
+// Sum of pass 1's splits (wavefront w takes the splits w, w + 4, ...), scaled copy and unscaled sums.
+template <typename T>
+__device__ __forceinline__ void nw_reduce(int bx, const double* __restrict__ part, int n_splits, int64_t total, int M,
+                                          const double* __restrict__ lam, T* __restrict__ Wn, double* __restrict__ W,
+                                          int64_t w_ld) {
+  __shared__ double red[4][64];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int64_t e = (int64_t)bx * 64 + lane;
+  const double* p = part + (e < total ? e : 0);
+  double acc[4] = {0, 0, 0, 0};
+  int sp = w;
+  for (; sp + 12 < n_splits; sp += 16)
+#pragma unroll
+    for (int u = 0; u < 4; ++u) acc[u] += p[(int64_t)(sp + 4 * u) * total];
+  for (; sp < n_splits; sp += 4) acc[0] += p[(int64_t)sp * total];
+  red[w][lane] = (acc[0] + acc[1]) + (acc[2] + acc[3]);
+  __syncthreads();
+  if (w != 0 || e >= total) return;
+  const double v = (red[0][lane] + red[1][lane]) + (red[2][lane] + red[3][lane]);
+  const int64_t row = e / M;
+  if (Wn) Wn[e] = (T)(lam[row] * v);
+  if (W) W[row * w_ld + (e - row * M)] = v;
+}
+
+template <typename T>
+__global__ void __launch_bounds__(256) k_nw_reduce(const double* __restrict__ part, int n_splits, int64_t total, int M,
+                                                    const double* __restrict__ lam, T* __restrict__ Wn,
+                                                    double* __restrict__ W, int64_t w_ld) {
+  nw_reduce(blockIdx.x, part, n_splits, total, M, lam, Wn, W, w_ld);
+}
+
+// Pass 2: a lane takes PPL points, the harmonic rows [z_lo, z_hi) stream by (one 16-byte load per row),
+// their rows of D W are wavefront-uniform values.  Per degree the sums over the harmonics are kept for
+// each radial function (up to four at a time) and folded into KV with its radial values.
+template <typename T, int SN, int M>
+__device__ __forceinline__ void nw_n_degree(const T* __restrict__ phi, int64_t ld_phi, const T* __restrict__ q,
+                                            int64_t ld_q, const DegDev& dg, int l0, int hlo, int hhi,
+                                            const T* __restrict__ Wn, T (&kv)[M][16 / sizeof(T)]) {
+  constexpr int PPL = 16 / sizeof(T), U = 8;
+  T t[SN][M][PPL];
+#pragma unroll
+  for (int l = 0; l < SN; ++l)
+#pragma unroll
+    for (int c = 0; c < M; ++c)
+#pragma unroll
+      for (int e = 0; e < PPL; ++e) t[l][c][e] = 0;
+  const T* row = phi + (int64_t)(dg.hoff + hlo) * ld_phi;
+  const T* w = Wn + ((int64_t)dg.roff + (int64_t)hlo * dg.s + l0) * M;
+  const int64_t ws = (int64_t)dg.s * M;
+  int h = hlo;
+  for (; h + U <= hhi; h += U) {
+    T a[U][PPL];
+#pragma unroll
+    for (int u = 0; u < U; ++u) nw_load(row + (int64_t)u * ld_phi, a[u]);
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int l = 0; l < SN; ++l)
+#pragma unroll
+        for (int c = 0; c < M; ++c) {
+          const T wv = w[u * ws + l * M + c];
+#pragma unroll
+          for (int e = 0; e < PPL; ++e) t[l][c][e] = nw_fma(a[u][e], wv, t[l][c][e]);
+        }
+    row += U * ld_phi;
+    w += U * ws;
+  }
+  for (; h < hhi; ++h) {
+    T a[PPL];
+    nw_load(row, a);
+#pragma unroll
+    for (int l = 0; l < SN; ++l)
+#pragma unroll
+      for (int c = 0; c < M; ++c) {
+        const T wv = w[l * M + c];
+#pragma unroll
+        for (int e = 0; e < PPL; ++e) t[l][c][e] = nw_fma(a[e], wv, t[l][c][e]);
+      }
+    row += ld_phi;
+    w += ws;
+  }
+#pragma unroll
+  for (int l = 0; l < SN; ++l) {
+    T ql[PPL];
+    nw_load(q + (int64_t)(dg.qoff + l0 + l) * ld_q, ql);
+#pragma unroll
+    for (int c = 0; c < M; ++c)
+#pragma unroll
+      for (int e = 0; e < PPL; ++e) kv[c][e] = nw_fma(ql[e], t[l][c][e], kv[c][e]);
+  }
+}
+
+template <typename T, typename TO, int M>
+__device__ __forceinline__ void nw_n(int64_t bx, int z, const T* __restrict__ phi, int64_t ld_phi,
+                                     const T* __restrict__ q, int64_t ld_q, const DegDev* __restrict__ degs, int n_deg,
+                                     const T* __restrict__ Wn, TO* __restrict__ KV, int64_t ldkv,
+                                     int64_t n, int z_rows, T* __restrict__ shares) {
+  constexpr int PPL = 16 / sizeof(T);
+  const int lane = threadIdx.x;
+  const int64_t pl = bx * (64 * PPL) + (int64_t)lane * PPL;
+  const int64_t pc = pl < n ? pl : 0;              // lanes past the points read the first ones and write nothing
+  const int z_lo = shares ? z * z_rows : 0, z_hi = shares ? z_lo + z_rows : 0x7fffffff;
+  T kv[M][PPL];
+#pragma unroll
+  for (int c = 0; c < M; ++c)
+#pragma unroll
+    for (int e = 0; e < PPL; ++e) kv[c][e] = 0;
+  for (int di = 0; di < n_deg; ++di) {
+    const DegDev dg = degs[di];
+    const int hlo = z_lo > dg.hoff ? z_lo - dg.hoff : 0;
+    const int hhi = z_hi - dg.hoff < dg.nh ? z_hi - dg.hoff : dg.nh;
+    if (hlo >= hhi) continue;
+    for (int l0 = 0; l0 < dg.s; l0 += 4) {
+      switch (dg.s - l0) {                         // uniform
+        case 1: nw_n_degree<T, 1, M>(phi + pc, ld_phi, q + pc, ld_q, dg, l0, hlo, hhi, Wn, kv); break;
+        case 2: nw_n_degree<T, 2, M>(phi + pc, ld_phi, q + pc, ld_q, dg, l0, hlo, hhi, Wn, kv); break;
+        case 3: nw_n_degree<T, 3, M>(phi + pc, ld_phi, q + pc, ld_q, dg, l0, hlo, hhi, Wn, kv); break;
+        default: nw_n_degree<T, 4, M>(phi + pc, ld_phi, q + pc, ld_q, dg, l0, hlo, hhi, Wn, kv); break;
+      }
+    }
+  }
+#pragma unroll
+  for (int e = 0; e < PPL; ++e)
+    if (pl + e < n) {
+#pragma unroll
+      for (int c = 0; c < M; ++c) {
+        if (shares) shares[((int64_t)z * n + pl + e) * M + c] = kv[c][e];
+        else KV[(pl + e) * ldkv + c] = (TO)kv[c][e];
+      }
+    }
+}
+
+template <typename T, typename TO, int M>
+__global__ void __launch_bounds__(64) k_nw_n(const T* __restrict__ phi, int64_t ld_phi, const T* __restrict__ q,
+                                             int64_t ld_q, const DegDev* __restrict__ degs, int n_deg,
+                                             const T* __restrict__ Wn, TO* __restrict__ KV, int64_t ldkv,
+                                             int64_t n, int z_rows, T* __restrict__ shares) {
+  nw_n<T, TO, M>(blockIdx.x, blockIdx.z, phi, ld_phi, q, ld_q, degs, n_deg, Wn, KV, ldkv, n, z_rows, shares);
+}
+
 // The products of many binary64 factors with one right-hand side each, a launch per phase over all of
 // them (blockIdx.y: the factor).  Launched one by one, thirty factors of 460 points and rank 1,290 took
-// 120 launches of a few workgroups, and the host's enqueueing bounded the KRR operator: 0.69 ms with
-// them on four streams, 0.45 ms so (0.30 of it the off-diagonal kernel beside them).
-__global__ void __launch_bounds__(kMvtThreads) __attribute__((amdgpu_waves_per_eu(MvtWaves<double, 1>::value, 8)))
-k_mvb_t(const MvBatch* __restrict__ batch, const double* __restrict__ v) {
+// 120 launches of a few workgroups, and the host's enqueueing bounded the KRR operator.
+__global__ void __launch_bounds__(256) k_nwb_t(const MvBatch* __restrict__ batch, const double* __restrict__ v) {
   const MvBatch f = batch[blockIdx.y];
-  if ((int)blockIdx.x >= (f.n_splits + 7) / 8 * 8 * f.n_groups) return;
-  mvt_tile<double, double, 1>(blockIdx.x, f.phi, f.ld, f.q, f.ld, f.waves, f.rank_rows, f.groups, f.n_groups,
-                              f.n_splits, f.split_len, v + f.pos, 1, f.n, 1, 16, f.rank, f.part);
+  const int groups = (f.n_items + 3) / 4;
+  const int gi = (int)blockIdx.x % groups, split = (int)blockIdx.x / groups;
+  const int item = 4 * gi + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  if (split >= f.n_splits || item >= f.n_items) return;
+  nw_t<double, double, 1>(item, split, f.phi, f.ld, f.q, f.ld, f.degs, f.n_deg, v + f.pos, 1, f.n, f.split_len, f.rank,
+                          f.lam, f.Wn, nullptr, 1, f.n_splits > 1 ? f.part : nullptr);
 }
 
-__global__ void __launch_bounds__(256) k_mvb_reduce(const MvBatch* __restrict__ batch) {
+__global__ void __launch_bounds__(256) k_nwb_reduce(const MvBatch* __restrict__ batch) {
   const MvBatch f = batch[blockIdx.y];
-  if ((int64_t)blockIdx.x * 64 >= f.n_blocks * 256) return;
-  mv_reduce<double>(blockIdx.x, f.part, f.n_splits, f.rank * 16, f.n_blocks * 256, 16, f.src, f.lam, nullptr, nullptr,
-                    f.Wb);
+  if (f.n_splits <= 1 || (int64_t)blockIdx.x * 64 >= f.rank) return;
+  nw_reduce<double>(blockIdx.x, f.part, f.n_splits, f.rank, 1, f.lam, f.Wn, nullptr, 1);
 }
 
-__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(MvnWaves<double, 1>::value, 8)))
-k_mvb_n(const MvBatch* __restrict__ batch) {
+__global__ void __launch_bounds__(64) k_nwb_n(const MvBatch* __restrict__ batch) {
   const MvBatch f = batch[blockIdx.y];
-  if ((int)blockIdx.z >= f.nz) return;
-  mv_n<double, double, 1, true>(blockIdx.x, blockIdx.z, f.phi, f.ld, f.q, f.ld, f.degs, f.n_deg, f.Wb, 16, nullptr, 1,
-                                f.n, 1, f.z_blocks, (int)f.n_blocks, f.shares);
+  if ((int)blockIdx.z >= f.nz || (int64_t)blockIdx.x * 128 >= f.n) return;
+  nw_n<double, double, 1>(blockIdx.x, blockIdx.z, f.phi, f.ld, f.q, f.ld, f.degs, f.n_deg, f.Wn, nullptr, 1, f.n,
+                          f.z_rows, f.shares);
 }
 
-__global__ void __launch_bounds__(256) k_mvb_sum(const MvBatch* __restrict__ batch, double* __restrict__ out) {
+__global__ void __launch_bounds__(256) k_nwb_sum(const MvBatch* __restrict__ batch, double* __restrict__ out) {
   const MvBatch f = batch[blockIdx.y];
   if ((int64_t)blockIdx.x * 64 >= f.n) return;
   mv_n_sum<double, double>(blockIdx.x, f.shares, f.nz, f.n, 1, out + f.pos, 1);
@@ -1892,14 +2204,97 @@ __global__ void __launch_bounds__(256) k_mvb_sum(const MvBatch* __restrict__ bat
 
 hipError_t launch_matvec_batch(const MvBatch* batch_dev, const MvBatchGrid& g, const double* v, double* out,
                                hipStream_t s) {
-  if (g.factors < 1 || g.t_blocks < 1 || g.r_blocks < 1 || g.n_blocks < 1 || g.shares < 1) return hipErrorInvalidValue;
+  if (g.factors < 1 || g.t_blocks < 1 || g.n_blocks < 1 || g.shares < 1) return hipErrorInvalidValue;
   const unsigned nf = (unsigned)g.factors;
-  k_mvb_t<<<dim3((unsigned)g.t_blocks, nf), kMvtThreads, matvec_tile_lds_bytes(16, 0), s>>>(batch_dev, v);
-  k_mvb_reduce<<<dim3((unsigned)g.r_blocks, nf), 256, 0, s>>>(batch_dev);
-  k_mvb_n<<<dim3((unsigned)((g.n_blocks + 7) / 8 * 8), nf, (unsigned)g.shares), 64, 0, s>>>(batch_dev);
-  k_mvb_sum<<<dim3((unsigned)g.n_blocks, nf), 256, 0, s>>>(batch_dev, out);
+  k_nwb_t<<<dim3((unsigned)g.t_blocks, nf), 256, 0, s>>>(batch_dev, v);
+  if (g.r_blocks > 0) k_nwb_reduce<<<dim3((unsigned)g.r_blocks, nf), 256, 0, s>>>(batch_dev);
+  k_nwb_n<<<dim3((unsigned)((g.n_blocks + 1) / 2), nf, (unsigned)g.shares), 64, 0, s>>>(batch_dev);
+  k_nwb_sum<<<dim3((unsigned)g.n_blocks, nf), 256, 0, s>>>(batch_dev, out);
   return hipGetLastError();
 }
+
+int narrow_items(const DegDev* degs, int n_deg, int prec, int m) {
+  int items = 0;
+  for (int di = 0; di < n_deg; ++di)
+    for (int l0 = 0; l0 < degs[di].s; l0 += 4) {
+      const int rows = nw_rows(prec == 1 ? 4 : 8, std::min(4, degs[di].s - l0), m);
+      items += (degs[di].nh + rows - 1) / rows;
+    }
+  return items;
+}
+
+void narrow_splits(int64_t n, int n_items, int prec, int64_t per_split_bytes, int64_t most_bytes, int* n_splits,
+                   int64_t* split_len) {
+  const int64_t step = 64 * (prec == 1 ? 4 : 2);
+  int64_t ns = std::max<int64_t>(1, 8192 / std::max(1, n_items));
+  ns = std::min(ns, std::max<int64_t>(1, n / (step * kNwSteps)));
+  ns = std::min(ns, std::max<int64_t>(1, most_bytes / per_split_bytes));
+  const int64_t len = ((n + ns - 1) / ns + step - 1) / step * step;
+  *split_len = len;
+  *n_splits = (int)((n + len - 1) / len);
+}
+
+#define HDF_NW_M(CALL, T, TV)                                                                                \
+  do {                                                                                                       \
+    if (m == 1) CALL(T, TV, 1);                                                                              \
+    else if (m == 2) CALL(T, TV, 2);                                                                         \
+    else if (m == 3) CALL(T, TV, 3);                                                                         \
+    else CALL(T, TV, 4);                                                                                     \
+  } while (0)
+#define HDF_NW(CALL)                                                                                         \
+  do {                                                                                                       \
+    if (prec == 1 && io == 0) HDF_NW_M(CALL, float, float);                                                  \
+    else if (prec == 0 && io == 1) HDF_NW_M(CALL, double, double);                                           \
+    else if (prec == 0 && io == 0) HDF_NW_M(CALL, double, float);                                            \
+    else return hipErrorInvalidValue;                                                                        \
+  } while (0)
+
+hipError_t launch_narrow_t(const void* phi, int64_t ld_phi, const void* q, int64_t ld_q, const DegDev* degs, int n_deg,
+                           int n_items, int n_splits, int64_t split_len, const void* V, int64_t ldv, int64_t n, int m,
+                           int64_t rank, const double* lam, void* Wn, double* W, int64_t w_ld, double* part, int prec,
+                           int io, hipStream_t s) {
+  const int64_t step = 64 * (prec == 1 ? 4 : 2);
+  if (m < 1 || m > kNwMax || n_deg < 1 || n_items < 1 || n_splits < 1 || split_len % step) return hipErrorInvalidValue;
+  if ((int64_t)(n_splits - 1) * split_len >= n || (int64_t)n_splits * split_len < n) return hipErrorInvalidValue;
+  if (n_splits > 1 && !part) return hipErrorInvalidValue;
+  double* dst = n_splits > 1 ? part : nullptr;
+  const unsigned nb = (unsigned)(((n_splits + 7) / 8) * 8 * ((n_items + 3) / 4));
+#define NW_T(T, TV, M)                                                                                        \
+  k_nw_t<T, TV, M><<<nb, 256, 0, s>>>((const T*)phi, ld_phi, (const T*)q, ld_q, degs, n_deg, n_items, n_splits, \
+                                      split_len, (const TV*)V, ldv, n, rank, lam, (T*)Wn, W, w_ld, dst)
+  HDF_NW(NW_T);
+#undef NW_T
+  if (n_splits > 1) {
+    const int64_t total = rank * m;
+    const unsigned rb = (unsigned)((total + 63) / 64);
+    if (prec == 1) k_nw_reduce<float><<<rb, 256, 0, s>>>(part, n_splits, total, m, lam, (float*)Wn, W, w_ld);
+    else k_nw_reduce<double><<<rb, 256, 0, s>>>(part, n_splits, total, m, lam, (double*)Wn, W, w_ld);
+  }
+  return hipGetLastError();
+}
+
+hipError_t launch_narrow_n(const void* phi, int64_t ld_phi, const void* q, int64_t ld_q, const DegDev* degs, int n_deg,
+                           const void* Wn, void* KV, int64_t ldkv, int64_t n, int m, int n_rows, int z_rows,
+                           void* shares, int prec, int io, hipStream_t s) {
+  if (m < 1 || m > kNwMax || n_deg < 1 || n_rows < 1) return hipErrorInvalidValue;
+  const int nz = z_rows > 0 ? (n_rows + z_rows - 1) / z_rows : 1;
+  if (nz > 1 && !shares) return hipErrorInvalidValue;
+  void* sh = nz > 1 ? shares : nullptr;
+  const int64_t step = 64 * (prec == 1 ? 4 : 2);
+  const dim3 grid((unsigned)((n + step - 1) / step), 1, (unsigned)nz);
+  const unsigned nb = (unsigned)((n * m + 63) / 64);
+#define NW_N(T, TO, M)                                                                                          \
+  do {                                                                                                          \
+    k_nw_n<T, TO, M><<<grid, 64, 0, s>>>((const T*)phi, ld_phi, (const T*)q, ld_q, degs, n_deg, (const T*)Wn,   \
+                                         (TO*)KV, ldkv, n, z_rows, (T*)sh);                                    \
+    if (nz > 1) k_mv_n_sum<T, TO><<<nb, 256, 0, s>>>((const T*)sh, nz, n, m, (TO*)KV, ldkv);                    \
+  } while (0)
+  HDF_NW(NW_N);
+#undef NW_N
+  return hipGetLastError();
+}
+#undef HDF_NW
+#undef HDF_NW_M
 
 constexpr int kMvNctF = 4;   // column tiles per item of k_mv_t, binary32
 constexpr int kMvNctD = 2;   // column tiles per item of k_mv_t, binary64

@@ -166,23 +166,35 @@ hipError_t launch_matvec_n(const void* phi, int64_t ld_phi, const void* q, int64
                            void* KV, int64_t ldkv, int64_t n, int m, int prec, int io, int z_blocks,
                            void* part, hipStream_t s);
 
+// Narrow products: 1 <= m <= kNwMax right-hand sides, on the vector units.  Pass 1 runs n_items (row
+// blocks) x n_splits wavefronts and leaves Wn[row][c] = lambda_row W (storage type, stride m) and, where
+// wanted, W (binary64, stride w_ld), by way of part (n_splits x rank x m) when there are several splits.
+// Pass 2 forms KV from Wn; z_rows > 0 splits the n_rows harmonics into shares (shares x n x m values).
+constexpr int kNwMax = 4;
+int narrow_items(const DegDev* degs_host, int n_deg, int prec, int m);
+void narrow_splits(int64_t n, int n_items, int prec, int64_t per_split_bytes, int64_t most_bytes, int* n_splits,
+                   int64_t* split_len);
+hipError_t launch_narrow_t(const void* phi, int64_t ld_phi, const void* q, int64_t ld_q, const DegDev* degs, int n_deg,
+                           int n_items, int n_splits, int64_t split_len, const void* V, int64_t ldv, int64_t n, int m,
+                           int64_t rank, const double* lam, void* Wn, double* W, int64_t w_ld, double* part, int prec,
+                           int io, hipStream_t s);
+hipError_t launch_narrow_n(const void* phi, int64_t ld_phi, const void* q, int64_t ld_q, const DegDev* degs, int n_deg,
+                           const void* Wn, void* KV, int64_t ldkv, int64_t n, int m, int n_rows, int z_rows,
+                           void* shares, int prec, int io, hipStream_t s);
+
 // Products of several binary64 factors, one right-hand side each (entries [pos, pos + n) of v and out).
 struct MvBatch {
   const double *phi, *q;
-  int64_t ld, n, pos, rank, n_blocks, split_len;
-  const MvtWave* waves;
-  const MvtRankRow* rank_rows;
-  const MvtGroup* groups;
+  int64_t ld, n, pos, rank, split_len;
   const DegDev* degs;
-  const int32_t* src;
   const double* lam;
-  double *part, *Wb, *shares;
-  int32_t n_groups, n_splits, n_deg, z_blocks, nz, pad;
+  double *part, *Wn, *shares;
+  int32_t n_items, n_splits, n_deg, z_rows, nz, pad;
 };
 struct MvBatchGrid {
   int factors;      // descriptors
   int t_blocks;     // largest number of pass-1 workgroups, ...
-  int r_blocks;     // ... of 64-entry groups of the reduction,
+  int r_blocks;     // ... of 64-row groups of the reduction (0: no factor has several splits),
   int n_blocks;     // ... of 64-point groups
   int shares;       // ... and of shares of pass 2
 };

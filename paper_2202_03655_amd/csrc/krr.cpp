@@ -24,15 +24,21 @@ namespace {
 constexpr int kMaxBlock = 16384;   // largest cluster: its dense block is 2 GiB
 constexpr int kBatch = 8;          // CG iterations enqueued per convergence check
 
+// Device memory from the library's allocator cache, given back after the device is idle.
 struct Buf {
   void* p = nullptr;
-  ~Buf() {
-    if (p) hipFree(p);
-  }
-  hipError_t alloc(size_t bytes) {
-    if (p) hipFree(p);
+  size_t bytes = 0;
+  int dev = 0;
+  ~Buf() { release(); }
+  void release() {
+    if (!p) return;
+    (void)hipDeviceSynchronize();
+    hdf::pool_release(p, bytes, dev);
     p = nullptr;
-    return hipMalloc(&p, std::max<size_t>(bytes, 256));
+  }
+  hipError_t alloc(size_t b) {
+    release();
+    return hdf::pool_alloc(&p, std::max<size_t>(b, 256), &bytes, &dev);
   }
   template <class T>
   T* as() const {

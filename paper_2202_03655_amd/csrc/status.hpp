@@ -15,6 +15,10 @@ void clear_error();
 // Switch the HIP events around a factor's products on or off (hdf_info then
 // reports no kernel times for them).  Products on many small factors use off.
 void set_product_timing(hdf_handle h, bool on);
+// The library's caching device allocator: a block of at least b bytes, its size and device; a block is
+// given back only when no enqueued work can use it.
+hipError_t pool_alloc(void** p, size_t b, size_t* got, int* dev);
+void pool_release(void* p, size_t bytes, int dev);
 // Products of several stored binary64 factors with one right-hand side each: the entries
 // [pos, pos + n) of v and out belong to the factor at pos.  The factors outlive the batch.
 struct ProductBatch;
