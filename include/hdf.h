@@ -254,8 +254,9 @@ hdf_status hdf_matvec_noalloc(hdf_handle h, const void* V, int64_t m, int64_t ld
  *   dlength  host, receives dF/dl (NULL: not computed).
  *   dX       device, n x d with leading dimension lddx (>= d), receives dF/dX
  *            (NULL: not computed); same dtype as the points.
- * One blocking synchronisation (U^T V and U^T W come to the host), two the
- * first time dF/dX is asked of a handle.  dF/dX needs a stored factor
+ * One blocking synchronisation when dF/dl is asked (U^T V and U^T W come to
+ * the host), one more the first time that dF/dX is asked for a dimension and
+ * largest degree (the derivative maps of its harmonics go to the device).  dF/dX needs a stored factor
  * (HDF_STORE_FACTOR) whose kept degrees are 0..K; otherwise HDF_E_ARG before
  * any device work.  It is formed from the stored factor: the stored harmonic
  * rows are solid harmonics, homogeneous harmonic polynomials of the scaled

@@ -258,7 +258,8 @@ struct hdf_factor {
   DevBuf dq, dq_coef, adj_degs, adj_c2, adj_cs, adj_kv2, adj_kvs;
   std::vector<hdf::DegDev> adj_degs_host;
   int64_t r_shift = 0, shift_blocks = 0;
-  std::vector<char> adj_c2_host, adj_cs_host;
+  std::vector<char> dq_coef_host;                 // outlives its upload
+  std::shared_ptr<struct AdjMap> adj_map;
   hdf::BuildTables tables{};
   ~hdf_factor() {
     // the device buffers go back to the allocator cache once no enqueued work can use them
@@ -1903,8 +1904,76 @@ hdf_status hdf_matvec_noalloc(hdf_handle h, const void* V, int64_t m, int64_t ld
   return HDF_OK;
 }
 
+// The derivative maps of the harmonic basis on the device: dS_{k,h}/dx_j = sum_h' G_k^(j)[h][h'] S_{k-1,h'},
+// rows (k, j, h') with their harmonics h of degree k.  They depend on the dimension and the largest
+// degree only and are fitted once (harmonic_derivative_maps); entries below 1e-12 of a degree's largest
+// are rounding of the fit (the exact ones are square roots of ratios of small integers) and are left
+// out.  The last kAdjMaps used are kept for the process; a handle holds the one it has enqueued work on.
+struct AdjMap {
+  int dev = 0, d = 0, K = 0;
+  DevBuf row, h, v;
+};
+constexpr size_t kAdjMaps = 8;
+
+static hdf_status adjoint_map(hdf_handle f, int Kh, hipStream_t s, std::shared_ptr<AdjMap>* out) {
+  static std::mutex* mu = new std::mutex;
+  static auto* kept = new std::vector<std::shared_ptr<AdjMap>>;   // least recently used first
+  const int d = f->d;
+  int dev = 0;
+  HIPCHK(hipGetDevice(&dev));
+  std::lock_guard<std::mutex> lk(*mu);
+  for (size_t i = 0; i < kept->size(); ++i)
+    if ((*kept)[i]->dev == dev && (*kept)[i]->d == d && (*kept)[i]->K == Kh) {
+      *out = (*kept)[i];
+      kept->erase(kept->begin() + i);
+      kept->push_back(*out);
+      return HDF_OK;
+    }
+  hdf::ChainCoeffs cc;
+  hdf::chain_coeffs(d, Kh, cc);
+  std::vector<int> rows_k(Kh + 1);
+  for (int k = 0; k <= Kh; ++k) rows_k[k] = f->degs[k].hoff;
+  std::vector<std::vector<double>> g;
+  hdf::harmonic_derivative_maps(d, Kh, cc, f->col_of_host.data(), (int)f->H, rows_k, g);
+  std::vector<int32_t> row(1, 0), hh;
+  std::vector<double> val;
+  for (int k = 1; k <= Kh; ++k) {
+    const int n0 = f->degs[k].nh, n1 = f->degs[k - 1].nh;
+    double big = 0.0;
+    for (double x : g[k]) big = std::max(big, std::fabs(x));
+    for (int j = 0; j < d; ++j)
+      for (int hp = 0; hp < n1; ++hp) {
+        for (int h0 = 0; h0 < n0; ++h0) {
+          const double x = g[k][((size_t)j * n0 + h0) * n1 + hp];
+          if (std::fabs(x) > 1e-12 * big) {
+            hh.push_back(h0);
+            val.push_back(x);
+          }
+        }
+        row.push_back((int32_t)hh.size());
+      }
+  }
+  auto m = std::make_shared<AdjMap>();
+  m->dev = dev;
+  m->d = d;
+  m->K = Kh;
+  HIPCHK(m->row.ensure(row.size() * 4));
+  HIPCHK(m->h.ensure(std::max<size_t>(hh.size(), 1) * 4));
+  HIPCHK(m->v.ensure(std::max<size_t>(val.size(), 1) * 8));
+  HIPCHK(hipMemcpyAsync(m->row.p, row.data(), row.size() * 4, hipMemcpyHostToDevice, s));
+  if (!hh.empty()) {
+    HIPCHK(hipMemcpyAsync(m->h.p, hh.data(), hh.size() * 4, hipMemcpyHostToDevice, s));
+    HIPCHK(hipMemcpyAsync(m->v.p, val.data(), val.size() * 8, hipMemcpyHostToDevice, s));
+  }
+  HIPCHK(hipStreamSynchronize(s));                 // other streams may use the map from here on
+  if (kept->size() >= kAdjMaps) kept->erase(kept->begin());
+  kept->push_back(m);
+  *out = m;
+  return HDF_OK;
+}
+
 // dF/dX by factor contractions (the formula above k_radial in kernels.hip): with Gv = C U^T V and
-// Gw = C U^T W (binary64, rank rows with stride gstride), the product of U' = phi q' with [Gv | Gw]
+// Gw = C U^T W (binary64, device, rank rows with stride gstride), the product of U' = phi q' with [Gv | Gw]
 // and of the shifted factor S_{k-1} q_k with [G^(j)T Gv | G^(j)T Gw] for every direction j, then the
 // pointwise combination.  Needs the kept degrees to be 0..K (every degree-(k-1) harmonic stored).
 static hdf_status adjoint_dx(hdf_handle h, const double* gv, const double* gw, int64_t gstride, int m,
@@ -1913,23 +1982,11 @@ static hdf_status adjoint_dx(hdf_handle h, const double* gv, const double* gw, i
   const int Kh = h->kept_k.back();
   const size_t fel = h->felem();
   const int io = h->fprec == 1 ? 0 : 1;          // contraction outputs in the factor's type
-  // derivative maps of the harmonic basis: depend on d and the degrees only, kept per process
-  static std::mutex maps_mu;
-  static std::map<std::pair<int, int>, std::vector<std::vector<double>>> maps;
-  const std::vector<std::vector<double>>* G = nullptr;
   {
-    std::lock_guard<std::mutex> lk(maps_mu);
-    auto it = maps.find({d, Kh});
-    if (it == maps.end()) {
-      hdf::ChainCoeffs cc;
-      hdf::chain_coeffs(d, Kh, cc);
-      std::vector<int> rows_k(Kh + 1);
-      for (int k = 0; k <= Kh; ++k) rows_k[k] = h->degs[k].hoff;
-      std::vector<std::vector<double>> g;
-      hdf::harmonic_derivative_maps(d, Kh, cc, h->col_of_host.data(), (int)h->H, rows_k, g);
-      it = maps.emplace(std::make_pair(d, Kh), std::move(g)).first;
-    }
-    G = &it->second;
+    std::shared_ptr<AdjMap> map;
+    const hdf_status st = adjoint_map(h, Kh, s, &map);
+    if (st != HDF_OK) return st;
+    h->adj_map = map;
   }
   // shifted-factor degrees: harmonics of k - 1 with the radial rows and rank of degree k
   if (h->adj_degs_host.empty() && Kh >= 1) {
@@ -1964,7 +2021,7 @@ static hdf_status adjoint_dx(hdf_handle h, const double* gv, const double* gw, i
         dc.insert(dc.end(), b.begin(), b.begin() + L);
       }
     }
-    std::vector<char>& keep = h->adj_c2_host;   // reused below; the coefficients go first
+    std::vector<char>& keep = h->dq_coef_host;
     keep.assign(dc.size() * fel, 0);
     if (fel == 4)
       for (size_t i = 0; i < dc.size(); ++i) ((float*)keep.data())[i] = (float)dc[i];
@@ -1976,72 +2033,32 @@ static hdf_status adjoint_dx(hdf_handle h, const double* gv, const double* gw, i
     HIPCHK(hdf::launch_radial(h->x_soa.p, h->dtype, h->ldN, h->N, d, (const hdf::GeoDev*)h->geo_dev.p, h->u0,
                               h->u1, h->tables.q_len, h->tables.q_off, h->dq_coef.p, (int)h->S, 2.0 / (h->u1 - h->u0),
                               h->fprec, h->dq.p, h->ldN, s));
-    HIPCHK(hipStreamSynchronize(s));             // the coefficient copy above is read before keep is reused
   }
   // coefficients: C2 = [lambda gv | lambda gw] (rank x 2m), Cs = [G^(j)T C2]_j (shifted rank x 2m d)
-  const int c2s = (m2 + 15) / 16 * 16, css = (md2 + 15) / 16 * 16;
-  std::vector<double> C2((size_t)h->r * m2), Cs((size_t)std::max<int64_t>(h->r_shift, 1) * md2, 0.0);
-  for (size_t di = 0; di < h->degs.size(); ++di) {
-    const hdf::DegDev& dg = h->degs[di];
-    const hdf::DegreeFactor& df = h->deg[h->kept_k[di]];
-    for (int hh = 0; hh < dg.nh; ++hh)
-      for (int l = 0; l < dg.s; ++l) {
-        const int64_t row = dg.roff + (int64_t)hh * dg.s + l;
-        for (int c = 0; c < m; ++c) {
-          C2[row * m2 + c] = df.lam[l] * gv[row * gstride + c];
-          C2[row * m2 + m + c] = df.lam[l] * gw[row * gstride + c];
-        }
-      }
-  }
-  for (int k = 1; k <= Kh; ++k) {
-    const hdf::DegDev& dg = h->degs[k];
-    const hdf::DegDev& e = h->adj_degs_host[k - 1];
-    const int n0 = dg.nh, n1 = e.nh, sk = dg.s;
-    const std::vector<double>& gk = (*G)[k];
-    for (int j = 0; j < d; ++j)
-      for (int hp = 0; hp < n1; ++hp)
-        for (int l = 0; l < sk; ++l) {
-          double* out = &Cs[(e.roff + (int64_t)hp * sk + l) * md2 + (int64_t)j * m2];
-          for (int hh = 0; hh < n0; ++hh) {
-            const double gg = gk[((size_t)j * n0 + hh) * n1 + hp];
-            if (gg == 0.0) continue;
-            const double* in = &C2[(dg.roff + (int64_t)hh * sk + l) * m2];
-            for (int c = 0; c < m2; ++c) out[c] += gg * in[c];
-          }
-        }
-  }
-  // the coefficients in pass 2's block order (the layout of k_mv_reduce's Wb)
-  auto pack = [&](const std::vector<double>& v, const std::vector<hdf::DegDev>& degs, int64_t blocks, int cols,
-                  int stride, std::vector<char>& dst) {
-    dst.assign((size_t)std::max<int64_t>(blocks, 1) * 16 * stride * fel, 0);
-    for (const hdf::DegDev& dg : degs)
-      for (int hh = 0; hh < dg.nh; ++hh)
-        for (int l = 0; l < dg.s; ++l) {
-          const double* row = &v[(dg.roff + (int64_t)hh * dg.s + l) * cols];
-          const int64_t blk = dg.boff + (int64_t)(hh / 16) * dg.s + l;
-          const int kb = (hh % 16) / 4, g = hh % 4;
-          for (int c = 0; c < cols; ++c) {
-            const int64_t at = (blk * (stride / 16) + c / 16) * 256 + (g * 16 + c % 16) * 4 + kb;
-            if (fel == 4) ((float*)dst.data())[at] = (float)row[c];
-            else ((double*)dst.data())[at] = row[c];
-          }
-        }
-  };
-  pack(C2, h->degs, h->n_wblocks, m2, c2s, h->adj_c2_host);
-  pack(Cs, h->adj_degs_host, h->shift_blocks, md2, css, h->adj_cs_host);
-  HIPCHK(h->adj_c2.ensure(h->adj_c2_host.size()));
-  HIPCHK(h->adj_cs.ensure(h->adj_cs_host.size()));
-  HIPCHK(hipMemcpyAsync(h->adj_c2.p, h->adj_c2_host.data(), h->adj_c2_host.size(), hipMemcpyHostToDevice, s));
-  HIPCHK(hipMemcpyAsync(h->adj_cs.p, h->adj_cs_host.data(), h->adj_cs_host.size(), hipMemcpyHostToDevice, s));
+  const bool nw = m2 <= hdf::kNwMax;
+  const int c2s = nw ? m2 : (m2 + 15) / 16 * 16, css = (md2 + 15) / 16 * 16;
+  const int64_t c2_rows = nw ? h->r : h->n_wblocks * 16;
+  HIPCHK(h->adj_c2.ensure((size_t)c2_rows * c2s * fel));
+  HIPCHK(h->adj_cs.ensure((size_t)std::max<int64_t>(h->shift_blocks, 1) * 16 * css * fel));
   HIPCHK(h->adj_kv2.ensure((size_t)h->N * m2 * fel));
   HIPCHK(h->adj_kvs.ensure((size_t)h->N * md2 * fel));
   if (!h->ev_adj[0])
     for (auto& e : h->ev_adj) HIPCHK(hipEventCreate(&e));
   HIPCHK(hipEventRecord(h->ev_adj[0], s));
   // U' [Gv | Gw] and the shifted factor times [G^(j)T Gv | G^(j)T Gw] (pass-2 kernel, one chunk)
-  HIPCHK(hdf::launch_matvec_n(h->phi.p, h->ldN, h->dq.p, h->ldN, (const hdf::DegDev*)h->degs_dev.p,
-                              (int)h->degs.size(), h->adj_c2.p, h->n_wblocks, c2s, h->adj_kv2.p, m2, h->N, m2,
-                              h->fprec, io, 0, nullptr, s));
+  HIPCHK(hdf::launch_adj_coefficients(gv, gw, gstride, m, d, (const double*)h->lam_row.p,
+                                      (const hdf::DegDev*)h->degs_dev.p, (const int32_t*)h->blk_src.p, c2_rows, c2s,
+                                      nw ? 0 : 1, h->adj_c2.p, (const hdf::DegDev*)h->adj_degs.p, Kh,
+                                      (const int32_t*)h->adj_map->row.p, (const int32_t*)h->adj_map->h.p,
+                                      (const double*)h->adj_map->v.p, h->shift_blocks, css, h->adj_cs.p, h->fprec, s));
+  if (nw)
+    HIPCHK(hdf::launch_narrow_n(h->phi.p, h->ldN, h->dq.p, h->ldN, (const hdf::DegDev*)h->degs_dev.p,
+                                (int)h->degs.size(), h->adj_c2.p, h->adj_kv2.p, m2, h->N, m2, (int)h->H, 0, nullptr,
+                                h->fprec, io, s));
+  else
+    HIPCHK(hdf::launch_matvec_n(h->phi.p, h->ldN, h->dq.p, h->ldN, (const hdf::DegDev*)h->degs_dev.p,
+                                (int)h->degs.size(), h->adj_c2.p, h->n_wblocks, c2s, h->adj_kv2.p, m2, h->N, m2,
+                                h->fprec, io, 0, nullptr, s));
   if (Kh >= 1) {
     HIPCHK(hdf::launch_matvec_n(h->phi.p, h->ldN, h->q.p, h->ldN, (const hdf::DegDev*)h->adj_degs.p, Kh, h->adj_cs.p,
                                 h->shift_blocks, css, h->adj_kvs.p, md2, h->N, md2, h->fprec, io, 0, nullptr, s));
@@ -2088,7 +2105,7 @@ hdf_status hdf_backward(hdf_handle h, const void* Wm, const void* Vm, int64_t m,
   int64_t gw_col = 0;
   if (joint) {
     const int64_t m2 = 2 * m;
-    m16 = (int)((m2 + 15) / 16 * 16);
+    m16 = narrow(h, m2) ? (int)m2 : (int)((m2 + 15) / 16 * 16);
     HIPCHK(h->bw_VW.ensure((size_t)h->N * m2 * el));
     HIPCHK(hipMemcpy2DAsync(h->bw_VW.p, m2 * el, Vm, ld * el, m * el, h->N, hipMemcpyDeviceToDevice, s));
     HIPCHK(hipMemcpy2DAsync((char*)h->bw_VW.p + m * el, m2 * el, Wm, ld * el, m * el, h->N,
@@ -2139,16 +2156,18 @@ hdf_status hdf_backward(hdf_handle h, const void* Wm, const void* Vm, int64_t m,
       }
     }
   }
-  // U^T V and U^T W on the host (binary64), one synchronisation
-  std::vector<double> gv((size_t)h->r * m16), gwbuf;
-  HIPCHK(hipMemcpyAsync(gv.data(), gv_src->p, gv.size() * 8, hipMemcpyDeviceToHost, s));
-  if (!joint) {
-    gwbuf.resize((size_t)h->r * m16);
-    HIPCHK(hipMemcpyAsync(gwbuf.data(), gw_src->p, gwbuf.size() * 8, hipMemcpyDeviceToHost, s));
-  }
-  HIPCHK(hipStreamSynchronize(s));
-  const double* gw = joint ? gv.data() + gw_col : gwbuf.data();
+  const double* gv_dev = (const double*)gv_src->p;
+  const double* gw_dev = joint ? gv_dev + gw_col : (const double*)gw_src->p;
+  // U^T V and U^T W on the host (binary64) for dF/dl, one synchronisation
   if (dlength) {
+    std::vector<double> gv((size_t)h->r * m16), gwbuf;
+    HIPCHK(hipMemcpyAsync(gv.data(), gv_src->p, gv.size() * 8, hipMemcpyDeviceToHost, s));
+    if (!joint) {
+      gwbuf.resize((size_t)h->r * m16);
+      HIPCHK(hipMemcpyAsync(gwbuf.data(), gw_src->p, gwbuf.size() * 8, hipMemcpyDeviceToHost, s));
+    }
+    HIPCHK(hipStreamSynchronize(s));
+    const double* gw = joint ? gv.data() + gw_col : gwbuf.data();
     double dl = 0.0;
     for (size_t dj = 0; dj < h->degs.size(); ++dj) {
       const hdf::DegDev& dg = h->degs[dj];
@@ -2167,7 +2186,7 @@ hdf_status hdf_backward(hdf_handle h, const void* Wm, const void* Vm, int64_t m,
     *dlength = dl;
   }
   if (dX) {
-    const hdf_status st = adjoint_dx(h, gv.data(), gw, m16, (int)m, Wm, Vm, ld, dX, lddx, s);
+    const hdf_status st = adjoint_dx(h, gv_dev, gw_dev, m16, (int)m, Wm, Vm, ld, dX, lddx, s);
     if (st != HDF_OK) return st;
   }
   return HDF_OK;

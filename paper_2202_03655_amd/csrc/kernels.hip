@@ -2213,6 +2213,81 @@ hipError_t launch_matvec_batch(const MvBatch* batch_dev, const MvBatchGrid& g, c
   return hipGetLastError();
 }
 
+// ------------------------------------------------------------------ adjoint coefficients
+// The coefficients of the adjoint's two products, from Gv = U^T V and Gw = U^T W (binary64, rank rows):
+//   C2[(k,h,l)][c]          = lambda Gv[c], then lambda Gw[c]                       (c < m each)
+//   Cs[(k,h',l)][2 m j + c] = sum_h G_k^(j)[h][h'] C2[(k,h,l)][c]                   (h' of degree k - 1)
+// written where pass 2 reads them, in block order (or C2 in rank order for the narrow pass).  The maps
+// G_k are sparse (a derivative of a harmonic touches a few of the degree below): rows (k, j, h') of
+// `map`, entry e the harmonic map_h[e] with the value map_v[e].  On the host the dense sums and the
+// uploads were most of the 2.3 ms that hdf_backward took to return (2e5 points, d = 4, degrees to 13); 0.3 so.
+__device__ __forceinline__ int64_t block_at(int64_t row, int c, int cpl) {
+  const int hh = (int)(row & 15);
+  return ((row >> 4) * cpl + (c >> 4)) * 256 + ((hh & 3) * 16 + (c & 15)) * 4 + (hh >> 2);
+}
+
+template <typename T>
+__global__ void __launch_bounds__(256) k_adj_c2(const double* __restrict__ gv, const double* __restrict__ gw,
+                                                int64_t gstride, int m, const double* __restrict__ lam,
+                                                const int32_t* __restrict__ src, int64_t rows, int cols,
+                                                int block_order, T* __restrict__ out) {
+  const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (e >= rows * cols) return;
+  const int64_t row = e / cols;
+  const int c = (int)(e - row * cols);
+  const int64_t sr = block_order ? src[row] : row;
+  double v = 0.0;
+  if (sr >= 0 && c < 2 * m) v = lam[sr] * (c < m ? gv[sr * gstride + c] : gw[sr * gstride + c - m]);
+  out[block_order ? block_at(row, c, cols >> 4) : e] = (T)v;
+}
+
+template <typename T>
+__global__ void __launch_bounds__(256) k_adj_cs(const double* __restrict__ gv, const double* __restrict__ gw,
+                                                int64_t gstride, int m, int d, const double* __restrict__ lam,
+                                                const DegDev* __restrict__ degs, const DegDev* __restrict__ shifted,
+                                                int n_shifted, const int32_t* __restrict__ map,
+                                                const int32_t* __restrict__ map_h, const double* __restrict__ map_v,
+                                                int64_t rows, int cols, T* __restrict__ out) {
+  const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (e >= rows * cols) return;
+  const int64_t row = e / cols, blk = row >> 4;
+  const int col = (int)(e - row * cols), j = col / (2 * m), c = col - j * 2 * m;
+  int di = 0, at = 0;                              // degree k = di + 1; at: first map row of the degree
+  while (di + 1 < n_shifted && shifted[di + 1].boff <= blk) at += d * shifted[di++].nh;
+  const DegDev sh = shifted[di], dg = degs[di + 1];
+  const int rel = (int)(blk - sh.boff), b = rel / sh.s, l = rel - b * sh.s, hp = 16 * b + (int)(row & 15);
+  double v = 0.0;
+  if (j < d && hp < sh.nh) {
+    const double* g = c < m ? gv + c : gw + (c - m);
+    const int mr = at + j * sh.nh + hp;
+    for (int t = map[mr]; t < map[mr + 1]; ++t) {
+      const int64_t rr = dg.roff + (int64_t)map_h[t] * dg.s + l;
+      v = fma(map_v[t], lam[rr] * g[rr * gstride], v);
+    }
+  }
+  out[block_at(row, col, cols >> 4)] = (T)v;
+}
+
+hipError_t launch_adj_coefficients(const double* gv, const double* gw, int64_t gstride, int m, int d,
+                                   const double* lam, const DegDev* degs, const int32_t* src, int64_t c2_rows,
+                                   int c2_cols, int c2_block_order, void* c2, const DegDev* shifted, int n_shifted,
+                                   const int32_t* map, const int32_t* map_h, const double* map_v,
+                                   int64_t shift_blocks, int cs_cols, void* cs, int prec, hipStream_t s) {
+  const unsigned b2 = (unsigned)((c2_rows * c2_cols + 255) / 256);
+  const unsigned bs = (unsigned)((shift_blocks * 16 * cs_cols + 255) / 256);
+#define ADJ_COEF(T)                                                                                            \
+  do {                                                                                                         \
+    k_adj_c2<T><<<b2, 256, 0, s>>>(gv, gw, gstride, m, lam, src, c2_rows, c2_cols, c2_block_order, (T*)c2);    \
+    if (n_shifted > 0)                                                                                         \
+      k_adj_cs<T><<<bs, 256, 0, s>>>(gv, gw, gstride, m, d, lam, degs, shifted, n_shifted, map, map_h, map_v,  \
+                                     shift_blocks * 16, cs_cols, (T*)cs);                                      \
+  } while (0)
+  if (prec == 1) ADJ_COEF(float);
+  else ADJ_COEF(double);
+#undef ADJ_COEF
+  return hipGetLastError();
+}
+
 int narrow_items(const DegDev* degs, int n_deg, int prec, int m) {
   int items = 0;
   for (int di = 0; di < n_deg; ++di)

@@ -201,6 +201,14 @@ struct MvBatchGrid {
 hipError_t launch_matvec_batch(const MvBatch* batch_dev, const MvBatchGrid& g, const double* v, double* out,
                                hipStream_t s);
 
+// Coefficients of the adjoint's products: c2 (c2_rows x c2_cols; blocks of pass 2 in block order, or
+// rank rows), cs (shift_blocks blocks of cs_cols columns, block order; n_shifted = 0: none).
+hipError_t launch_adj_coefficients(const double* gv, const double* gw, int64_t gstride, int m, int d,
+                                   const double* lam, const DegDev* degs, const int32_t* src, int64_t c2_rows,
+                                   int c2_cols, int c2_block_order, void* c2, const DegDev* shifted, int n_shifted,
+                                   const int32_t* map, const int32_t* map_h, const double* map_v,
+                                   int64_t shift_blocks, int cs_cols, void* cs, int prec, hipStream_t s);
+
 // Adjoint by contractions (see hdf_backward).  launch_radial evaluates S
 // Chebyshev series of t(rho^2) at every point: out[row][i] = scale * sum_a
 // coef[q_off[row] + a] T_a(t_i), a < q_len[row] (rows padded: the launch
