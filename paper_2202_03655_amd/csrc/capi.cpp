@@ -1047,7 +1047,9 @@ hdf_status hdf_build_ex(const void* points, int dtype, int64_t n, int d, int64_t
   double t0 = now_ms();
   HIPCHK(f->x_soa.ensure((size_t)d * f->ldN * in_elem));
   HIPCHK(f->geo_dev.ensure(sizeof(hdf::GeoDev)));
-  HIPCHK(f->part.ensure((size_t)hdf::kPrepBlocks * 32 * sizeof(double)));
+  // the Gram pass's records at the largest degree: a buffer that grows would wait for the device
+  HIPCHK(f->part.ensure(std::max((size_t)hdf::kPrepBlocks * 32, (size_t)hdf::gram_blocks(n) * 32 * 64) * sizeof(double) +
+                        4096));
   HIPCHK(hdf::launch_prep(points, dtype, n, d, ld, f->x_soa.p, f->ldN, kernel, lengthscale,
                           (double*)f->part.p, (hdf::GeoDev*)f->geo_dev.p, s));
   HIPCHK(hipMemcpyAsync(&f->geo, f->geo_dev.p, sizeof(hdf::GeoDev), hipMemcpyDeviceToHost, s));
@@ -1191,14 +1193,14 @@ hdf_status hdf_build_ex(const void* points, int dtype, int64_t n, int d, int64_t
     std::vector<double> g2h(refine.size() * 1024);
     HIPCHK(hipMemcpyAsync(g2h.data(), g2.p, g2h.size() * 8, hipMemcpyDeviceToHost, s));
     HIPCHK(hipStreamSynchronize(s));
-    for (size_t ri = 0; ri < refine.size(); ++ri) {
+    hdf::parallel_for((int)refine.size(), [&](int ri) {
       const int k = refine[ri];
       const int L = K - k + 1;
       std::vector<double> G2((size_t)L * L);
       for (int aa = 0; aa < L; ++aa)
-        for (int bb = 0; bb < L; ++bb) G2[(size_t)aa * L + bb] = g2h[ri * 1024 + aa * 32 + bb];
+        for (int bb = 0; bb < L; ++bb) G2[(size_t)aa * L + bb] = g2h[(size_t)ri * 1024 + aa * 32 + bb];
       hdf::compress_degree_refined(k, L, G2.data(), pcs[k], f->cores[k].data(), f->tau, 1e-14, f->deg[k]);
-    }
+    });
   }
   f->tau0 = f->tau;
   if (rule == HDF_RULE_SAMPLED) {
@@ -1336,7 +1338,8 @@ hdf_status hdf_build_cross(const void* x, int64_t nx, int64_t ldx, const void* y
     for (double v : pc.lam1c) { gmax = std::max(gmax, v); gmin = std::min(gmin, v); }
     return gmax / gmin;
   };
-  for (int k = 0; k <= K; ++k) {
+  std::vector<char> needs_refine(K + 1, 0);
+  hdf::parallel_for(K + 1, [&](int k) {
     const int L = K - k + 1;
     std::vector<double> Gx, Gy;
     gram_of(mom.data(), k, L, Gx);
@@ -1350,7 +1353,10 @@ hdf_status hdf_build_cross(const void* x, int64_t nx, int64_t ldx, const void* y
     double smax = 0.0;
     for (double v : dc[k].sig) smax = std::max(smax, v);
     const double est = eta1 * std::max(cond_of(pcx[k]), cond_of(pcy[k])) * (smax > 0 ? f->tau / smax : 1.0);
-    if (est > target) refine.push_back(k);
+    needs_refine[k] = est > target;
+  });
+  for (int k = 0; k <= K; ++k) {
+    if (needs_refine[k]) refine.push_back(k);
     t1_off[k] = (int32_t)t1x.size();
     t1x.insert(t1x.end(), pcx[k].T1.begin(), pcx[k].T1.end());
     t1y.insert(t1y.end(), pcy[k].T1.begin(), pcy[k].T1.end());
@@ -1380,20 +1386,20 @@ hdf_status hdf_build_cross(const void* x, int64_t nx, int64_t ldx, const void* y
     std::vector<double> g2h(2 * refine.size() * 1024);
     HIPCHK(hipMemcpyAsync(g2h.data(), g2.p, g2h.size() * 8, hipMemcpyDeviceToHost, s));
     HIPCHK(hipStreamSynchronize(s));
-    for (size_t ri = 0; ri < refine.size(); ++ri) {
+    hdf::parallel_for((int)refine.size(), [&](int ri) {
       const int k = refine[ri];
       const int L = K - k + 1;
       std::vector<double> G2x((size_t)L * L), G2y((size_t)L * L);
       for (int aa = 0; aa < L; ++aa)
         for (int bb = 0; bb < L; ++bb) {
-          G2x[(size_t)aa * L + bb] = g2h[ri * 1024 + aa * 32 + bb];
-          G2y[(size_t)aa * L + bb] = g2h[(refine.size() + ri) * 1024 + aa * 32 + bb];
+          G2x[(size_t)aa * L + bb] = g2h[(size_t)ri * 1024 + aa * 32 + bb];
+          G2y[(size_t)aa * L + bb] = g2h[(refine.size() + (size_t)ri) * 1024 + aa * 32 + bb];
         }
       hdf::SqrtFactor fx, fy;
       hdf::sqrt_factor_refined(L, G2x.data(), pcx[k], 1e-14, fx);
       hdf::sqrt_factor_refined(L, G2y.data(), pcy[k], 1e-14, fy);
       hdf::compress_degree_cross(k, L, fx, fy, f->cores[k].data(), f->tau, dc[k]);
-    }
+    });
   }
   for (int k = 0; k <= K; ++k) {
     hdf::DegreeFactor& dx = f->deg[k];

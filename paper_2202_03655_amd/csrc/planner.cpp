@@ -65,6 +65,8 @@ double kernel_dl(int kind, double r, double l) {
 
 // ---------------------------------------------------------------- host pool
 namespace {
+thread_local bool in_pool = false;   // a task of the pool is running on this thread
+
 class Pool {
  public:
   explicit Pool(int n_workers) : pid_(getpid()) {
@@ -102,7 +104,9 @@ class Pool {
 
  private:
   void work(const std::function<void(int)>& fn, int n) {
+    in_pool = true;
     for (int i = next_.fetch_add(1); i < n; i = next_.fetch_add(1)) fn(i);
+    in_pool = false;
   }
   void loop() {
     uint64_t seen = 0;
@@ -132,7 +136,7 @@ class Pool {
 }  // namespace
 
 void parallel_for(int n, const std::function<void(int)>& fn) {
-  if (n <= 1) {
+  if (n <= 1 || in_pool) {             // a task's own loops run on its thread
     for (int i = 0; i < n; ++i) fn(i);
     return;
   }
