@@ -223,7 +223,6 @@ struct hdf_factor {
   std::vector<int32_t> index_table;               // H x (d-1)
   int64_t H = 0, S = 0, r = 0;
   int64_t n_wblocks = 0;                          // blocks of pass 2's block-ordered copy of D W
-  int max_s = 0;
   int n_refined = 0;                              // degrees refined by the second Gram pass
   double t_prep = 0, t_plan = 0, t_gram = 0, t_compress = 0, t_finish = 0, t_build = -1;
   hipEvent_t ev_b0 = nullptr, ev_b1 = nullptr;
@@ -232,12 +231,11 @@ struct hdf_factor {
   bool mv_timed = false, adj_timed = false;
   bool time_products = true;                      // HIP events around the product's kernels
   // device storage
-  DevBuf x_soa, geo_dev, part, phi, q, tiles_dev, moments;
+  DevBuf x_soa, geo_dev, part, phi, q, moments;
   // tables of the factor evaluation (in build_tabs) and of the products (in prod_tabs), each
   // set uploaded in one copy
   DevBuf build_tabs, prod_tabs;
   DevView col_of, chain, q_len, q_off, q_coef, leaves, degs_dev, lam_row, blk_src, tile_tabs, degs_by_k;
-  int n_tiles = 0, tiles_cpl = 0;                 // pass-1 work items for cpl = m16/16
   // tile-major pass 1 (m16 <= 64): wave items and their workgroup groups for each cpl = m16 / 16
   // in 1..4, built with the factor; tile_tabs holds all wave items, then all groups, then the
   // rank-row table
@@ -247,7 +245,6 @@ struct hdf_factor {
   // host copies of uploaded build tables: they outlive their asynchronous uploads
   std::vector<std::vector<char>> host_keep;
   // host copies of the pass-1 tables: they outlive their asynchronous uploads
-  std::vector<hdf::TileDev> tiles_host;
   // matvec / adjoint workspace
   DevBuf ws_part, ws_Wd, ws_Wb, ws_n, bw_GV, bw_GW, bw_VW;
   DevBuf cphi, cq;                                // matrix-free chunk scratch
@@ -727,7 +724,6 @@ static hdf_status finish_build(hdf_factor* f, double t0, hipStream_t s) {
     hoff += nh;
     qoff += df.s;
     roff += nh * df.s;
-    f->max_s = std::max(f->max_s, df.s);
   }
   f->H = hoff; f->S = qoff; f->r = roff; f->n_wblocks = boff;
   f->t_compress = now_ms() - t0;
@@ -1457,8 +1453,6 @@ static hdf_status reduce_splits(hdf_handle h, int n_splits, int m16, const PassO
   return HDF_OK;
 }
 
-// Pass 1 of a matrix-free factor: per chunk, evaluate the factor, then contract it into its own range
-// of split partials; one fixed-order reduction over all chunks' partials gives W.
 // Device tables of the tile-major pass 1 for cpl = m16 / 16 (1..4), built with the factor.
 static const hdf::MvtWave* tile_waves(hdf_handle h, int cpl) {
   return (const hdf::MvtWave*)h->tile_tabs.p + h->tw_off[cpl];
@@ -1483,17 +1477,28 @@ static void tile_splits(int64_t n, int n_groups, size_t per_split, int* n_splits
   *n_splits = (int)((n + len - 1) / len);
 }
 
+// Pass 1 over n points of a factor into split partials of m16 columns: the whole slabs of 64 columns
+// in one launch (few splits of few groups leave the chip idle: 250,007 points x 256 columns of rank
+// 1413: the product takes 4.4 ms, 5.5 with a launch each), the rest in another.
+static hdf_status launch_pass1(hdf_handle h, const void* phi, const void* q, int64_t ld, const void* V, int64_t ldv,
+                               int64_t n, int m, int m16, int n_splits, int64_t split_len, double* part,
+                               hipStream_t s) {
+  for (int c0 = 0, n_slabs; c0 < m16; c0 += 64 * n_slabs) {
+    const int w16 = std::min(64, m16 - c0), cpl = w16 / 16;
+    n_slabs = std::max(1, (m16 - c0) / 64);
+    HIPCHK(hdf::launch_matvec_t_tile(phi, ld, q, ld, tile_waves(h, cpl), tile_rank_rows(h), tile_groups(h, cpl),
+                                     h->n_tgroups[cpl], n_splits, split_len, (const char*)V + c0 * h->ioel(), ldv, n,
+                                     m - c0, w16, n_slabs, m16, h->r, part + c0, h->fprec, h->dtype, s));
+  }
+  return HDF_OK;
+}
+
 // Pass 1 of a matrix-free factor: per chunk, evaluate the factor, then contract it into its own range
 // of split partials; one fixed-order reduction over all chunks' partials gives W.
 static hdf_status pass1_chunked(hdf_handle h, const void* V, int64_t m, int64_t ldv, int m16, const PassOut& out,
                                 hipStream_t s, bool timed) {
-  const size_t el = h->felem();
-  const int cpl = m16 / 16;
   const size_t per_split = (size_t)h->r * m16 * sizeof(double);
-  // work items and groups as for a stored factor of chunk points
-  hdf_status st = pass1(h, 2, V, m, ldv, m16, out, s, false);   // side 2: tables only
-  if (st != HDF_OK) return st;
-  const bool tile = m16 <= 64;
+  hdf_status st = HDF_OK;
   std::vector<int> splits;
   std::vector<int64_t> slen;
   int total = 0;
@@ -1501,13 +1506,19 @@ static hdf_status pass1_chunked(hdf_handle h, const void* V, int64_t m, int64_t 
     const int64_t nc = std::min(h->chunk, h->N - c0);
     int ns;
     int64_t len;
-    if (tile) {
-      tile_splits(nc, h->n_tgroups[cpl], per_split, &ns, &len);
+    if (m16 <= 64) {
+      tile_splits(nc, h->n_tgroups[m16 / 16], per_split, &ns, &len);
     } else {
-      ns = (int)std::max<int64_t>(1, 16384 / std::max<int64_t>(1, (int64_t)h->n_tiles));
+      // about 16k units of 32 harmonics by four (binary32) or two column tiles of one degree: with the bound below,
+      // the sizes that are accepted
+      int64_t units = 0;
+      const int col_tiles = h->fprec == 1 ? 4 : 2;
+      for (const hdf::DegDev& dg : h->degs)
+        units += (int64_t)((dg.nh + 31) / 32) * ((dg.s * (m16 / 16) + col_tiles - 1) / col_tiles);
+      ns = (int)std::max<int64_t>(1, 16384 / std::max<int64_t>(1, units));
       ns = (int)std::min<int64_t>(ns, (nc + 1023) / 1024);
       ns = std::max(ns, 1);
-      len = ((nc + ns - 1) / ns + 15) / 16 * 16;
+      len = ((nc + ns - 1) / ns + 127) / 128 * 128;
       ns = (int)((nc + len - 1) / len);
     }
     splits.push_back(ns);
@@ -1530,15 +1541,8 @@ static hdf_status pass1_chunked(hdf_handle h, const void* V, int64_t m, int64_t 
     if (st != HDF_OK) return st;
     const void* Vc = (const char*)V + c0 * ldv * h->ioel();
     double* part = (double*)h->ws_part.p + (size_t)slot * h->r * m16;
-    if (tile)
-      HIPCHK(hdf::launch_matvec_t_tile(h->cphi.p, h->ldC, h->cq.p, h->ldC, tile_waves(h, cpl), tile_rank_rows(h),
-                                       tile_groups(h, cpl), h->n_tgroups[cpl], splits[ci], slen[ci], Vc, ldv, nc,
-                                       (int)m, m16, h->r, part,
-                                       h->fprec, h->dtype, s));
-    else
-      HIPCHK(hdf::launch_matvec_t(h->cphi.p, h->ldC, h->cq.p, h->ldC, (const hdf::DegDev*)h->degs_dev.p,
-                                  (const hdf::TileDev*)h->tiles_dev.p, h->n_tiles, h->max_s * cpl, Vc, ldv, nc,
-                                  (int)m, m16, splits[ci], slen[ci], h->r, part, h->fprec, h->dtype, s));
+    st = launch_pass1(h, h->cphi.p, h->cq.p, h->ldC, Vc, ldv, nc, (int)m, m16, splits[ci], slen[ci], part, s);
+    if (st != HDF_OK) return st;
     slot += splits[ci];
   }
   if (timed) HIPCHK(hipEventRecord(h->ev_mv[1], s));
@@ -1668,85 +1672,30 @@ static hdf_status pass2_narrow(hdf_handle h, int64_t m, void* KV, int64_t ldkv, 
   return HDF_OK;
 }
 
-// side 2 (matrix-free factors): build the work-item tables only.
 static hdf_status pass1(hdf_handle h, int side, const void* V, int64_t m, int64_t ldv, int m16, const PassOut& out,
                         hipStream_t s, bool timed) {
-  if (h->storage == HDF_STORE_NONE && side != 2)
+  if (h->storage == HDF_STORE_NONE)
     return h->mf_fused ? pass1_fused(h, V, m, ldv, m16, out, s, timed)
                        : pass1_chunked(h, V, m, ldv, m16, out, s, timed);
   if (narrow(h, m)) return pass1_narrow(h, side, V, m, ldv, m16, out, s, timed);
-  const int64_t n = side == 1 ? h->N2 : (side == 2 ? h->chunk : h->N);
-  const void* phi = side == 1 ? h->phi2.p : h->phi.p;
-  const void* qv = side == 1 ? h->q2.p : h->q.p;
-  const int64_t ldn = side == 1 ? h->ldN2 : h->ldN;
-  const size_t el = h->felem();
-  const int cpl = m16 / 16;
-  const int max_nct = h->max_s * cpl;
-  if (h->tiles_cpl != cpl) {
-    // work items: (degree, row block, column slice), no empty slices
-    std::vector<hdf::TileDev>& tiles = h->tiles_host;
-    tiles.clear();
-    const int nct = hdf::matvec_col_tiles(h->fprec);
-    for (size_t di = 0; di < h->degs.size(); ++di)
-      for (int h0 = 0; h0 < h->degs[di].nh; h0 += hdf::matvec_row_block())
-        for (int ct0 = 0; ct0 < h->degs[di].s * cpl; ct0 += nct)
-          tiles.push_back(hdf::TileDev{(int32_t)di, h0, ct0, 0});
-    HIPCHK(h->tiles_dev.ensure(tiles.size() * sizeof(hdf::TileDev)));
-    HIPCHK(hipMemcpyAsync(h->tiles_dev.p, tiles.data(), tiles.size() * sizeof(hdf::TileDev),
-                          hipMemcpyHostToDevice, s));
-    h->n_tiles = (int)tiles.size();
-    h->tiles_cpl = cpl;
-  }
+  const int64_t n = side == 1 ? h->N2 : h->N;
   const size_t per_split = (size_t)h->r * m16 * sizeof(double);
-  if (side == 2 && m16 > 64) return HDF_OK;
-  if (m16 <= 64) {
-    // tile-major variant: the wave items and groups of this cpl were built with the factor
-    if (side == 2) return HDF_OK;
-    int n_splits;
-    int64_t split_len;
-    tile_splits(n, h->n_tgroups[cpl], per_split, &n_splits, &split_len);
-    HIPCHK(h->ws_part.ensure(per_split * n_splits));
-    if (timed) {
-      if (!h->ev_mv[0])
-        for (auto& e : h->ev_mv) HIPCHK(hipEventCreate(&e));
-      HIPCHK(hipEventRecord(h->ev_mv[0], s));
-    }
-    HIPCHK(hdf::launch_matvec_t_tile(phi, ldn, qv, ldn, tile_waves(h, cpl), tile_rank_rows(h), tile_groups(h, cpl),
-                                     h->n_tgroups[cpl],
-                                     n_splits, split_len, V, ldv, n, (int)m, m16, h->r, (double*)h->ws_part.p,
-                                     h->fprec, h->dtype, s));
-    if (timed) HIPCHK(hipEventRecord(h->ev_mv[1], s));
-    {
-    const hdf_status rst = reduce_splits(h, n_splits, m16, out, s);
-    if (rst != HDF_OK) return rst;
-  }
-    if (timed) HIPCHK(hipEventRecord(h->ev_mv[2], s));
-    return HDF_OK;
-  }
-  if (side == 2) return HDF_OK;
-  // about 16k wavefronts in pass 1, partial records capped at ~96 MB
-  int n_splits = (int)std::max<int64_t>(1, 16384 / std::max<int64_t>(1, (int64_t)h->n_tiles));
-  n_splits = (int)std::min<int64_t>(n_splits, std::max<int64_t>(1, (int64_t)(96e6 / (double)per_split)));
-  n_splits = (int)std::min<int64_t>(n_splits, (n + 1023) / 1024);
-  n_splits = std::max(n_splits, 1);
-  int64_t split_len = (n + n_splits - 1) / n_splits;
-  split_len = (split_len + 15) / 16 * 16;
-  n_splits = (int)((n + split_len - 1) / split_len);
+  int n_splits;
+  int64_t split_len;
+  tile_splits(n, h->n_tgroups[std::min(4, m16 / 16)], per_split, &n_splits, &split_len);
   HIPCHK(h->ws_part.ensure(per_split * n_splits));
   if (timed) {
     if (!h->ev_mv[0])
       for (auto& e : h->ev_mv) HIPCHK(hipEventCreate(&e));
     HIPCHK(hipEventRecord(h->ev_mv[0], s));
   }
-  HIPCHK(hdf::launch_matvec_t(phi, ldn, qv, ldn, (const hdf::DegDev*)h->degs_dev.p,
-                              (const hdf::TileDev*)h->tiles_dev.p, h->n_tiles, max_nct, V, ldv, n,
-                              (int)m, m16, n_splits, split_len, h->r, (double*)h->ws_part.p,
-                              h->fprec, h->dtype, s));
+  hdf_status st = launch_pass1(h, side == 1 ? h->phi2.p : h->phi.p, side == 1 ? h->q2.p : h->q.p,
+                               side == 1 ? h->ldN2 : h->ldN, V, ldv, n, (int)m, m16, n_splits, split_len,
+                               (double*)h->ws_part.p, s);
+  if (st != HDF_OK) return st;
   if (timed) HIPCHK(hipEventRecord(h->ev_mv[1], s));
-  {
-    const hdf_status rst = reduce_splits(h, n_splits, m16, out, s);
-    if (rst != HDF_OK) return rst;
-  }
+  st = reduce_splits(h, n_splits, m16, out, s);
+  if (st != HDF_OK) return st;
   if (timed) HIPCHK(hipEventRecord(h->ev_mv[2], s));
   return HDF_OK;
 }
@@ -1900,7 +1849,7 @@ hdf_status hdf_matvec_noalloc(hdf_handle h, const void* V, int64_t m, int64_t ld
   double* part = (double*)((char*)base + wb_bytes);
   HIPCHK(hdf::launch_matvec_t_tile(side ? h->phi2.p : h->phi.p, side ? h->ldN2 : h->ldN, side ? h->q2.p : h->q.p,
                                    side ? h->ldN2 : h->ldN, tile_waves(h, cpl), tile_rank_rows(h), tile_groups(h, cpl),
-                                   h->n_tgroups[cpl], n_splits, split_len, V, ldv, n1, (int)m, m16, h->r, part,
+                                   h->n_tgroups[cpl], n_splits, split_len, V, ldv, n1, (int)m, m16, 1, m16, h->r, part,
                                    h->fprec, h->dtype, s));
   HIPCHK(hdf::launch_matvec_reduce(part, n_splits, h->r, m16, (const int32_t*)h->blk_src.p, h->n_wblocks,
                                    (const double*)h->lam_row.p, nullptr, nullptr, Wb, h->fprec, s));

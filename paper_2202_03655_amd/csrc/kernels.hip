@@ -1090,145 +1090,6 @@ hipError_t launch_adj_combine(const void* x_soa, int dtype, int64_t ldx, int64_t
   return hipGetLastError();
 }
 
-// ------------------------------------------------------------------ matvec
-// Vector load of 8 consecutive values of a harmonic / radial row starting at
-// p (a multiple of 8, p < N + 56).  Rows are padded by 64 points past N, so
-// the 16-byte loads never leave the row; values at or past `end` (or of an
-// invalid row) are replaced by zero with selects, never by branches, so all
-// loads of an iteration issue back to back.
-template <typename T>
-__device__ __forceinline__ void load8(const T* __restrict__ row, int64_t p, int64_t end, bool ok, T (&a)[8]) {
-  T v[8];
-  if constexpr (sizeof(T) == 4) {
-    const floatx4 v0 = *reinterpret_cast<const floatx4*>(row + p);
-    const floatx4 v1 = *reinterpret_cast<const floatx4*>(row + p + 4);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) { v[e] = v0[e]; v[4 + e] = v1[e]; }
-  } else {
-#pragma unroll
-    for (int h = 0; h < 4; ++h) {
-      const doublex2 w = *reinterpret_cast<const doublex2*>(row + p + 2 * h);
-      v[2 * h] = w[0];
-      v[2 * h + 1] = w[1];
-    }
-  }
-#pragma unroll
-  for (int e = 0; e < 8; ++e) a[e] = (ok && p + e < end) ? v[e] : (T)0;
-}
-
-// Pass 1, W = U^T V.  Per degree k this is the product Phi_k (Q_k o V)
-// (Khatri-Rao: column (k,h,l) of U is phi_h * q_{k,l}).  One wavefront owns
-// a block of 32 harmonics of one degree (two 16-row MFMA tiles, so every B
-// operand q_{k,l}(i) V[i][c] is reused twice) and a contiguous range of
-// points; output columns j = l * m16 + c are produced NCT 16-wide tiles at a
-// time.  The reduction index (points) is assigned so that lane group g reads
-// 8 consecutive points of each harmonic row (two 16-byte loads per row).
-constexpr int kMvtRowTiles = 2;
-
-template <typename T, int NCT, typename TV>
-__global__ void __launch_bounds__(64) k_mv_t(const T* __restrict__ phi, int64_t ld_phi,
-                                              const T* __restrict__ q, int64_t ld_q,
-                                              const DegDev* __restrict__ degs,
-                                              const TileDev* __restrict__ tiles,
-                                              const TV* __restrict__ V, int64_t ldv, int64_t n,
-                                              int m, int m16, int64_t split_len, int64_t rank,
-                                              double* __restrict__ part) {
-  typedef typename Mfma<T>::V Acc;
-  const TileDev tile = tiles[blockIdx.x];
-  const DegDev dg = degs[tile.deg];
-  const int split = blockIdx.y;
-  const int cpl = m16 / 16;                      // column tiles per radial function
-  const int nct_all = dg.s * cpl;
-  const int ct0 = tile.ct0;
-  const int lane = threadIdx.x, li = lane & 15, g = lane >> 4;
-  const T* prow[kMvtRowTiles];
-  bool rowv[kMvtRowTiles];
-#pragma unroll
-  for (int rt = 0; rt < kMvtRowTiles; ++rt) {
-    const int row = tile.h0 + rt * 16 + li;
-    rowv[rt] = row < dg.nh;
-    prow[rt] = phi + (int64_t)(dg.hoff + (rowv[rt] ? row : 0)) * ld_phi;
-  }
-  const T* qrow[NCT];
-  int cc[NCT];
-  bool cv[NCT];
-#pragma unroll
-  for (int ct = 0; ct < NCT; ++ct) {
-    const int tix = ct0 + ct;
-    const int l = tix / cpl;
-    cc[ct] = (tix % cpl) * 16 + li;
-    cv[ct] = (tix < nct_all) && (cc[ct] < m);
-    qrow[ct] = q + (int64_t)(dg.qoff + (tix < nct_all ? l : 0)) * ld_q;
-  }
-  Acc acc[kMvtRowTiles][NCT];
-#pragma unroll
-  for (int rt = 0; rt < kMvtRowTiles; ++rt)
-#pragma unroll
-    for (int ct = 0; ct < NCT; ++ct) acc[rt][ct] = Acc{0, 0, 0, 0};
-  const int64_t p_begin = (int64_t)split * split_len;
-  const int64_t p_end = (p_begin + split_len < n) ? p_begin + split_len : n;
-  // software pipeline: the Phi tiles of the next 32 points are loaded while
-  // the MFMAs of the current ones run
-  T a_nxt[kMvtRowTiles][8];
-#pragma unroll
-  for (int rt = 0; rt < kMvtRowTiles; ++rt) load8(prow[rt], p_begin + 8 * g, p_end, rowv[rt], a_nxt[rt]);
-  for (int64_t p = p_begin; p < p_end; p += 32) {
-    const int64_t pb = p + 8 * g;
-    T a[kMvtRowTiles][8];
-#pragma unroll
-    for (int rt = 0; rt < kMvtRowTiles; ++rt)
-#pragma unroll
-      for (int e = 0; e < 8; ++e) a[rt][e] = a_nxt[rt][e];
-    if (p + 32 < p_end) {
-#pragma unroll
-      for (int rt = 0; rt < kMvtRowTiles; ++rt) load8(prow[rt], pb + 32, p_end, rowv[rt], a_nxt[rt]);
-    }
-    // B operands: unconditional in-bounds loads (clamped point / column),
-    // invalid entries zeroed by selects
-#pragma unroll
-    for (int t = 0; t < 8; ++t) {
-      const int64_t pt = pb + t;
-      const bool pv = pt < p_end;
-      const int64_t ptc = pv ? pt : p_begin;
-      const TV* vrow = V + ptc * ldv;
-      T b[NCT];
-      // the clamped indices address valid (finite) data, so validity is
-      // applied as a 0/1 factor; a select would be turned back into a branch
-      const T pmask = pv ? (T)1 : (T)0;
-      if (cpl == 1) {
-        const T vv = (T)vrow[li < m ? li : 0] * (li < m ? pmask : (T)0);
-#pragma unroll
-        for (int ct = 0; ct < NCT; ++ct) b[ct] = qrow[ct][ptc] * vv;
-      } else {
-#pragma unroll
-        for (int ct = 0; ct < NCT; ++ct)
-          b[ct] = qrow[ct][ptc] * (T)vrow[cc[ct] < m ? cc[ct] : 0] * (cv[ct] ? pmask : (T)0);
-      }
-#pragma unroll
-      for (int ct = 0; ct < NCT; ++ct) {
-        if (ct0 + ct >= nct_all) break;          // uniform: live column tiles only
-#pragma unroll
-        for (int rt = 0; rt < kMvtRowTiles; ++rt) acc[rt][ct] = Mfma<T>::run(a[rt][t], b[ct], acc[rt][ct]);
-      }
-    }
-  }
-  double* out = part + (int64_t)split * rank * m16;
-#pragma unroll
-  for (int ct = 0; ct < NCT; ++ct) {
-    const int tix = ct0 + ct;
-    if (tix >= nct_all) continue;
-    const int l = tix / cpl;
-    const int c = (tix % cpl) * 16 + li;
-#pragma unroll
-    for (int rt = 0; rt < kMvtRowTiles; ++rt)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int h = tile.h0 + rt * 16 + Mfma<T>::row(g, e);
-        if (h < dg.nh) out[(int64_t)(dg.roff + h * dg.s + l) * m16 + c] = (double)acc[rt][ct][e];
-      }
-  }
-}
-
 // Pass 1, tile-major.  Per degree k, W_k = Phi_k (Q_k o V): every wave item
 // owns one 16-row tile of Phi_k and up to eight accumulator tiles (radial
 // function l, column tile ct), so one pair of 16-byte loads of the tile's
@@ -1245,6 +1106,11 @@ __global__ void __launch_bounds__(64) k_mv_t(const T* __restrict__ phi, int64_t 
 // unit, Phi and Q rows are padded by at least 63 points past n (zeros), V rows
 // are clamped to n - 1 and the values of points past the split multiplied by
 // zero.
+// More than 64 columns run in slabs of 64 (blockIdx.y) into their columns of rows of mo entries: the
+// staged V^T of 64 columns is what LDS and the accumulators take, and a slab is bound by the matrix
+// cores, so reading the tile again costs nothing.  Products of more than 64 columns with the
+// per-column-tile kernel before and now: 1e6 points x 168 18.9 and 12.3 ms, 100,003 x 128 binary64 5.1 and
+// 3.5, 44,599 x 80 0.31 and 0.18, 9,973 x 100 0.21 and 0.09.
 // Prefetch depth (chunks of the tile in flight) and occupancy per type and column tiles, chosen so
 // that the registers fit without spills: binary32 with one column tile 4 chunks deep at four
 // wavefronts per SIMD (<= 128 registers), otherwise 2 deep (binary32: four wavefronts, three with
@@ -1272,7 +1138,7 @@ __device__ __forceinline__ void mvt_tile(int b, const T* __restrict__ phi, int64
                                          const T* __restrict__ q, int64_t ld_q, const MvtWave* __restrict__ waves,
                                          const MvtRankRow* __restrict__ rrows, const MvtGroup* __restrict__ groups,
                                          int n_groups, int n_splits, int64_t split_len, const TV* __restrict__ V,
-                                         int64_t ldv, int64_t n, int m, int m16, int64_t rank,
+                                         int64_t ldv, int64_t n, int m, int m16, int mo, int64_t rank,
                                          double* __restrict__ part) {
   typedef typename Mfma<T>::V Acc;
   constexpr int PF = MvtPF<T, NCT>::value;
@@ -1466,7 +1332,7 @@ __device__ __forceinline__ void mvt_tile(int b, const T* __restrict__ phi, int64
     }
   }
   if (!active) return;
-  double* out = part + (int64_t)split * rank * m16;
+  double* out = part + (int64_t)split * rank * mo;
   if (rank_item) {
 #pragma unroll
     for (int ct = 0; ct < NCT; ++ct) {
@@ -1475,7 +1341,7 @@ __device__ __forceinline__ void mvt_tile(int b, const T* __restrict__ phi, int64
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           const int r = Mfma<T>::row(g, e);
-          if (r < wi.nr) out[(int64_t)rrows[wi.row0 + r].out * m16 + c] = (double)acc[0][ct][e];
+          if (r < wi.nr) out[(int64_t)rrows[wi.row0 + r].out * mo + c] = (double)acc[0][ct][e];
         }
       }
     }
@@ -1491,7 +1357,7 @@ __device__ __forceinline__ void mvt_tile(int b, const T* __restrict__ phi, int64
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
             const int h = Mfma<T>::row(g, e);
-            if (h < wi.nr) out[(int64_t)(wi.out0 + h * wi.s + l) * m16 + c] = (double)acc[l][ct][e];
+            if (h < wi.nr) out[(int64_t)(wi.out0 + h * wi.s + l) * mo + c] = (double)acc[l][ct][e];
           }
         }
       }
@@ -1504,9 +1370,11 @@ __global__ void __launch_bounds__(kMvtThreads) __attribute__((amdgpu_waves_per_e
 k_mv_t_tile(const T* __restrict__ phi, int64_t ld_phi, const T* __restrict__ q, int64_t ld_q,
             const MvtWave* __restrict__ waves, const MvtRankRow* __restrict__ rrows,
             const MvtGroup* __restrict__ groups, int n_groups, int n_splits, int64_t split_len,
-            const TV* __restrict__ V, int64_t ldv, int64_t n, int m, int m16, int64_t rank, double* __restrict__ part) {
-  mvt_tile<T, TV, NCT>(blockIdx.x, phi, ld_phi, q, ld_q, waves, rrows, groups, n_groups, n_splits, split_len, V, ldv, n,
-                       m, m16, rank, part);
+            const TV* __restrict__ V, int64_t ldv, int64_t n, int m, int m16, int mo, int64_t rank,
+            double* __restrict__ part) {
+  const int c0 = blockIdx.y * m16;                  // the slab's first column
+  mvt_tile<T, TV, NCT>(blockIdx.x, phi, ld_phi, q, ld_q, waves, rrows, groups, n_groups, n_splits, split_len, V + c0, ldv,
+                       n, m - c0, m16, mo, rank, part + c0);
 }
 
 int matvec_tile_nl(int prec, int nct) {
@@ -1522,18 +1390,19 @@ hipError_t launch_matvec_t_tile(const void* phi, int64_t ld_phi, const void* q, 
                                 const MvtWave* waves, const MvtRankRow* rank_rows, const MvtGroup* groups,
                                 int n_groups, int n_splits,
                                 int64_t split_len, const void* V, int64_t ldv, int64_t n, int m, int m16,
-                                int64_t rank, double* partials, int prec, int io, hipStream_t s) {
-  if (m16 < 16 || m16 > 64 || m16 % 16 || n_groups < 1 || n_splits < 1 || split_len % kMvtCH)
+                                int n_slabs, int mo, int64_t rank, double* partials, int prec, int io, hipStream_t s) {
+  if (m16 < 16 || m16 > 64 || m16 % 16 || n_slabs < 1 || mo < n_slabs * m16 || m <= (n_slabs - 1) * m16 ||
+      n_groups < 1 || n_splits < 1 || split_len % kMvtCH)
     return hipErrorInvalidValue;
   if ((int64_t)(n_splits - 1) * split_len >= n || (int64_t)n_splits * split_len < n) return hipErrorInvalidValue;
   const int cpl = m16 / 16;
   const size_t lds = matvec_tile_lds_bytes(m16, prec);
   const unsigned n_blocks = (unsigned)(((n_splits + 7) / 8) * 8 * n_groups);
 #define HDF_MVTT(T, TV, NC)                                                                                   \
-  k_mv_t_tile<T, TV, NC><<<n_blocks, kMvtThreads, lds, s>>>((const T*)phi, ld_phi, (const T*)q, ld_q, waves,          \
+  k_mv_t_tile<T, TV, NC><<<dim3(n_blocks, n_slabs), kMvtThreads, lds, s>>>((const T*)phi, ld_phi, (const T*)q, ld_q, waves,          \
                                                     rank_rows, groups,                                        \
                                                     n_groups, n_splits, split_len, (const TV*)V, ldv, n, m,   \
-                                                    m16, rank, partials)
+                                                    m16, mo, rank, partials)
 #define HDF_MVTT_NCT(T, TV)                                                                                   \
   do {                                                                                                        \
     if (cpl == 1) HDF_MVTT(T, TV, 1);                                                                         \
@@ -2370,36 +2239,6 @@ hipError_t launch_narrow_n(const void* phi, int64_t ld_phi, const void* q, int64
 }
 #undef HDF_NW
 #undef HDF_NW_M
-
-constexpr int kMvNctF = 4;   // column tiles per item of k_mv_t, binary32
-constexpr int kMvNctD = 2;   // column tiles per item of k_mv_t, binary64
-
-int matvec_row_block() { return 16 * kMvtRowTiles; }
-int matvec_col_tiles(int prec) { return prec == 1 ? kMvNctF : kMvNctD; }
-
-hipError_t launch_matvec_t(const void* phi, int64_t ld_phi, const void* q, int64_t ld_q,
-                           const DegDev* degs, const TileDev* tiles, int n_tiles, int max_nct,
-                           const void* V, int64_t ldv, int64_t n, int m, int m16, int n_splits,
-                           int64_t split_len, int64_t rank, double* partials, int prec, int io,
-                           hipStream_t s) {
-  (void)max_nct;
-  const dim3 grid(n_tiles, n_splits);
-  if (prec == 1 && io == 0)
-    k_mv_t<float, kMvNctF, float><<<grid, 64, 0, s>>>((const float*)phi, ld_phi, (const float*)q, ld_q, degs,
-                                                     tiles, (const float*)V, ldv, n, m, m16, split_len, rank,
-                                                     partials);
-  else if (prec == 0 && io == 1)
-    k_mv_t<double, kMvNctD, double><<<grid, 64, 0, s>>>((const double*)phi, ld_phi, (const double*)q, ld_q,
-                                                       degs, tiles, (const double*)V, ldv, n, m, m16,
-                                                       split_len, rank, partials);
-  else if (prec == 0 && io == 0)
-    k_mv_t<double, kMvNctD, float><<<grid, 64, 0, s>>>((const double*)phi, ld_phi, (const double*)q, ld_q,
-                                                      degs, tiles, (const float*)V, ldv, n, m, m16,
-                                                      split_len, rank, partials);
-  else
-    return hipErrorInvalidValue;
-  return hipGetLastError();
-}
 
 hipError_t launch_matvec_reduce(const double* partials, int n_splits, int64_t rank, int m16, const int32_t* src,
                                 int64_t n_blocks, const double* lam_row, double* W, void* Wd, void* Wb, int prec,

@@ -85,25 +85,12 @@ struct DegDev {
   int32_t boff;   // first block of the degree in pass 2's block-ordered copy of D W
   int32_t pad[2];
 };
-struct TileDev {
-  int32_t deg;    // index into DegDev
-  int32_t h0;     // first harmonic of the row block
-  int32_t ct0;    // first 16-wide output column tile of the slice
-  int32_t pad;
-};
 // Contraction launchers: prec is the factor's storage and arithmetic type (1 = binary32,
 // 0 = binary64), io the type of V and KV (0 = float32, 1 = float64).  Supported pairs:
 // (1, 0), (0, 1) and (0, 0), the last for a binary64 factor of binary32 data.
-int matvec_row_block();          // harmonic rows per pass-1 row block
-int matvec_col_tiles(int prec);  // 16-wide column tiles per pass-1 launch slice
 
-// Pass 1: partial[split][row][c] = sum_{i in split} U[i,row] V[i,c]
-// (row = (k,h,l), c < m16, binary64 partials).
-hipError_t launch_matvec_t(const void* phi, int64_t ld_phi, const void* q, int64_t ld_q,
-                           const DegDev* degs, const TileDev* tiles, int n_tiles, int max_nct,
-                           const void* V, int64_t ldv, int64_t n, int m, int m16, int n_splits,
-                           int64_t split_len, int64_t rank, double* partials, int prec, int io,
-                           hipStream_t s);
+// Pass 1: partial[split][row][c] = sum_{i in split} U[i,row] V[i,c] (row = (k,h,l), c < m16, rows of mo
+// entries, binary64); with n_slabs > 1 the m columns are n_slabs slabs of m16.
 // Pass 1, tile-major (m16 <= 64).  A wave item is one 16-row tile of one
 // degree's harmonics with a range of nl <= matvec_tile_nl(prec, NCT) of its
 // radial functions and the column tiles [ct0, ct0 + nct) (NCT = 1, 2 or 4
@@ -146,7 +133,7 @@ hipError_t launch_matvec_t_tile(const void* phi, int64_t ld_phi, const void* q, 
                                 const MvtWave* waves, const MvtRankRow* rank_rows, const MvtGroup* groups,
                                 int n_groups, int n_splits,
                                 int64_t split_len, const void* V, int64_t ldv, int64_t n, int m, int m16,
-                                int64_t rank, double* partials, int prec, int io, hipStream_t s);
+                                int n_slabs, int mo, int64_t rank, double* partials, int prec, int io, hipStream_t s);
 // Pass 2 takes D W in blocks of 16 harmonics x one radial function, batch after batch of a degree and
 // degree after degree (n_blocks = sum over degrees of ceil(nh / 16) s; the degrees' first blocks in
 // DegDev::boff), 16 m16 values per block.  launch_matvec_reduce sums the pass-1 partials over the
