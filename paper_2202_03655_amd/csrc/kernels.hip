@@ -400,6 +400,14 @@ __device__ __forceinline__ void radial_point(const Tin* __restrict__ x_soa, int6
   t = (2.0 * s - u0 - u1) / (u1 - u0);
 }
 
+// A wavefront of the Gram passes takes chunks of `tpc` tiles of 16 points: lane p < 16 tpc evaluates the
+// radial variables of the chunk's point p (a division per coordinate, the longest part of a tile) once
+// and leaves them in LDS for the lanes that use them.  Chunks of four tiles keep all lanes busy with it;
+// where that would leave wavefronts of the launch without a chunk, chunks of one.  Evaluated by each
+// lane that used them, k_gram2 took 351 us on 200,000 points in d = 4 (thirteen degrees) and 156 so; in
+// one of sixteen lanes for a tile, k_gram 99 us on 1e6 points in d = 5 and 86 so.
+static int gram_chunk_tiles(int64_t n, int64_t waves) { return (n + 63) / 64 >= waves ? 4 : 1; }
+
 // A 16-point tile feeds four MFMA K-steps: in step e, lane group g (lanes
 // 16g..16g+15) supplies point tile*16 + g + 4e, lane r of the group supplies
 // row / column index r of the two operands.  Any bijection between (g, e)
@@ -409,7 +417,7 @@ __device__ __forceinline__ void radial_point(const Tin* __restrict__ x_soa, int6
 template <typename Tin, int MODE, int NRT, int NCT>
 __global__ void __launch_bounds__(256) k_gram(const Tin* __restrict__ x_soa, int64_t ldx, int64_t n,
                                                int d, const GeoDev* __restrict__ geo, double u0,
-                                               double u1, int K, double* __restrict__ part) {
+                                               double u1, int K, int tpc, double* __restrict__ part) {
   constexpr int nrt = NRT, nct = NCT;
   typedef typename std::conditional<MODE == 0, double, float>::type T;
   typedef typename Mfma<T>::V V;
@@ -417,6 +425,7 @@ __global__ void __launch_bounds__(256) k_gram(const Tin* __restrict__ x_soa, int
   // T_c(t) (c < 16 NCT) and rho^2 of a tile's 16 points, one row per point, per wavefront
   constexpr int TCS = 16 * NCT + 1;
   __shared__ double tcs[4][16 * TCS];
+  __shared__ double rad[4][2 * 64];                 // rho^2 and t of the chunk's points
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int li = lane & 15, g = lane >> 4;
   const double Reff = geo->Reff;
@@ -434,89 +443,100 @@ __global__ void __launch_bounds__(256) k_gram(const Tin* __restrict__ x_soa, int
   for (int a = 0; a < NRT; ++a)
 #pragma unroll
     for (int b = 0; b < NCT; ++b) acc[a][b] = V{0, 0, 0, 0};
-  for (int64_t tile = (int64_t)blockIdx.x * 4 + wave; tile < ntile; tile += (int64_t)gridDim.x * 4) {
-    double w[NRT][4], tc[NCT][4];
-    // the radial point and the T_c(t) recurrence of point g + 4 e run once, in lane e of group g,
-    // and go through LDS to the sixteen lanes that use them (T_c for c = b*16 + li, rho^2 for
-    // the powers rho^(2k), k = a*16 + li)
-    double* trow = &tcs[wave][0];
-    if (li < 4) {
-      const int64_t i = tile * 16 + g + 4 * li;
+  const int64_t tiles_step = (int64_t)gridDim.x * 4 * tpc;
+  for (int64_t tile0 = ((int64_t)blockIdx.x * 4 + wave) * tpc; tile0 < ntile; tile0 += tiles_step) {
+    if (lane < 16 * tpc) {
+      const int64_t i = tile0 * 16 + lane;
       double rho2 = 0.0, tp = 0.0;
       if (i < n) radial_point(x_soa, ldx, i, d, geo, Reff, u0, u1, rho2, tp);
-      double* dst = trow + (g + 4 * li) * TCS;
-      dst[16 * NCT] = rho2;
-      double tm1 = 1.0, t0 = tp;
-#pragma unroll
-      for (int c = 0; c < 16 * NCT; ++c) {
-        double cur;
-        if (c == 0) cur = 1.0;
-        else if (c == 1) cur = tp;
-        else { cur = 2.0 * tp * t0 - tm1; tm1 = t0; t0 = cur; }
-        dst[c] = cur;
-      }
+      rad[wave][lane] = rho2;
+      rad[wave][64 + lane] = tp;
     }
-    // the rows are read by the other lanes of the wavefront (wavefront-synchronous exchange; the
-    // next tile's rows are written after this tile's MFMAs, which every lane reaches first)
     __builtin_amdgcn_wave_barrier();
+    for (int tt = 0; tt < tpc; ++tt) {
+      const int64_t tile = tile0 + tt;
+      if (tile >= ntile) break;                       // uniform
+      double w[NRT][4], tc[NCT][4];
+      // the T_c(t) recurrence of point g + 4 e runs once, in lane e of group g, and goes through LDS to
+      // the sixteen lanes that use it (T_c for c = b*16 + li, rho^2 for the powers rho^(2k),
+      // k = a*16 + li)
+      double* trow = &tcs[wave][0];
+      if (li < 4) {
+        const double rho2 = rad[wave][16 * tt + g + 4 * li], tp = rad[wave][64 + 16 * tt + g + 4 * li];
+        double* dst = trow + (g + 4 * li) * TCS;
+        dst[16 * NCT] = rho2;
+        double tm1 = 1.0, t0 = tp;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int64_t i = tile * 16 + g + 4 * e;
-      const double rho2 = trow[(g + 4 * e) * TCS + 16 * NCT];
-#pragma unroll
-      for (int a = 0; a < NRT; ++a) {
-        const int k = a * 16 + li;
-        double pw = 0.0;
-        if (i < n && a < nrt && k <= K) {
-          pw = 1.0;
-          double base = rho2;
-          for (int q = k; q > 0; q >>= 1) {
-            if (q & 1) pw *= base;
-            base *= base;
-          }
-        }
-        w[a][e] = pw;
-      }
-    }
-#pragma unroll
-    for (int b = 0; b < NCT; ++b) {
-      const int c = b * 16 + li;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) tc[b][e] = (b < nct && c <= 2 * K) ? trow[(g + 4 * e) * TCS + c] : 0.0;
-    }
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int64_t i = tile * 16 + g + 4 * e;
-#pragma unroll
-      for (int a = 0; a < NRT; ++a) {
-        if (a >= nrt) continue;
-#pragma unroll
-        for (int b = 0; b < NCT; ++b) {
-          if (b >= nct) continue;
-          const double wv = (i < n) ? w[a][e] : 0.0;
-          if constexpr (MODE == 2) {
-            const float ah = (float)wv, al = (float)(wv - (double)ah);
-            const float bh = (float)tc[b][e], bl = (float)(tc[b][e] - (double)bh);
-            acc[a][b] = Mfma<float>::run(ah, bh, acc[a][b]);
-            acc[a][b] = Mfma<float>::run(ah, bl, acc[a][b]);
-            acc[a][b] = Mfma<float>::run(al, bh, acc[a][b]);
-          } else {
-            acc[a][b] = Mfma<T>::run((T)wv, (T)tc[b][e], acc[a][b]);
-          }
+        for (int c = 0; c < 16 * NCT; ++c) {
+          double cur;
+          if (c == 0) cur = 1.0;
+          else if (c == 1) cur = tp;
+          else { cur = 2.0 * tp * t0 - tm1; tm1 = t0; t0 = cur; }
+          dst[c] = cur;
         }
       }
-    }
-    // binary32 accumulators are flushed to binary64 every 4 tiles (64 points)
-    if (MODE != 0 && ++since_flush == 4) {
-      since_flush = 0;
+      // the rows are read by the other lanes of the wavefront (wavefront-synchronous exchange; the
+      // next tile's rows are written after this tile's MFMAs, which every lane reaches first)
+      __builtin_amdgcn_wave_barrier();
 #pragma unroll
-      for (int a = 0; a < NRT; ++a)
+      for (int e = 0; e < 4; ++e) {
+        const int64_t i = tile * 16 + g + 4 * e;
+        const double rho2 = trow[(g + 4 * e) * TCS + 16 * NCT];
 #pragma unroll
-        for (int b = 0; b < NCT; ++b) {
-#pragma unroll
-          for (int e = 0; e < 4; ++e) dacc[a][b][e] += (double)acc[a][b][e];
-          acc[a][b] = V{0, 0, 0, 0};
+        for (int a = 0; a < NRT; ++a) {
+          const int k = a * 16 + li;
+          double pw = 0.0;
+          if (i < n && a < nrt && k <= K) {
+            pw = 1.0;
+            double base = rho2;
+            for (int q = k; q > 0; q >>= 1) {
+              if (q & 1) pw *= base;
+              base *= base;
+            }
+          }
+          w[a][e] = pw;
         }
+      }
+#pragma unroll
+      for (int b = 0; b < NCT; ++b) {
+        const int c = b * 16 + li;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) tc[b][e] = (b < nct && c <= 2 * K) ? trow[(g + 4 * e) * TCS + c] : 0.0;
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int64_t i = tile * 16 + g + 4 * e;
+#pragma unroll
+        for (int a = 0; a < NRT; ++a) {
+          if (a >= nrt) continue;
+#pragma unroll
+          for (int b = 0; b < NCT; ++b) {
+            if (b >= nct) continue;
+            const double wv = (i < n) ? w[a][e] : 0.0;
+            if constexpr (MODE == 2) {
+              const float ah = (float)wv, al = (float)(wv - (double)ah);
+              const float bh = (float)tc[b][e], bl = (float)(tc[b][e] - (double)bh);
+              acc[a][b] = Mfma<float>::run(ah, bh, acc[a][b]);
+              acc[a][b] = Mfma<float>::run(ah, bl, acc[a][b]);
+              acc[a][b] = Mfma<float>::run(al, bh, acc[a][b]);
+            } else {
+              acc[a][b] = Mfma<T>::run((T)wv, (T)tc[b][e], acc[a][b]);
+            }
+          }
+        }
+      }
+      // binary32 accumulators are flushed to binary64 every 4 tiles (64 points)
+      if (MODE != 0 && ++since_flush == 4) {
+        since_flush = 0;
+#pragma unroll
+        for (int a = 0; a < NRT; ++a)
+#pragma unroll
+          for (int b = 0; b < NCT; ++b) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) dacc[a][b][e] += (double)acc[a][b][e];
+            acc[a][b] = V{0, 0, 0, 0};
+          }
+      }
     }
   }
 #pragma unroll
@@ -545,26 +565,32 @@ __global__ void __launch_bounds__(256) k_gram(const Tin* __restrict__ x_soa, int
     }
 }
 
-// Fixed-order sum over block partial records: out[e] = sum_b part[b][e].
 // Fixed-order sum of the per-block partial records, out[e] = sum_b part[b][e].
-// A block owns 64 consecutive entries; wavefront w takes the records
-// b = w, w + 4, ... with eight independent running sums (loads in flight),
-// and the four wavefront sums are combined in a fixed order through LDS.
-__global__ void __launch_bounds__(256) k_gram_fin(const double* __restrict__ part, int nblk, int total,
-                                                   double* __restrict__ out) {
-  __shared__ double red[4][64];
+// A block owns 64 consecutive entries; wavefront w takes the records b = w, w + 16, ... with eight
+// independent running sums (loads in flight), and the sixteen wavefront sums are combined in a fixed
+// order through LDS.  A few blocks (512 entries make eight) read 1,024 records: the chain of loads of a
+// wavefront is what takes the time.
+constexpr int kFinWaves = 16;
+
+__global__ void __launch_bounds__(64 * kFinWaves) k_gram_fin(const double* __restrict__ part, int nblk, int total,
+                                                             double* __restrict__ out) {
+  __shared__ double red[kFinWaves][64];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int e = blockIdx.x * 64 + lane;
   const int ee = e < total ? e : 0;
   double acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
   int b = w;
-  for (; b + 28 < nblk; b += 32)
+  for (; b + 7 * kFinWaves < nblk; b += 8 * kFinWaves)
 #pragma unroll
-    for (int u = 0; u < 8; ++u) acc[u] += part[(int64_t)(b + 4 * u) * total + ee];
-  for (; b < nblk; b += 4) acc[0] += part[(int64_t)b * total + ee];
+    for (int u = 0; u < 8; ++u) acc[u] += part[(int64_t)(b + kFinWaves * u) * total + ee];
+  for (; b < nblk; b += kFinWaves) acc[0] += part[(int64_t)b * total + ee];
   red[w][lane] = ((acc[0] + acc[1]) + (acc[2] + acc[3])) + ((acc[4] + acc[5]) + (acc[6] + acc[7]));
   __syncthreads();
-  if (w == 0 && e < total) out[e] = (red[0][lane] + red[1][lane]) + (red[2][lane] + red[3][lane]);
+  if (w == 0 && e < total) {
+    double t = 0.0;
+    for (int v = 0; v < kFinWaves; ++v) t += red[v][lane];
+    out[e] = t;
+  }
 }
 
 int gram_blocks(int64_t n) {
@@ -580,9 +606,9 @@ hipError_t launch_gram(const void* x_soa, int dtype, int64_t ldx, int64_t n, int
                        double* partials, double* moments, hipStream_t s) {
   const int nrt = (K + 1 + 15) / 16, nct = (2 * K + 1 + 15) / 16;
   if (nrt > kGramRowTiles || nct > kGramColTiles) return hipErrorInvalidValue;
-  const int nb = gram_blocks(n);
+  const int nb = gram_blocks(n), tpc = gram_chunk_tiles(n, 4 * nb);
 #define GRAM_TILES(TIN, MODE, R, C)                                                               \
-  k_gram<TIN, MODE, R, C><<<nb, 256, 0, s>>>((const TIN*)x_soa, ldx, n, d, geo, u0, u1, K, partials)
+  k_gram<TIN, MODE, R, C><<<nb, 256, 0, s>>>((const TIN*)x_soa, ldx, n, d, geo, u0, u1, K, tpc, partials)
 #define GRAM_LAUNCH(TIN, MODE)                                                                    \
   do {                                                                                            \
     if (nrt == 1 && nct == 1) GRAM_TILES(TIN, MODE, 1, 1);                                         \
@@ -603,7 +629,7 @@ hipError_t launch_gram(const void* x_soa, int dtype, int64_t ldx, int64_t n, int
 #undef GRAM_LAUNCH
 #undef GRAM_TILES
   const int total = nrt * 16 * nct * 16;
-  k_gram_fin<<<(total + 63) / 64, 256, 0, s>>>(partials, nb, total, moments);
+  k_gram_fin<<<(total + 63) / 64, 64 * kFinWaves, 0, s>>>(partials, nb, total, moments);
   return hipGetLastError();
 }
 
@@ -619,13 +645,14 @@ hipError_t launch_gram(const void* x_soa, int dtype, int64_t ldx, int64_t n, int
 template <typename Tin>
 __global__ void __launch_bounds__(256) k_gram2(const Tin* __restrict__ x_soa, int64_t ldx, int64_t n,
                                                 int d, const GeoDev* __restrict__ geo, double u0,
-                                                double u1, int K, const double* __restrict__ T1,
+                                                double u1, int K, int tpc, const double* __restrict__ T1,
                                                 const int32_t* __restrict__ t1_off,
                                                 const int32_t* __restrict__ sel, int n_sel,
                                                 double* __restrict__ part) {
   typedef Mfma<double>::V V;
   __shared__ double t1s[32 * 32];
   __shared__ double sh[4][4 * 64];
+  __shared__ double rad[4][2 * 64];                 // t and rho^k of the chunk's points
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int li = lane & 15, g = lane >> 4;
   const int k = sel[blockIdx.y];
@@ -641,14 +668,13 @@ __global__ void __launch_bounds__(256) k_gram2(const Tin* __restrict__ x_soa, in
     for (int b = 0; b < 2; ++b) acc[a][b] = V{0, 0, 0, 0};
   const bool j0 = li < L, j1 = 16 + li < L;
   const int64_t ntile = (n + 15) / 16;
-  for (int64_t tile = (int64_t)blockIdx.x * 4 + wave; tile < ntile; tile += (int64_t)gridDim.x * 4) {
-    double t[4], rk[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int64_t i = tile * 16 + g + 4 * e;
-      double rho2 = 0.0, tt = 0.0, pw = 0.0;
+  const int64_t tiles_step = (int64_t)gridDim.x * 4 * tpc;
+  for (int64_t tile0 = ((int64_t)blockIdx.x * 4 + wave) * tpc; tile0 < ntile; tile0 += tiles_step) {
+    if (lane < 16 * tpc) {
+      const int64_t i = tile0 * 16 + lane;
+      double rho2 = 0.0, tp = 0.0, pw = 0.0;
       if (i < n) {
-        radial_point(x_soa, ldx, i, d, geo, Reff, u0, u1, rho2, tt);
+        radial_point(x_soa, ldx, i, d, geo, Reff, u0, u1, rho2, tp);
         pw = 1.0;
         double base = sqrt(rho2);
         for (int q = k; q > 0; q >>= 1) {
@@ -656,32 +682,42 @@ __global__ void __launch_bounds__(256) k_gram2(const Tin* __restrict__ x_soa, in
           base *= base;
         }
       }
-      t[e] = tt;
-      rk[e] = pw;
+      rad[wave][lane] = tp;
+      rad[wave][64 + lane] = pw;
     }
-    double z0[4] = {0, 0, 0, 0}, z1[4] = {0, 0, 0, 0};
-    double tm1[4], tc[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) { tm1[e] = 0.0; tc[e] = 1.0; }
-    for (int a = 0; a < L; ++a) {
-      const double c0 = j0 ? t1s[a * L + li] : 0.0;
-      const double c1 = j1 ? t1s[a * L + 16 + li] : 0.0;
+    __builtin_amdgcn_wave_barrier();
+    for (int tt = 0; tt < tpc; ++tt) {
+      if (tile0 + tt >= ntile) break;                 // uniform
+      double t[4], rk[4];
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        if (a == 1) { tm1[e] = 1.0; tc[e] = t[e]; }
-        else if (a >= 2) { const double tn = 2.0 * t[e] * tc[e] - tm1[e]; tm1[e] = tc[e]; tc[e] = tn; }
-        const double ya = rk[e] * tc[e];
-        z0[e] += c0 * ya;
-        z1[e] += c1 * ya;
+        t[e] = rad[wave][16 * tt + g + 4 * e];
+        rk[e] = rad[wave][64 + 16 * tt + g + 4 * e];
       }
-    }
+      double z0[4] = {0, 0, 0, 0}, z1[4] = {0, 0, 0, 0};
+      double tm1[4], tc[4];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      acc[0][0] = Mfma<double>::run(z0[e], z0[e], acc[0][0]);
-      if (nt > 1) {
-        acc[0][1] = Mfma<double>::run(z0[e], z1[e], acc[0][1]);
-        acc[1][0] = Mfma<double>::run(z1[e], z0[e], acc[1][0]);
-        acc[1][1] = Mfma<double>::run(z1[e], z1[e], acc[1][1]);
+      for (int e = 0; e < 4; ++e) { tm1[e] = 0.0; tc[e] = 1.0; }
+      for (int a = 0; a < L; ++a) {
+        const double c0 = j0 ? t1s[a * L + li] : 0.0;
+        const double c1 = j1 ? t1s[a * L + 16 + li] : 0.0;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          if (a == 1) { tm1[e] = 1.0; tc[e] = t[e]; }
+          else if (a >= 2) { const double tn = 2.0 * t[e] * tc[e] - tm1[e]; tm1[e] = tc[e]; tc[e] = tn; }
+          const double ya = rk[e] * tc[e];
+          z0[e] += c0 * ya;
+          if (nt > 1) z1[e] += c1 * ya;               // uniform
+        }
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        acc[0][0] = Mfma<double>::run(z0[e], z0[e], acc[0][0]);
+        if (nt > 1) {
+          acc[0][1] = Mfma<double>::run(z0[e], z1[e], acc[0][1]);
+          acc[1][0] = Mfma<double>::run(z1[e], z0[e], acc[1][0]);
+          acc[1][1] = Mfma<double>::run(z1[e], z1[e], acc[1][1]);
+        }
       }
     }
   }
@@ -716,16 +752,16 @@ hipError_t launch_gram2(const void* x_soa, int dtype, int64_t ldx, int64_t n, in
                         const int32_t* t1_off, const int32_t* sel, int n_sel, double* partials,
                         double* out, hipStream_t s) {
   if (K + 1 > 32 || n_sel < 1) return hipErrorInvalidValue;
-  const int nb = gram2_blocks(n, n_sel);
+  const int nb = gram2_blocks(n, n_sel), tpc = gram_chunk_tiles(n, 4 * nb);
   const dim3 grid(nb, n_sel);
   if (dtype == 0)
-    k_gram2<float><<<grid, 256, 0, s>>>((const float*)x_soa, ldx, n, d, geo, u0, u1, K, T1, t1_off, sel,
+    k_gram2<float><<<grid, 256, 0, s>>>((const float*)x_soa, ldx, n, d, geo, u0, u1, K, tpc, T1, t1_off, sel,
                                         n_sel, partials);
   else
-    k_gram2<double><<<grid, 256, 0, s>>>((const double*)x_soa, ldx, n, d, geo, u0, u1, K, T1, t1_off, sel,
+    k_gram2<double><<<grid, 256, 0, s>>>((const double*)x_soa, ldx, n, d, geo, u0, u1, K, tpc, T1, t1_off, sel,
                                          n_sel, partials);
   const int total = n_sel * 1024;
-  k_gram_fin<<<(total + 63) / 64, 256, 0, s>>>(partials, nb, total, out);
+  k_gram_fin<<<(total + 63) / 64, 64 * kFinWaves, 0, s>>>(partials, nb, total, out);
   return hipGetLastError();
 }
 
