@@ -1148,14 +1148,17 @@ hipError_t launch_adj_combine(const void* x_soa, int dtype, int64_t ldx, int64_t
 // per-column-tile kernel before and now: 1e6 points x 168 18.9 and 12.3 ms, 100,003 x 128 binary64 5.1 and
 // 3.5, 44,599 x 80 0.31 and 0.18, 9,973 x 100 0.21 and 0.09.
 // Prefetch depth (chunks of the tile in flight) and occupancy per type and column tiles, chosen so
-// that the registers fit without spills: binary32 with one column tile 4 chunks deep at four
-// wavefronts per SIMD (<= 128 registers), otherwise 2 deep (binary32: four wavefronts, three with
-// four column tiles; binary64: two with one column tile, three with more).
+// that the loops hold their registers: binary32 at four wavefronts per SIMD (<= 128 registers, two
+// workgroups on a CU), with one column tile 4 chunks deep, otherwise 2; binary64 two with one column
+// tile (117 registers all the same), three with more.  Binary32 with four column tiles spills one
+// register around the loop: at three wavefronts (132 registers, one workgroup on a CU) 64 columns on 1e6
+// points took 2.3 ms instead of 2.05.  Binary64 with more column tiles spills inside the loop at four: the
+// product of 64 columns took 7.1 ms instead of 4.5, of 32 columns 1.71 instead of 1.46.
 // Without the occupancy hint the scheduler hoists the operands of all radial functions and
 // overflows the registers.
 template <typename T, int NCT> struct MvtPF { static constexpr int value = sizeof(T) == 4 && NCT == 1 ? 4 : 2; };
 template <typename T, int NCT> struct MvtWaves {
-  static constexpr int value = sizeof(T) == 4 ? (NCT < 4 ? 4 : 3) : (NCT == 1 ? 2 : 3);
+  static constexpr int value = sizeof(T) == 4 ? 4 : (NCT == 1 ? 2 : 3);
 };
 // radial functions per wave item (accumulator tiles per wavefront: NL * NCT); binary32 with two
 // column tiles keeps three, the registers of four spill
