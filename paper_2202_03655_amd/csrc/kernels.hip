@@ -1152,7 +1152,7 @@ hipError_t launch_adj_combine(const void* x_soa, int dtype, int64_t ldx, int64_t
 // workgroups on a CU), with one column tile 4 chunks deep, otherwise 2; binary64 two with one column
 // tile (117 registers all the same), three with more.  Binary32 with four column tiles spills one
 // register around the loop: at three wavefronts (132 registers, one workgroup on a CU) 64 columns on 1e6
-// points took 2.3 ms instead of 2.05.  Binary64 with more column tiles spills inside the loop at four: the
+// points took 2.31 ms instead of 2.04.  Binary64 with more column tiles spills inside the loop at four: the
 // product of 64 columns took 7.1 ms instead of 4.5, of 32 columns 1.71 instead of 1.46.
 // Without the occupancy hint the scheduler hoists the operands of all radial functions and
 // overflows the registers.
