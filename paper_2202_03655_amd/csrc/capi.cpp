@@ -649,8 +649,11 @@ static bool mf_tables(hdf_factor* f, const std::vector<int32_t>& col_of, std::ve
     return g;
   };
   std::vector<int32_t> so1, so2;
-  f->mf_g1 = groups(s1, r1, 17, hdf::kMfSlots1, hdf::kMfBlock1, [] { hdf::MfSlot1 x{}; x.out0 = -1; return x; }, so1);
-  f->mf_g2 = groups(s2, r2, 5, hdf::kMfSlots2, hdf::kMfBlock2, [] { hdf::MfSlot2 x{}; x.nv = 0; return x; }, so2);
+  const bool f32 = f->fprec == 1;
+  f->mf_g1 = groups(s1, r1, 17, hdf::mf_slots(f32, f->mf_spec, 1), hdf::kMfBlock1,
+                    [] { hdf::MfSlot1 x{}; x.out0 = -1; return x; }, so1);
+  f->mf_g2 = groups(s2, r2, 5, hdf::mf_slots(f32, f->mf_spec, 2), hdf::kMfBlock2,
+                    [] { hdf::MfSlot2 x{}; x.nv = 0; return x; }, so2);
   if ((int64_t)r1.size() > f->mf_nr1 || (int64_t)r2.size() > f->mf_nr2) return false;   // the LDS layout's room
   f->mf_nr1 = (int)r1.size();
   f->mf_nr2 = (int)r2.size();
@@ -747,8 +750,6 @@ static hdf_status finish_build(hdf_factor* f, double t0, hipStream_t s) {
       const int64_t g = std::max<int64_t>(1, (t + cap - 1) / cap);
       return t + g * hdf::kMfWaves * (block - 1);
     };
-    f->mf_nr1 = (int)(17 * padded(t1, hdf::kMfSlots1, hdf::kMfBlock1));
-    f->mf_nr2 = (int)(5 * padded(t2, hdf::kMfSlots2, hdf::kMfBlock2));
     f->mf_t1 = t1;
     f->mf_t2 = t2;
     int lmax = 1;
@@ -758,6 +759,8 @@ static hdf_status finish_build(hdf_factor* f, double t0, hipStream_t s) {
     f->mf_nqc = (int64_t)f->mf_spad * f->mf_lpad;
     const int64_t ntasks = d == 3 ? 2 * Kh + 1 : (int64_t)(Kh + 1) * (Kh + 1);
     auto lays = [&](bool spec) {
+      f->mf_nr1 = (int)(17 * padded(t1, hdf::mf_slots(f->fprec == 1, spec, 1), hdf::kMfBlock1));
+      f->mf_nr2 = (int)(5 * padded(t2, hdf::mf_slots(f->fprec == 1, spec, 2), hdf::kMfBlock2));
       f->mf_lay1 = hdf::mf_layout(f->mf_nloop, (int)f->S, f->mf_nr1, f->mf_nqc, ntasks, d, Kh, f->fprec, 1, spec);
       f->mf_lay2 = hdf::mf_layout(f->mf_nloop, (int)f->S, f->mf_nr2, f->mf_nqc, ntasks, d, Kh, f->fprec, 2, spec);
     };

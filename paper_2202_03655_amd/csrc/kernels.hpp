@@ -257,8 +257,12 @@ struct MfLayout {
 // spec: the wavefront-specialised kernels (2 kMfWaves wavefronts, the chunk data double-buffered)
 MfLayout mf_layout(int64_t n_loop, int S, int64_t n_rows, int64_t n_qcoef, int64_t n_tasks, int d, int K, int prec,
                    int pass, bool spec);
-constexpr int kMfSlots1 = 16;            // pass-1 accumulator tiles per wavefront
-constexpr int kMfSlots2 = 64;            // pass-2 steps per wavefront (their D W operands stay in registers)
+// Pass-1 accumulator tiles and pass-2 steps per wavefront (the D W operands of the steps stay in
+// registers).  Ranks beyond a workgroup's slots take several slot groups, each of which evaluates the
+// factor again.  The plain binary32 kernels run where two buffers of the harmonics exceed LDS, so one
+// workgroup has a CU and half the wavefronts per SIMD: they take the registers for half as many again.
+// 1e6 points in d = 5 of rank 2142, 16 columns: 7.9 ms with 16 and 64 (two groups a pass), 4.6 so.
+constexpr int mf_slots(bool f32, bool spec, int pass) { return (f32 && !spec ? 3 : 2) * (pass == 1 ? 8 : 32); }
 // A wavefront's slot list is padded to whole blocks (pass 1: padding slots have out0 = -1; pass 2:
 // nv = 0) so that the kernels test the list length once per block.
 constexpr int kMfBlock1 = 4;

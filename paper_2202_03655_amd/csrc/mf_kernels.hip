@@ -53,9 +53,9 @@ template <> struct MfMma<double> {
 #endif
 
 constexpr int kMfThreads = 64 * kMfWaves;
-static_assert(kMfSlots1 % kMfBlock1 == 0 && kMfSlots2 % kMfBlock2 == 0, "slot lists are whole blocks");
-// wavefronts per SIMD the register budget targets: binary32 two workgroups per CU, binary64 one
-template <typename T> struct MfWavesPerEu { static constexpr int value = sizeof(T) == 4 ? 4 : 2; };
+static_assert(mf_slots(true, true, 1) % kMfBlock1 == 0 && mf_slots(true, true, 2) % kMfBlock2 == 0 &&
+                  mf_slots(true, false, 1) % kMfBlock1 == 0 && mf_slots(true, false, 2) % kMfBlock2 == 0,
+              "slot lists are whole blocks");
 
 // Four consecutive LDS values (one 16-byte read in binary32, two in binary64).
 template <typename T>
@@ -430,7 +430,7 @@ template <bool SPEC> struct MfMode {
   static constexpr int nbuf = SPEC ? 2 : 1;
 };
 template <typename T, bool SPEC> struct MfWaves {
-  static constexpr int value = SPEC ? 4 : MfWavesPerEu<T>::value;
+  static constexpr int value = SPEC ? 4 : 2;        // the plain kernels: one workgroup of eight per CU
 };
 // In the specialised kernels the two roles run separate loops with the same number of barriers (on
 // the device every s_barrier of a workgroup counts alike); the CPU emulation of the kernels is told
@@ -502,7 +502,7 @@ k_mf_t(MfArgs a, MfLayout lay, const MfSlot1* __restrict__ slots, const int32_t*
        const int32_t* __restrict__ rows, int n_rows, int cpl, int64_t split_len, const Tin* __restrict__ V,
        int64_t ldv, int m, int m16, int64_t rank, double* __restrict__ part) {
   typedef typename MfMma<T>::V Acc;
-  constexpr int NS = kMfSlots1;
+  constexpr int NS = mf_slots(sizeof(T) == 4, SPEC, 1);
   extern __shared__ unsigned char smem_raw[];
   T* phc = reinterpret_cast<T*>(smem_raw + lay.phc);            // nbuf buffers of lay.phc_len values
   T* qc = reinterpret_cast<T*>(smem_raw + lay.qc);
@@ -657,7 +657,7 @@ __attribute__((amdgpu_waves_per_eu(MfWaves<T, SPEC>::value, 8)))
 k_mf_n(MfArgs a, MfLayout lay, const MfSlot2* __restrict__ slots, const int32_t* __restrict__ slot_off,
        const int32_t* __restrict__ rows, int n_rows, int cpl, int64_t range_len, const T* __restrict__ Wd, int m16,
        Tin* __restrict__ KV, int64_t ldkv, int m, int n_groups, T* __restrict__ part) {
-  constexpr int NS = kMfSlots2;
+  constexpr int NS = mf_slots(sizeof(T) == 4, SPEC, 2);
   extern __shared__ unsigned char smem_raw[];
   T* phc = reinterpret_cast<T*>(smem_raw + lay.phc);
   T* qc = reinterpret_cast<T*>(smem_raw + lay.qc);
