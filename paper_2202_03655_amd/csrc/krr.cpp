@@ -404,6 +404,8 @@ hdf_status hdf_krr_create(const double* points, int64_t n, int d, int64_t ld, co
     hdf_status st = hdf::batch_create(factors, pos, s, &h->batch);
     if (st != HDF_OK) return st;
   }
+  // the call is blocking: the system may be used on any stream from here on
+  KCHK(hipStreamSynchronize(s));
   *out = h.release();
   return HDF_OK;
 }

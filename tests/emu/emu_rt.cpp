@@ -512,6 +512,8 @@ hipError_t hipOccupancyMaxActiveBlocksPerMultiprocessor(int* nb, const void*, in
 hipError_t hipGetLastError() { hipError_t e = emu::g_last; emu::g_last = hipSuccess; return e; }
 const char* hipGetErrorString(hipError_t e) { return e ? "emulated error" : "no error"; }
 void emu_flush() { emu::flush(); }
+// operations enqueued and not yet run: what a caller would find pending on its streams
+long long emu_pending() { return (long long)emu::q.size(); }
 void emu_register(void* p, size_t n) { emu::user_regions[(uintptr_t)p] = n; }
 hipError_t hipGetSymbolAddress(void** p, const void* symbol) {
   if (!emu::allocs.count((uintptr_t)symbol)) {
