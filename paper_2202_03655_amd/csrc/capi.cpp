@@ -1866,7 +1866,8 @@ hdf_status hdf_matvec_noalloc(hdf_handle h, const void* V, int64_t m, int64_t ld
 // rows (k, j, h') with their harmonics h of degree k.  They depend on the dimension and the largest
 // degree only and are fitted once (harmonic_derivative_maps); entries below 1e-12 of a degree's largest
 // are rounding of the fit (the exact ones are square roots of ratios of small integers) and are left
-// out.  The last kAdjMaps used are kept for the process; a handle holds the one it has enqueued work on.
+// out.  The last kAdjMaps used are kept for the process; a handle keeps its own until it is freed, since
+// its enqueued work may read it.
 struct AdjMap {
   int dev = 0, d = 0, K = 0;
   DevBuf row, h, v;
@@ -1940,11 +1941,9 @@ static hdf_status adjoint_dx(hdf_handle h, const double* gv, const double* gw, i
   const int Kh = h->kept_k.back();
   const size_t fel = h->felem();
   const int io = h->fprec == 1 ? 0 : 1;          // contraction outputs in the factor's type
-  {
-    std::shared_ptr<AdjMap> map;
-    const hdf_status st = adjoint_map(h, Kh, s, &map);
+  if (!h->adj_map) {                              // d and Kh are the handle's own: looked up once
+    const hdf_status st = adjoint_map(h, Kh, s, &h->adj_map);
     if (st != HDF_OK) return st;
-    h->adj_map = map;
   }
   // shifted-factor degrees: harmonics of k - 1 with the radial rows and rank of degree k
   if (h->adj_degs_host.empty() && Kh >= 1) {

@@ -438,8 +438,10 @@ hipError_t hipMalloc(void** p, size_t b) {
   *p = m;
   return hipSuccess;
 }
+static long long g_frees = 0;
 hipError_t hipFree(void* p) {
   emu::flush();
+  ++g_frees;
   if (!p) return hipSuccess;
   if (!emu::allocs.erase((uintptr_t)p)) { fprintf(stderr, "EMU hipFree of unknown %p\n", p); abort(); }
   auto it = g_guarded.find((uintptr_t)p);
@@ -513,6 +515,7 @@ hipError_t hipGetLastError() { hipError_t e = emu::g_last; emu::g_last = hipSucc
 const char* hipGetErrorString(hipError_t e) { return e ? "emulated error" : "no error"; }
 void emu_flush() { emu::flush(); }
 // operations enqueued and not yet run: what a caller would find pending on its streams
+long long emu_frees() { return g_frees; }
 long long emu_pending() { return (long long)emu::q.size(); }
 void emu_register(void* p, size_t n) { emu::user_regions[(uintptr_t)p] = n; }
 hipError_t hipGetSymbolAddress(void** p, const void* symbol) {

@@ -14,7 +14,8 @@ import torch
 import run_cases as rc
 from run_cases import _raw, check, dense, hdf, rel, to_dev, wl
 
-_raw.emu_pending.restype = ctypes.c_longlong
+for _f in ("emu_pending", "emu_frees"):
+    getattr(_raw, _f).restype = ctypes.c_longlong
 
 
 def _krr(n=90, k=3, d=3, seed=31):
@@ -36,7 +37,46 @@ def case_krr_create():
     check("krr_create apply", e <= 1e-6, f"{e:.2e}")
 
 
-CASES = {"krr_create": case_krr_create}
+def _ball_factor(l, tol, n=24):
+    return hdf.Factor(to_dev(wl.unit_ball(n, 3, 33), torch.float64), "gaussian", l, tol, precision=hdf.HDF_FP64)
+
+
+def _degree(f):
+    s_k = f.info()["s_k"]
+    assert all(s_k[:len(s_k)]) or s_k.index(0) == len([x for x in s_k if x]), "kept degrees are 0..K"
+    return sum(1 for x in s_k if x) - 1
+
+
+def _dx(f, n=24):
+    W, V = (to_dev(wl.rhs(n, 1, s), torch.float64) for s in (34, 35))
+    g = f.backward(W, V, need_l=False)[1]
+    _raw.emu_flush()
+    return g.numpy().copy()
+
+
+def case_adjoint_map():
+    """A factor keeps the derivative map that its enqueued work reads: factors of nine other degrees, then another of its
+    own degree, come between two of its gradients, and the second gives back no memory."""
+    first = _ball_factor(1.0, 1e-4)
+    g1, K = _dx(first), _degree(first)
+    seen = {K}
+    for tol in (1e-1, 1e-2, 1e-3, 1e-5, 1e-6, 1e-7, 1e-8, 1e-10, 1e-11):
+        for l in (0.8, 1.0, 1.6):
+            f = _ball_factor(l, tol)
+            if _degree(f) not in seen and len(seen) < 10:
+                seen.add(_degree(f))
+                _dx(f)
+    check("adjoint_map degrees", len(seen) == 10, f"{sorted(seen)}")
+    other = _ball_factor(1.0, 1e-4)
+    _dx(other)
+    before = _raw.emu_frees()
+    g2 = _dx(first)
+    freed = _raw.emu_frees() - before
+    check("adjoint_map kept", freed == 0, f"{freed} buffers given back while work may read them")
+    check("adjoint_map gradient", np.array_equal(g1, g2), "the same bits again")
+
+
+CASES = {"adjoint_map": case_adjoint_map, "krr_create": case_krr_create}
 
 if __name__ == "__main__":
     rc._install()
