@@ -152,7 +152,7 @@ struct DevBuf {
     if (b <= bytes && p) return hipSuccess;
     if (p) {
       // work enqueued on the old block may still run
-      hipError_t e = hipDeviceSynchronize();
+      hipError_t e = hdf::wait_device(dev);
       if (e != hipSuccess) return e;
       release();
     }
@@ -176,6 +176,16 @@ double now_ms() {
 namespace hdf {
 hdf_status set_error(hdf_status s, const std::string& msg) { return fail(s, msg); }
 void clear_error() { g_err.clear(); }
+hipError_t wait_device(int dev) {
+  int cur = 0;
+  hipError_t e = hipGetDevice(&cur);
+  if (e != hipSuccess) return e;
+  if (cur == dev) return hipDeviceSynchronize();
+  if ((e = hipSetDevice(dev)) != hipSuccess) return e;
+  e = hipDeviceSynchronize();
+  const hipError_t back = hipSetDevice(cur);
+  return e != hipSuccess ? e : back;
+}
 hipError_t pool_alloc(void** p, size_t b, size_t* got, int* dev) { return pool::alloc(p, b, got, dev); }
 void pool_release(void* p, size_t bytes, int dev) { pool::release(p, bytes, dev); }
 }  // namespace hdf
@@ -259,8 +269,9 @@ struct hdf_factor {
   std::shared_ptr<struct AdjMap> adj_map;
   hdf::BuildTables tables{};
   ~hdf_factor() {
-    // the device buffers go back to the allocator cache once no enqueued work can use them
-    (void)hipDeviceSynchronize();
+    // the device buffers go back to the allocator cache once no enqueued work can use them (the points'
+    // buffer is the first of a build: without it nothing was enqueued)
+    if (x_soa.p) (void)hdf::wait_device(x_soa.dev);
     if (ev_b0) hipEventDestroy(ev_b0);
     if (ev_b1) hipEventDestroy(ev_b1);
     for (auto& e : ev_mv)
@@ -2342,7 +2353,9 @@ struct ProductBatch {
   std::vector<MvBatch> host;     // outlives its upload
   MvBatchGrid grid{};
   DevBuf desc, ws;
-  ~ProductBatch() { (void)hipDeviceSynchronize(); }
+  ~ProductBatch() {
+    if (ws.p) (void)wait_device(ws.dev);
+  }
 };
 
 hdf_status batch_create(const std::vector<hdf_handle>& factors, const std::vector<int64_t>& pos, hipStream_t s,

@@ -32,7 +32,7 @@ constexpr int kBatch = 8;          // CG iterations enqueued per convergence che
 #endif
 constexpr int kBuildLanes = 9;
 
-// Device memory from the library's allocator cache, given back after the device is idle.
+// Device memory from the library's allocator cache, given back after its device is idle.
 struct Buf {
   void* p = nullptr;
   size_t bytes = 0;
@@ -40,7 +40,7 @@ struct Buf {
   ~Buf() { release(); }
   void release() {
     if (!p) return;
-    (void)hipDeviceSynchronize();
+    (void)hdf::wait_device(dev);
     hdf::pool_release(p, bytes, dev);
     p = nullptr;
   }

@@ -15,6 +15,8 @@ void clear_error();
 // Switch the HIP events around a factor's products on or off (hdf_info then
 // reports no kernel times for them).  Products on many small factors use off.
 void set_product_timing(hdf_handle h, bool on);
+// Waits for everything enqueued on device `dev`, whichever device is current.
+hipError_t wait_device(int dev);
 // The library's caching device allocator: a block of at least b bytes, its size and device; a block is
 // given back only when no enqueued work can use it.
 hipError_t pool_alloc(void** p, size_t b, size_t* got, int* dev);

@@ -482,7 +482,10 @@ hipError_t hipMemsetAsync(void* dst, int v, size_t b, hipStream_t s) {
   return hipSuccess;
 }
 hipError_t hipStreamSynchronize(hipStream_t) { emu::flush(); return hipSuccess; }
-hipError_t hipDeviceSynchronize() { emu::flush(); return hipSuccess; }
+// two devices with one queue and one memory; a wait for the current one is counted
+static thread_local int g_device = 0;
+static long long g_waits[2] = {0, 0};
+hipError_t hipDeviceSynchronize() { ++g_waits[g_device]; emu::flush(); return hipSuccess; }
 hipError_t hipEventCreate(hipEvent_t* e) { *e = new emu_event; return hipSuccess; }
 hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) { *e = new emu_event; return hipSuccess; }
 // one queue runs all work in submission order: every stream wait is already satisfied
@@ -502,7 +505,13 @@ hipError_t hipEventElapsedTime(float* ms, hipEvent_t a, hipEvent_t b) {
   return hipSuccess;
 }
 hipError_t hipMemGetInfo(size_t* f, size_t* t) { *f = (size_t)200 << 30; *t = (size_t)288 << 30; return hipSuccess; }
-hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
+hipError_t hipGetDevice(int* d) { *d = g_device; return hipSuccess; }
+hipError_t hipSetDevice(int d) {
+  if (d < 0 || d > 1) return hipErrorInvalidValue;
+  g_device = d;
+  return hipSuccess;
+}
+long long emu_waits(int d) { return g_waits[d]; }
 // a small device: 4 CUs, one workgroup of a kernel at a time, the gfx950 LDS limit
 hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t a, int) {
   if (a == hipDeviceAttributeMaxSharedMemoryPerBlock) *v = 160 * 1024;

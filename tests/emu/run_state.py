@@ -14,7 +14,7 @@ import torch
 import run_cases as rc
 from run_cases import _raw, check, dense, hdf, rel, to_dev, wl
 
-for _f in ("emu_pending", "emu_frees"):
+for _f in ("emu_pending", "emu_frees", "emu_waits"):
     getattr(_raw, _f).restype = ctypes.c_longlong
 
 
@@ -76,7 +76,23 @@ def case_adjoint_map():
     check("adjoint_map gradient", np.array_equal(g1, g2), "the same bits again")
 
 
-CASES = {"adjoint_map": case_adjoint_map, "krr_create": case_krr_create}
+def case_own_device():
+    """What is freed while another device is current waits for its own device."""
+    for what in ("factor", "krr"):
+        _raw.hipSetDevice(1)
+        obj = _ball_factor(1.0, 1e-4) if what == "factor" else _krr()[1]
+        _raw.hipSetDevice(0)
+        before = _raw.emu_waits(0), _raw.emu_waits(1)
+        del obj
+        now = _raw.emu_waits(0), _raw.emu_waits(1)
+        check(f"own_device {what}", now[1] > before[1] and now[0] == before[0],
+              f"waits for devices 0 and 1: {before} before, {now} after")
+        dev = ctypes.c_int(-1)
+        _raw.hipGetDevice(ctypes.byref(dev))
+        check(f"own_device {what} current", dev.value == 0, f"device {dev.value} is current")
+
+
+CASES = {"own_device": case_own_device, "adjoint_map": case_adjoint_map, "krr_create": case_krr_create}
 
 if __name__ == "__main__":
     rc._install()
