@@ -1873,12 +1873,9 @@ hdf_status hdf_matvec_noalloc(hdf_handle h, const void* V, int64_t m, int64_t ld
   return HDF_OK;
 }
 
-// The derivative maps of the harmonic basis on the device: dS_{k,h}/dx_j = sum_h' G_k^(j)[h][h'] S_{k-1,h'},
-// rows (k, j, h') with their harmonics h of degree k.  They depend on the dimension and the largest
-// degree only and are fitted once (harmonic_derivative_maps); entries below 1e-12 of a degree's largest
-// are rounding of the fit (the exact ones are square roots of ratios of small integers) and are left
-// out.  The last kAdjMaps used are kept for the process; a handle keeps its own until it is freed, since
-// its enqueued work may read it.
+// The derivative maps of the harmonic basis (SparseMaps) on the device.  They depend on the dimension and
+// the largest degree only.  The host keeps all that it has fitted; on the device the last kAdjMaps used are
+// kept for the process, and a handle keeps its own until it is freed, since its enqueued work may read it.
 struct AdjMap {
   int dev = 0, d = 0, K = 0;
   DevBuf row, h, v;
@@ -1891,51 +1888,44 @@ static hdf_status adjoint_map(hdf_handle f, int Kh, hipStream_t s, std::shared_p
   const int d = f->d;
   int dev = 0;
   HIPCHK(hipGetDevice(&dev));
-  std::lock_guard<std::mutex> lk(*mu);
-  for (size_t i = 0; i < kept->size(); ++i)
-    if ((*kept)[i]->dev == dev && (*kept)[i]->d == d && (*kept)[i]->K == Kh) {
-      *out = (*kept)[i];
-      kept->erase(kept->begin() + i);
-      kept->push_back(*out);
-      return HDF_OK;
-    }
-  hdf::ChainCoeffs cc;
-  hdf::chain_coeffs(d, Kh, cc);
-  std::vector<int> rows_k(Kh + 1);
-  for (int k = 0; k <= Kh; ++k) rows_k[k] = f->degs[k].hoff;
-  std::vector<std::vector<double>> g;
-  hdf::harmonic_derivative_maps(d, Kh, cc, f->col_of_host.data(), (int)f->H, rows_k, g);
-  std::vector<int32_t> row(1, 0), hh;
-  std::vector<double> val;
-  for (int k = 1; k <= Kh; ++k) {
-    const int n0 = f->degs[k].nh, n1 = f->degs[k - 1].nh;
-    double big = 0.0;
-    for (double x : g[k]) big = std::max(big, std::fabs(x));
-    for (int j = 0; j < d; ++j)
-      for (int hp = 0; hp < n1; ++hp) {
-        for (int h0 = 0; h0 < n0; ++h0) {
-          const double x = g[k][((size_t)j * n0 + h0) * n1 + hp];
-          if (std::fabs(x) > 1e-12 * big) {
-            hh.push_back(h0);
-            val.push_back(x);
-          }
-        }
-        row.push_back((int32_t)hh.size());
+  auto find = [&] {
+    for (size_t i = 0; i < kept->size(); ++i)
+      if ((*kept)[i]->dev == dev && (*kept)[i]->d == d && (*kept)[i]->K == Kh) {
+        *out = (*kept)[i];
+        kept->erase(kept->begin() + i);
+        kept->push_back(*out);
+        return true;
       }
+    return false;
+  };
+  {
+    std::lock_guard<std::mutex> lk(*mu);
+    if (find()) return HDF_OK;
   }
+  const hdf::SparseMaps& maps = hdf::derivative_maps(d, Kh, [&] {
+    hdf::ChainCoeffs cc;
+    hdf::chain_coeffs(d, Kh, cc);
+    std::vector<int> rows_k(Kh + 1);
+    for (int k = 0; k <= Kh; ++k) rows_k[k] = f->degs[k].hoff;
+    std::vector<std::vector<double>> g;
+    hdf::harmonic_derivative_maps(d, Kh, cc, f->col_of_host.data(), (int)f->H, rows_k, g);
+    return hdf::sparse_maps(d, Kh, g);
+  });
   auto m = std::make_shared<AdjMap>();
   m->dev = dev;
   m->d = d;
   m->K = Kh;
-  HIPCHK(m->row.ensure(row.size() * 4));
-  HIPCHK(m->h.ensure(std::max<size_t>(hh.size(), 1) * 4));
-  HIPCHK(m->v.ensure(std::max<size_t>(val.size(), 1) * 8));
-  HIPCHK(hipMemcpyAsync(m->row.p, row.data(), row.size() * 4, hipMemcpyHostToDevice, s));
-  if (!hh.empty()) {
-    HIPCHK(hipMemcpyAsync(m->h.p, hh.data(), hh.size() * 4, hipMemcpyHostToDevice, s));
-    HIPCHK(hipMemcpyAsync(m->v.p, val.data(), val.size() * 8, hipMemcpyHostToDevice, s));
+  HIPCHK(m->row.ensure(maps.row.size() * 4));
+  HIPCHK(m->h.ensure(std::max<size_t>(maps.h.size(), 1) * 4));
+  HIPCHK(m->v.ensure(std::max<size_t>(maps.v.size(), 1) * 8));
+  HIPCHK(hipMemcpyAsync(m->row.p, maps.row.data(), maps.row.size() * 4, hipMemcpyHostToDevice, s));
+  if (!maps.h.empty()) {
+    HIPCHK(hipMemcpyAsync(m->h.p, maps.h.data(), maps.h.size() * 4, hipMemcpyHostToDevice, s));
+    HIPCHK(hipMemcpyAsync(m->v.p, maps.v.data(), maps.v.size() * 8, hipMemcpyHostToDevice, s));
   }
   HIPCHK(hipStreamSynchronize(s));                 // other streams may use the map from here on
+  std::lock_guard<std::mutex> lk(*mu);
+  if (find()) return HDF_OK;                       // another thread's came first; nothing reads this one
   if (kept->size() >= kAdjMaps) kept->erase(kept->begin());
   kept->push_back(m);
   *out = m;

@@ -656,6 +656,37 @@ void harmonic_derivative_maps(int d, int K, const ChainCoeffs& cc, const int32_t
   }
 }
 
+SparseMaps sparse_maps(int d, int K, const std::vector<std::vector<double>>& G) {
+  SparseMaps m;
+  m.row.push_back(0);
+  for (int k = 1; k <= K; ++k) {
+    const int n0 = (int)index_count(d, k), n1 = (int)index_count(d, k - 1);
+    double big = 0.0;
+    for (double x : G[k]) big = std::max(big, std::fabs(x));
+    for (int j = 0; j < d; ++j)
+      for (int hp = 0; hp < n1; ++hp) {
+        for (int h = 0; h < n0; ++h) {
+          const double x = G[k][((size_t)j * n0 + h) * n1 + hp];
+          if (std::fabs(x) > 1e-12 * big) {
+            m.h.push_back(h);
+            m.v.push_back(x);
+          }
+        }
+        m.row.push_back((int32_t)m.h.size());
+      }
+  }
+  return m;
+}
+
+const SparseMaps& derivative_maps(int d, int K, const std::function<SparseMaps()>& fit) {
+  static std::mutex* mu = new std::mutex;
+  static auto* maps = new std::map<std::pair<int, int>, SparseMaps>;
+  std::lock_guard<std::mutex> lk(*mu);
+  auto it = maps->find({d, K});
+  if (it == maps->end()) it = maps->emplace(std::make_pair(d, K), fit()).first;
+  return it->second;                    // entries are neither moved nor removed
+}
+
 // ------------------------------------------------------------ eigen
 void jacobi_eigh(int n, double* A, double* w, double* V) {
   for (int i = 0; i < n; ++i)

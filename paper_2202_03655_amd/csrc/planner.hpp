@@ -170,4 +170,16 @@ void harmonics_and_gradients(int d, int K, const ChainCoeffs& cc, const int32_t*
 void harmonic_derivative_maps(int d, int K, const ChainCoeffs& cc, const int32_t* col_of, int H,
                               const std::vector<int>& rows_k, std::vector<std::vector<double>>& G);
 
+// The same maps without their zeros: row (k, j, h') for k = 1..K, j < d, h' of degree k - 1 holds entries
+// [row[i], row[i + 1]), each a harmonic h of degree k and the value G_k^(j)[h][h'].  Entries below 1e-12 of a
+// degree's largest are rounding of the fit (the exact ones are square roots of ratios of small integers).
+struct SparseMaps {
+  std::vector<int32_t> row, h;
+  std::vector<double> v;
+};
+SparseMaps sparse_maps(int d, int K, const std::vector<std::vector<double>>& G);
+// The maps of dimension d and degrees 0..K, kept for the process: `fit` makes them on the first call (a
+// call for others waits meanwhile).  At most HDF_MAX_DIM - 2 dimensions times HDF_MAX_DEGREE / 2 + 1 of them.
+const SparseMaps& derivative_maps(int d, int K, const std::function<SparseMaps()>& fit);
+
 }  // namespace hdf
