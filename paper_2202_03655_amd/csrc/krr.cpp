@@ -25,11 +25,7 @@ namespace {
 
 constexpr int kMaxBlock = 16384;   // largest cluster: its dense block is 2 GiB
 constexpr int kBatch = 8;          // CG iterations enqueued per convergence check
-// Block builds in flight at once: the host pool's workers (at most eight) and the caller.  The CPU
-// emulation (no allocator cache) has one host thread and builds them one after the other.
-#ifndef HDF_ALLOC_CACHE
-#define HDF_ALLOC_CACHE 1
-#endif
+// Block builds in flight at once: the host pool's workers (at most eight) and the caller.
 constexpr int kBuildLanes = 9;
 
 // Device memory from the library's allocator cache, given back after its device is idle.
@@ -306,7 +302,6 @@ hdf_status hdf_krr_create(const double* points, int64_t n, int d, int64_t ld, co
       return hdf_build(h->xs.as<double>() + B.pos * d, 1, B.n, d, d, kernel, lengthscale, tol, HDF_FP64, t,
                        &h->fac[h->block_cluster[b]]);
     };
-#if HDF_ALLOC_CACHE
     const int lanes_n = std::min(nb, kBuildLanes);
     struct Lanes {
       std::vector<hipStream_t> free;
@@ -346,7 +341,6 @@ hdf_status hdf_krr_create(const double* points, int64_t n, int d, int64_t ld, co
       lanes.free.push_back(t);
     });
     hdf::clear_error();
-#endif
     for (int b = 0; b < nb; ++b) {
       const int c = h->block_cluster[b];
       const hdf_status st = h->fac[c] ? HDF_OK : build(b, s);

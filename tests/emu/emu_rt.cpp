@@ -30,10 +30,21 @@
 #include <cstdlib>
 #include <deque>
 #include <map>
+#include <mutex>
+#include <thread>
 #include <vector>
 #include <chrono>
 
 namespace emu {
+
+// Host threads may call the runtime at the same time: one lock over its state, held while queued work runs.
+static std::recursive_mutex& mu() {
+  static auto* m = new std::recursive_mutex;
+  return *m;
+}
+struct Lock {
+  std::lock_guard<std::recursive_mutex> lk{mu()};
+};
 
 enum { READY = 0, BARRIER = 1, MFMA32 = 2, MFMA64 = 3, DONE = 4, SHFL = 5 };
 
@@ -59,6 +70,7 @@ static long long g_block_serial = 0;
 static std::map<const void*, long long> g_shared_filled;
 static int g_garbage = getenv("EMU_FILL") ? (int)strtol(getenv("EMU_FILL"), nullptr, 0) : 0xbe;
 static long long g_launches = 0;
+static std::map<std::thread::id, long long> g_by_thread;   // kernel launches by host thread
 static hipError_t g_last = hipSuccess;
 const char* g_kernel_name = "";
 
@@ -218,7 +230,9 @@ void check_launch(unsigned grid, unsigned block, size_t shm) {
 }
 
 void run_grid(dim3 grid, unsigned block, size_t shm, const std::function<void()>& body) {
+  Lock lock;
   ++g_launches;
+  ++g_by_thread[std::this_thread::get_id()];
   const size_t ss = (getenv("EMU_STACK_KB") ? atoi(getenv("EMU_STACK_KB")) : 128) * 1024;
   if (fibers.size() < block) {
     size_t old = fibers.size();
@@ -355,7 +369,10 @@ void run_grid(dim3 grid, unsigned block, size_t shm, const std::function<void()>
 
 // ---- queue ----
 static std::deque<std::function<void()>> q;
-void enqueue(hipStream_t, std::function<void()> f) { q.push_back(std::move(f)); }
+void enqueue(hipStream_t, std::function<void()> f) {
+  Lock lock;
+  q.push_back(std::move(f));
+}
 static void flush() {
   while (!q.empty()) {
     auto f = std::move(q.front());
@@ -395,6 +412,7 @@ static void check_range(const void* p, size_t n, bool dev, const char* what) {
 static bool strict() { static const bool s = getenv("EMU_STRICT") != nullptr; return s; }
 void check_ptr(const char* kname, const char* what, int idx, const void* p) {
   if (!strict() || !p) return;
+  Lock lock;
   if (in_dev(p, 1) || in_user(p, 1)) return;
   fprintf(stderr, "EMU STRICT: kernel %s %s #%d = %p is not device memory\n", kname, what, idx, p);
   fflush(stderr);
@@ -419,7 +437,7 @@ static long long g_tick = 0;
 
 extern "C" {
 static std::map<uintptr_t, std::pair<void*, size_t>> g_guarded;
-hipError_t hipMalloc(void** p, size_t b) {
+hipError_t hipMalloc(void** p, size_t b) { emu::Lock lock;
   void* m = nullptr;
   static const bool guard = getenv("EMU_GUARD") != nullptr;
   if (guard) {
@@ -439,7 +457,7 @@ hipError_t hipMalloc(void** p, size_t b) {
   return hipSuccess;
 }
 static long long g_frees = 0;
-hipError_t hipFree(void* p) {
+hipError_t hipFree(void* p) { emu::Lock lock;
   emu::flush();
   ++g_frees;
   if (!p) return hipSuccess;
@@ -451,14 +469,14 @@ hipError_t hipFree(void* p) {
 }
 static bool dev_dst(hipMemcpyKind k) { return k == hipMemcpyHostToDevice || k == hipMemcpyDeviceToDevice; }
 static bool dev_src(hipMemcpyKind k) { return k == hipMemcpyDeviceToHost || k == hipMemcpyDeviceToDevice; }
-hipError_t hipMemcpyAsync(void* dst, const void* src, size_t b, hipMemcpyKind k, hipStream_t s) {
+hipError_t hipMemcpyAsync(void* dst, const void* src, size_t b, hipMemcpyKind k, hipStream_t s) { emu::Lock lock;
   emu::check_range(dst, b, dev_dst(k), "memcpy dst");
   emu::check_range(src, b, dev_src(k), "memcpy src");
   emu::enqueue(s, [=]() { memcpy(dst, src, b); });
   return hipSuccess;
 }
 hipError_t hipMemcpy2DAsync(void* dst, size_t dp, const void* src, size_t sp, size_t w, size_t h,
-                            hipMemcpyKind k, hipStream_t s) {
+                            hipMemcpyKind k, hipStream_t s) { emu::Lock lock;
   if (w > dp || w > sp) { fprintf(stderr, "EMU memcpy2D width > pitch\n"); return hipErrorInvalidValue; }
   if (h) {
     emu::check_range(dst, dp * (h - 1) + w, dev_dst(k), "memcpy2D dst");
@@ -469,65 +487,66 @@ hipError_t hipMemcpy2DAsync(void* dst, size_t dp, const void* src, size_t sp, si
   });
   return hipSuccess;
 }
-hipError_t hipMemset2DAsync(void* dst, size_t pitch, int v, size_t w, size_t h, hipStream_t s) {
+hipError_t hipMemset2DAsync(void* dst, size_t pitch, int v, size_t w, size_t h, hipStream_t s) { emu::Lock lock;
   if (h) emu::check_range(dst, pitch * (h - 1) + w, true, "memset2D");
   emu::enqueue(s, [=]() {
     for (size_t r = 0; r < h; ++r) memset((char*)dst + r * pitch, v, w);
   });
   return hipSuccess;
 }
-hipError_t hipMemsetAsync(void* dst, int v, size_t b, hipStream_t s) {
+hipError_t hipMemsetAsync(void* dst, int v, size_t b, hipStream_t s) { emu::Lock lock;
   emu::check_range(dst, b, true, "memset");
   emu::enqueue(s, [=]() { memset(dst, v, b); });
   return hipSuccess;
 }
-hipError_t hipStreamSynchronize(hipStream_t) { emu::flush(); return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t) { emu::Lock lock; emu::flush(); return hipSuccess; }
 // two devices with one queue and one memory; a wait for the current one is counted
 static thread_local int g_device = 0;
 static long long g_waits[2] = {0, 0};
-hipError_t hipDeviceSynchronize() { ++g_waits[g_device]; emu::flush(); return hipSuccess; }
-hipError_t hipEventCreate(hipEvent_t* e) { *e = new emu_event; return hipSuccess; }
-hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) { *e = new emu_event; return hipSuccess; }
+hipError_t hipDeviceSynchronize() { emu::Lock lock; ++g_waits[g_device]; emu::flush(); return hipSuccess; }
+hipError_t hipEventCreate(hipEvent_t* e) { emu::Lock lock; *e = new emu_event; return hipSuccess; }
+hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) { emu::Lock lock; *e = new emu_event; return hipSuccess; }
 // one queue runs all work in submission order: every stream wait is already satisfied
 hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) { static char dummy[8]; *s = (hipStream_t)dummy; return hipSuccess; }
-hipError_t hipStreamDestroy(hipStream_t) { return hipSuccess; }
-hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuccess; }
-hipError_t hipEventDestroy(hipEvent_t e) { delete e; return hipSuccess; }
-hipError_t hipEventRecord(hipEvent_t e, hipStream_t s) {
+hipError_t hipStreamDestroy(hipStream_t) { emu::Lock lock; return hipSuccess; }
+hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { emu::Lock lock; return hipSuccess; }
+hipError_t hipEventDestroy(hipEvent_t e) { emu::Lock lock; delete e; return hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t e, hipStream_t s) { emu::Lock lock;
   e->done = false;
   emu::enqueue(s, [e]() { e->done = true; e->t = ++g_tick; });
   return hipSuccess;
 }
-hipError_t hipEventSynchronize(hipEvent_t) { emu::flush(); return hipSuccess; }
-hipError_t hipEventElapsedTime(float* ms, hipEvent_t a, hipEvent_t b) {
+hipError_t hipEventSynchronize(hipEvent_t) { emu::Lock lock; emu::flush(); return hipSuccess; }
+hipError_t hipEventElapsedTime(float* ms, hipEvent_t a, hipEvent_t b) { emu::Lock lock;
   if (!a->done || !b->done) return hipErrorNotReady;
   *ms = 0.001f * (float)(b->t - a->t);
   return hipSuccess;
 }
-hipError_t hipMemGetInfo(size_t* f, size_t* t) { *f = (size_t)200 << 30; *t = (size_t)288 << 30; return hipSuccess; }
+hipError_t hipMemGetInfo(size_t* f, size_t* t) { emu::Lock lock; *f = (size_t)200 << 30; *t = (size_t)288 << 30; return hipSuccess; }
 hipError_t hipGetDevice(int* d) { *d = g_device; return hipSuccess; }
 hipError_t hipSetDevice(int d) {
   if (d < 0 || d > 1) return hipErrorInvalidValue;
   g_device = d;
   return hipSuccess;
 }
-long long emu_waits(int d) { return g_waits[d]; }
+long long emu_launching_threads() { emu::Lock lock; return (long long)emu::g_by_thread.size(); }
+long long emu_waits(int d) { emu::Lock lock; return g_waits[d]; }
 // a small device: 4 CUs, one workgroup of a kernel at a time, the gfx950 LDS limit
-hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t a, int) {
+hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t a, int) { emu::Lock lock;
   if (a == hipDeviceAttributeMaxSharedMemoryPerBlock) *v = 160 * 1024;
   else if (a == hipDeviceAttributeMultiprocessorCount) *v = 4;
   else return hipErrorInvalidValue;
   return hipSuccess;
 }
-hipError_t hipOccupancyMaxActiveBlocksPerMultiprocessor(int* nb, const void*, int, size_t) { *nb = 1; return hipSuccess; }
-hipError_t hipGetLastError() { hipError_t e = emu::g_last; emu::g_last = hipSuccess; return e; }
+hipError_t hipOccupancyMaxActiveBlocksPerMultiprocessor(int* nb, const void*, int, size_t) { emu::Lock lock; *nb = 1; return hipSuccess; }
+hipError_t hipGetLastError() { emu::Lock lock; hipError_t e = emu::g_last; emu::g_last = hipSuccess; return e; }
 const char* hipGetErrorString(hipError_t e) { return e ? "emulated error" : "no error"; }
-void emu_flush() { emu::flush(); }
+void emu_flush() { emu::Lock lock; emu::flush(); }
 // operations enqueued and not yet run: what a caller would find pending on its streams
-long long emu_frees() { return g_frees; }
-long long emu_pending() { return (long long)emu::q.size(); }
-void emu_register(void* p, size_t n) { emu::user_regions[(uintptr_t)p] = n; }
-hipError_t hipGetSymbolAddress(void** p, const void* symbol) {
+long long emu_frees() { emu::Lock lock; return g_frees; }
+long long emu_pending() { emu::Lock lock; return (long long)emu::q.size(); }
+void emu_register(void* p, size_t n) { emu::Lock lock; emu::user_regions[(uintptr_t)p] = n; }
+hipError_t hipGetSymbolAddress(void** p, const void* symbol) { emu::Lock lock;
   if (!emu::allocs.count((uintptr_t)symbol)) {
     size_t n = 0;
     for (auto& e : emu::pending_symbols())
@@ -542,5 +561,5 @@ hipError_t hipGetSymbolAddress(void** p, const void* symbol) {
   *p = const_cast<void*>(symbol);
   return hipSuccess;
 }
-long long emu_launches() { return emu::g_launches; }
+long long emu_launches() { emu::Lock lock; return emu::g_launches; }
 }

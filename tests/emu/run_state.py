@@ -6,6 +6,7 @@ Unlike run_cases.py the library's calls are not followed by a flush unless a cas
 counters are read as a caller on another stream would find them.
 """
 import ctypes
+import os
 import sys
 
 import numpy as np
@@ -14,7 +15,7 @@ import torch
 import run_cases as rc
 from run_cases import _raw, check, dense, hdf, rel, to_dev, wl
 
-for _f in ("emu_pending", "emu_frees", "emu_waits"):
+for _f in ("emu_pending", "emu_frees", "emu_waits", "emu_launching_threads"):
     getattr(_raw, _f).restype = ctypes.c_longlong
 
 
@@ -92,7 +93,21 @@ def case_own_device():
         check(f"own_device {what} current", dev.value == 0, f"device {dev.value} is current")
 
 
-CASES = {"own_device": case_own_device, "adjoint_map": case_adjoint_map, "krr_create": case_krr_create}
+def case_krr_lanes():
+    """The concurrent block builds of a KRR system run here too (several host threads launch kernels), and the operator
+    is that of the dense system."""
+    before = _raw.emu_launching_threads()
+    X, S = _krr(n=1100, k=24, seed=37)
+    threads = _raw.emu_launching_threads() - before
+    check("krr_lanes threads", threads >= 2 or (os.cpu_count() or 1) < 2, f"{threads} more threads launched kernels")
+    v = wl.rhs(len(X), 1, 32)[:, 0]
+    y = S.apply(to_dev(v, torch.float64))
+    _raw.emu_flush()
+    e = rel(y.numpy(), dense.dense_K(X, "gaussian", 0.8) @ v + 0.1 * v)
+    check("krr_lanes apply", e <= 1e-6, f"{e:.2e}")
+
+
+CASES = {"krr_lanes": case_krr_lanes, "own_device": case_own_device, "adjoint_map": case_adjoint_map, "krr_create": case_krr_create}
 
 if __name__ == "__main__":
     rc._install()
