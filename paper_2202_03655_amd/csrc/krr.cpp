@@ -25,7 +25,7 @@ namespace {
 
 constexpr int kMaxBlock = 16384;   // largest cluster: its dense block is 2 GiB
 constexpr int kBatch = 8;          // CG iterations enqueued per convergence check
-// Block builds in flight at once: the host pool's workers (at most eight) and the caller.
+// Block builds in flight at once: the pool's workers (at most eight) and the caller.
 constexpr int kBuildLanes = 9;
 
 // Device memory from the library's allocator cache, given back after its device is idle.
@@ -293,10 +293,11 @@ hdf_status hdf_krr_create(const double* points, int64_t n, int d, int64_t ld, co
   double t0 = now_ms();
   {
     // The build of a small cluster is a serial chain of short kernels, host planning and
-    // synchronisations that leaves the device idle: the builds run on the host pool's threads, each
-    // on a stream of its own and with its own loops on its thread (30 clusters of 460 points: the whole
-    // construction and solve 21.9 ms with the builds one after the other, 10.8 ms so).  A build that fails here (its
-    // neighbours hold scratch of their own) is repeated by itself on the caller's stream.
+    // synchronisations that leaves the device idle: the builds run on the threads of a pool kept for
+    // such work, each on a stream of its own and with its own loops on its thread (30 clusters of 460
+    // points: the whole construction and solve 21.9 ms with the builds one after the other, 10.8 ms so).
+    // While another construction has the pool they run one after the other on the caller's stream, as
+    // does a build that fails here (its neighbours hold scratch of their own).
     auto build = [&](int b, hipStream_t t) {
       const Block& B = h->blocks[b];
       return hdf_build(h->xs.as<double>() + B.pos * d, 1, B.n, d, d, kernel, lengthscale, tol, HDF_FP64, t,
@@ -318,7 +319,7 @@ hdf_status hdf_krr_create(const double* points, int64_t n, int d, int64_t ld, co
       KCHK(hipStreamCreateWithFlags(&t, hipStreamNonBlocking));
       lanes.free.push_back(t);
     }
-    hdf::parallel_for(nb, [&](int b) {
+    hdf::try_device_tasks(nb, [&](int b) {
       hipStream_t t;
       {
         std::lock_guard<std::mutex> lk(lanes.mu);

@@ -65,7 +65,8 @@ double kernel_dl(int kind, double r, double l) {
 
 // ---------------------------------------------------------------- host pool
 namespace {
-thread_local bool in_pool = false;   // a task of the pool is running on this thread
+thread_local bool in_pool = false;   // a task of a pool is running on this thread
+int pool_workers() { return (int)std::min(8u, std::max(1u, std::thread::hardware_concurrency()) - 1); }
 
 class Pool {
  public:
@@ -81,11 +82,24 @@ class Pool {
     for (auto& t : workers_) t.join();
   }
   void run(int n, const std::function<void(int)>& fn) {
-    if (workers_.empty() || getpid() != pid_) {
+    if (!usable()) {
       for (int i = 0; i < n; ++i) fn(i);
       return;
     }
     std::lock_guard<std::mutex> serial(call_mu_);
+    run_locked(n, fn);
+  }
+  bool try_run(int n, const std::function<void(int)>& fn) {
+    if (!usable()) return false;
+    std::unique_lock<std::mutex> serial(call_mu_, std::try_to_lock);
+    if (!serial.owns_lock()) return false;
+    run_locked(n, fn);
+    return true;
+  }
+
+ private:
+  bool usable() const { return !workers_.empty() && getpid() == pid_; }
+  void run_locked(int n, const std::function<void(int)>& fn) {
     {
       std::lock_guard<std::mutex> lk(mu_);
       fn_ = &fn;
@@ -101,8 +115,6 @@ class Pool {
     done_.wait(lk, [&] { return finished_ == (int)workers_.size(); });
     fn_ = nullptr;
   }
-
- private:
   void work(const std::function<void(int)>& fn, int n) {
     in_pool = true;
     for (int i = next_.fetch_add(1); i < n; i = next_.fetch_add(1)) fn(i);
@@ -140,8 +152,14 @@ void parallel_for(int n, const std::function<void(int)>& fn) {
     for (int i = 0; i < n; ++i) fn(i);
     return;
   }
-  static Pool pool((int)std::min(8u, std::max(1u, std::thread::hardware_concurrency()) - 1));
+  static Pool pool(pool_workers());
   pool.run(n, fn);
+}
+
+bool try_device_tasks(int n, const std::function<void(int)>& fn) {
+  if (in_pool) return false;
+  static Pool pool(pool_workers());
+  return pool.try_run(n, fn);
 }
 
 // ---------------------------------------------------------------- DCT-II

@@ -103,10 +103,15 @@ bool place_wave_items(const std::vector<int>& loads, int wg, int ns, std::vector
                       std::vector<int>& nw);
 // Runs fn(i) for every i in [0, n) on the calling thread and the workers of a process-wide
 // pool (at most 8, created on first use), each taking the next index from a shared counter;
-// returns when every call has returned.  The calls must be independent of each other; a
-// parallel_for inside a call runs on that call's thread.  Concurrent callers are served one after the other; in a process forked
-// after the pool started, everything runs on the calling thread.
+// returns when every call has returned.  The calls must be independent of each other, and they are
+// host arithmetic: concurrent callers are served one after the other, so a call that waited for a device
+// would hold up the builds of every other thread.  A parallel_for inside a call runs on that call's thread;
+// in a process forked after the pool started, everything runs on the calling thread.
 void parallel_for(int n, const std::function<void(int)>& fn);
+// The same on a pool of its own, for calls that wait for a device.  False, with nothing run, while another
+// thread's calls have that pool, or where there are no workers (one CPU, a forked process): the caller then
+// does its work on its own thread.
+bool try_device_tasks(int n, const std::function<void(int)>& fn);
 double tau_threshold(double tol, double nu, double N, int d, int p);
 
 // Tighter degree and rank selection (remark after Eq. bound).  The relative

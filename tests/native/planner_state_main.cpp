@@ -1,10 +1,12 @@
 // Host-only driver of what the planner keeps for the process, under AddressSanitizer/UBSan and ThreadSanitizer:
 //   maps   each dimension and degree is fitted once, however many others come in between; concurrent callers
 //          get the same entry; the sparse form holds the dense entries above the fit's rounding
+//   pools  tasks that wait (for a device, here for another thread) do not hold up parallel_for, nor each other
 #include <atomic>
+#include <chrono>
 #include <cmath>
 #include <cstdio>
-#include <cstring>
+#include <string>
 #include <thread>
 #include <vector>
 
@@ -53,8 +55,42 @@ static int maps() {
   return 0;
 }
 
+static int pools() {
+  if (std::thread::hardware_concurrency() < 2) return 0;
+  // the tasks wait until another thread's parallel_for has run and its own tasks were refused
+  std::atomic<bool> done{false};
+  std::atomic<int> started{0}, late{0}, nested{0};
+  std::thread other([&] {
+    while (!started) std::this_thread::yield();
+    std::vector<int> hit(50, 0);
+    hdf::parallel_for(50, [&](int i) { hit[i] += 1; });
+    for (int h : hit)
+      if (h != 1) ++late;
+    if (hdf::try_device_tasks(4, [&](int) { ++late; })) ++late;
+    done = true;
+  });
+  std::vector<int> ran(12, 0);
+  const bool taken = hdf::try_device_tasks(12, [&](int i) {
+    ++started;
+    for (int ms = 0; !done && ms < 20000; ++ms) std::this_thread::sleep_for(std::chrono::milliseconds(1));
+    if (!done) ++late;
+    ran[i] += 1;
+    const std::thread::id self = std::this_thread::get_id();
+    hdf::parallel_for(5, [&](int) { nested += std::this_thread::get_id() == self; });
+  });
+  other.join();
+  int wrong = !taken + late + (nested != 60);
+  for (int r : ran) wrong += r != 1;
+  // the pool is free again
+  std::atomic<int> again{0};
+  wrong += !hdf::try_device_tasks(3, [&](int) { ++again; }) + (again != 3);
+  if (wrong) std::printf("pools: taken %d, late %d, nested %d, again %d\n", taken, late.load(), nested.load(), again.load());
+  return wrong != 0;
+}
+
 int main(int argc, char** argv) {
-  const int rc = argc > 1 && !std::strcmp(argv[1], "maps") ? maps() : 2;
+  const std::string what = argc > 1 ? argv[1] : "";
+  const int rc = what == "maps" ? maps() : what == "pools" ? pools() : 2;
   if (rc == 0) std::printf("ok\n");
   return rc;
 }

@@ -23,7 +23,7 @@ def exe(request, tmp_path_factory):
     return str(out)
 
 
-@pytest.mark.parametrize("case", ["maps"])
+@pytest.mark.parametrize("case", ["maps", "pools"])
 def test_kept_state(exe, case):
     r = subprocess.run([exe, case], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=120)
     assert r.returncode == 0 and "ok" in r.stdout, r.stdout
