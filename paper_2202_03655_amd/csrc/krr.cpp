@@ -25,8 +25,6 @@ namespace {
 
 constexpr int kMaxBlock = 16384;   // largest cluster: its dense block is 2 GiB
 constexpr int kBatch = 8;          // CG iterations enqueued per convergence check
-// Block builds in flight at once: the pool's workers (at most eight) and the caller.
-constexpr int kBuildLanes = 9;
 
 // Device memory from the library's allocator cache, given back after its device is idle.
 struct Buf {
@@ -303,7 +301,7 @@ hdf_status hdf_krr_create(const double* points, int64_t n, int d, int64_t ld, co
       return hdf_build(h->xs.as<double>() + B.pos * d, 1, B.n, d, d, kernel, lengthscale, tol, HDF_FP64, t,
                        &h->fac[h->block_cluster[b]]);
     };
-    const int lanes_n = std::min(nb, kBuildLanes);
+    const int lanes_n = std::min(nb, hdf::kPoolThreads);   // one for each task that can be running
     struct Lanes {
       std::vector<hipStream_t> free;
       std::mutex mu;
@@ -323,7 +321,7 @@ hdf_status hdf_krr_create(const double* points, int64_t n, int d, int64_t ld, co
       hipStream_t t;
       {
         std::lock_guard<std::mutex> lk(lanes.mu);
-        t = lanes.free.back();                  // never empty: one lane for each thread
+        t = lanes.free.back();                  // never empty: see lanes_n
         lanes.free.pop_back();
       }
       hdf_handle& f = h->fac[h->block_cluster[b]];

@@ -66,7 +66,7 @@ double kernel_dl(int kind, double r, double l) {
 // ---------------------------------------------------------------- host pool
 namespace {
 thread_local bool in_pool = false;   // a task of a pool is running on this thread
-int pool_workers() { return (int)std::min(8u, std::max(1u, std::thread::hardware_concurrency()) - 1); }
+int pool_workers() { return (int)std::min<unsigned>(kPoolThreads, std::max(1u, std::thread::hardware_concurrency())) - 1; }
 
 class Pool {
  public:

@@ -101,8 +101,10 @@ void compress_degree_cross(int k, int L, const SqrtFactor& fx, const SqrtFactor&
 // of each group.  Returns false (outputs unspecified) if the inputs admit no placement.
 bool place_wave_items(const std::vector<int>& loads, int wg, int ns, std::vector<int>& order,
                       std::vector<int>& nw);
+// Threads that run the calls of one parallel_for or try_device_tasks at the most: a pool's workers and the caller.
+constexpr int kPoolThreads = 9;
 // Runs fn(i) for every i in [0, n) on the calling thread and the workers of a process-wide
-// pool (at most 8, created on first use), each taking the next index from a shared counter;
+// pool (created on first use), each taking the next index from a shared counter;
 // returns when every call has returned.  The calls must be independent of each other, and they are
 // host arithmetic: concurrent callers are served one after the other, so a call that waited for a device
 // would hold up the builds of every other thread.  A parallel_for inside a call runs on that call's thread;

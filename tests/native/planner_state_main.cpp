@@ -81,6 +81,16 @@ static int pools() {
   other.join();
   int wrong = !taken + late + (nested != 60);
   for (int r : ran) wrong += r != 1;
+  // no more tasks at once than kPoolThreads, by which callers size what each running task holds
+  std::atomic<int> running{0}, most{0};
+  hdf::try_device_tasks(200, [&](int) {
+    const int now = ++running;
+    for (int m = most; m < now && !most.compare_exchange_weak(m, now);) {
+    }
+    std::this_thread::sleep_for(std::chrono::milliseconds(1));
+    --running;
+  });
+  wrong += most > hdf::kPoolThreads;
   // the pool is free again
   std::atomic<int> again{0};
   wrong += !hdf::try_device_tasks(3, [&](int) { ++again; }) + (again != 3);
