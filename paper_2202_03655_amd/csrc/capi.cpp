@@ -24,9 +24,11 @@
 namespace {
 
 thread_local std::string g_err;
+thread_local bool g_memory = false;   // the last failure was for want of device memory
 
-hdf_status fail(hdf_status s, const std::string& msg) {
+hdf_status fail(hdf_status s, const std::string& msg, bool memory = false) {
   g_err = msg;
+  g_memory = memory || s == HDF_E_OOM;
   return s;
 }
 
@@ -176,6 +178,7 @@ double now_ms() {
 namespace hdf {
 hdf_status set_error(hdf_status s, const std::string& msg) { return fail(s, msg); }
 void clear_error() { g_err.clear(); }
+bool failed_for_memory() { return g_memory; }
 hipError_t wait_device(int dev) {
   int cur = 0;
   hipError_t e = hipGetDevice(&cur);
@@ -799,7 +802,7 @@ static hdf_status finish_build(hdf_factor* f, double t0, hipStream_t s) {
     char buf[200];
     snprintf(buf, sizeof buf, "factor needs %.3g GB (H=%lld, S=%lld), budget %.3g GB",
              fbytes / 1e9, (long long)f->H, (long long)f->S, budget / 1e9);
-    return fail(HDF_E_INFEASIBLE, buf);
+    return fail(HDF_E_INFEASIBLE, buf, true);
   }
   if (f->H > 0) {
     if (mfree) {

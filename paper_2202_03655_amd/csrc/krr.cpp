@@ -5,6 +5,7 @@
 #include <hip/hip_runtime_api.h>
 
 #include <algorithm>
+#include <atomic>
 #include <chrono>
 #include <cmath>
 #include <cstring>
@@ -295,7 +296,9 @@ hdf_status hdf_krr_create(const double* points, int64_t n, int d, int64_t ld, co
     // such work, each on a stream of its own and with its own loops on its thread (30 clusters of 460
     // points: the whole construction and solve 21.9 ms with the builds one after the other, 10.8 ms so).
     // While another construction has the pool they run one after the other on the caller's stream, as
-    // does a build that fails here (its neighbours hold scratch of their own).
+    // does a build that finds no memory here (its neighbours hold scratch of their own).  Any other failure
+    // is the construction's, the one of the lowest cluster as when they run one after the other; clusters
+    // above it are passed over.
     auto build = [&](int b, hipStream_t t) {
       const Block& B = h->blocks[b];
       return hdf_build(h->xs.as<double>() + B.pos * d, 1, B.n, d, d, kernel, lengthscale, tol, HDF_FP64, t,
@@ -317,7 +320,15 @@ hdf_status hdf_krr_create(const double* points, int64_t n, int d, int64_t ld, co
       KCHK(hipStreamCreateWithFlags(&t, hipStreamNonBlocking));
       lanes.free.push_back(t);
     }
+    struct Failure {
+      hdf_status st = HDF_OK;
+      bool memory = false;
+      std::string msg;
+    };
+    std::vector<Failure> failure(nb);
+    std::atomic<int> first_bad{nb};
     hdf::try_device_tasks(nb, [&](int b) {
+      if (b > first_bad) return;
       hipStream_t t;
       {
         std::lock_guard<std::mutex> lk(lanes.mu);
@@ -325,26 +336,45 @@ hdf_status hdf_krr_create(const double* points, int64_t n, int d, int64_t ld, co
         lanes.free.pop_back();
       }
       hdf_handle& f = h->fac[h->block_cluster[b]];
+      Failure& e = failure[b];
       try {
-        hdf_info_t info;                        // reads the build's events while their stream is there
-        if (hipSetDevice(dev) == hipSuccess && build(b, t) == HDF_OK) hdf_info(f, &info);
-      } catch (...) {
+        hipError_t he = hipSetDevice(dev);
+        if (he != hipSuccess) {
+          e = {HDF_E_HIP, false, std::string("hipSetDevice: ") + hipGetErrorString(he)};
+        } else if ((e.st = build(b, t)) != HDF_OK) {
+          e.memory = hdf::failed_for_memory();
+          e.msg = hdf_last_error();
+        } else {
+          hdf_info_t info;                      // reads the build's events while their stream is there
+          hdf_info(f, &info);
+        }
+        if ((he = hipStreamSynchronize(t)) != hipSuccess && e.st == HDF_OK) {
+          hdf_free(f);
+          f = nullptr;
+          e = {HDF_E_HIP, false, std::string("hipStreamSynchronize: ") + hipGetErrorString(he)};
+        }
+      } catch (...) {                           // no host memory: repeated alone, as want of device memory is
         f = nullptr;
+        e.st = HDF_E_OOM;
+        e.memory = true;
       }
-      const bool idle = hipStreamSynchronize(t) == hipSuccess;
-      if (!idle && f) {
-        hdf_free(f);
-        f = nullptr;
-      }
+      if (e.st != HDF_OK && !e.memory)
+        for (int m = first_bad; b < m && !first_bad.compare_exchange_weak(m, b);) {
+        }
       std::lock_guard<std::mutex> lk(lanes.mu);
       lanes.free.push_back(t);
     });
     hdf::clear_error();
     for (int b = 0; b < nb; ++b) {
       const int c = h->block_cluster[b];
-      const hdf_status st = h->fac[c] ? HDF_OK : build(b, s);
-      if (st != HDF_OK)
-        return hdf::set_error(st, "factor of cluster " + std::to_string(c) + ": " + hdf_last_error());
+      if (!h->fac[c]) {
+        Failure& e = failure[b];
+        if (e.st == HDF_OK || e.memory) {
+          e.st = build(b, s);
+          e.msg = hdf_last_error();
+        }
+        if (e.st != HDF_OK) return hdf::set_error(e.st, "factor of cluster " + std::to_string(c) + ": " + e.msg);
+      }
       hdf::set_product_timing(h->fac[c], false);
     }
   }

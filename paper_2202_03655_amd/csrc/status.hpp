@@ -12,6 +12,9 @@
 namespace hdf {
 hdf_status set_error(hdf_status s, const std::string& msg);
 void clear_error();
+// Whether this thread's last failure was for want of device memory: the same call may succeed when less
+// runs beside it.
+bool failed_for_memory();
 // Switch the HIP events around a factor's products on or off (hdf_info then
 // reports no kernel times for them).  Products on many small factors use off.
 void set_product_timing(hdf_handle h, bool on);

@@ -437,7 +437,12 @@ static long long g_tick = 0;
 
 extern "C" {
 static std::map<uintptr_t, std::pair<void*, size_t>> g_guarded;
+// emu_fail: the n-th following hipMalloc (what = 0) finds no memory, or the n-th copy (1) fails; n = 0: none
+static int g_fail[2] = {0, 0};
+static bool fail_now(int what) { return g_fail[what] > 0 && --g_fail[what] == 0; }
+void emu_fail(int what, int n) { emu::Lock lock; g_fail[what] = n; }
 hipError_t hipMalloc(void** p, size_t b) { emu::Lock lock;
+  if (fail_now(0)) return hipErrorOutOfMemory;
   void* m = nullptr;
   static const bool guard = getenv("EMU_GUARD") != nullptr;
   if (guard) {
@@ -470,6 +475,7 @@ hipError_t hipFree(void* p) { emu::Lock lock;
 static bool dev_dst(hipMemcpyKind k) { return k == hipMemcpyHostToDevice || k == hipMemcpyDeviceToDevice; }
 static bool dev_src(hipMemcpyKind k) { return k == hipMemcpyDeviceToHost || k == hipMemcpyDeviceToDevice; }
 hipError_t hipMemcpyAsync(void* dst, const void* src, size_t b, hipMemcpyKind k, hipStream_t s) { emu::Lock lock;
+  if (fail_now(1)) return hipErrorInvalidValue;
   emu::check_range(dst, b, dev_dst(k), "memcpy dst");
   emu::check_range(src, b, dev_src(k), "memcpy src");
   emu::enqueue(s, [=]() { memcpy(dst, src, b); });

@@ -15,7 +15,7 @@ import torch
 import run_cases as rc
 from run_cases import _raw, check, dense, hdf, rel, to_dev, wl
 
-for _f in ("emu_pending", "emu_frees", "emu_waits", "emu_launching_threads"):
+for _f in ("emu_pending", "emu_frees", "emu_waits", "emu_launching_threads", "emu_launches"):
     getattr(_raw, _f).restype = ctypes.c_longlong
 
 
@@ -107,7 +107,41 @@ def case_krr_lanes():
     check("krr_lanes apply", e <= 1e-6, f"{e:.2e}")
 
 
-CASES = {"krr_lanes": case_krr_lanes, "own_device": case_own_device, "adjoint_map": case_adjoint_map, "krr_create": case_krr_create}
+def _status(make):
+    try:
+        return 0, make()
+    except hdf.HDFError as e:
+        return e.status, str(e)
+
+
+def case_krr_failures():
+    """A block build that fails beside others: for want of memory it is repeated alone, any other failure is reported
+    once, and an infeasible build is not made twice."""
+    _raw.emu_fail(0, 20)                         # construction's own allocations before the builds: 6
+    st, made = _status(_krr)
+    check("krr_failures memory", st == 0, f"status {st}")
+    if st == 0:
+        X, S = made
+        v = wl.rhs(len(X), 1, 32)[:, 0]
+        y = S.apply(to_dev(v, torch.float64))
+        _raw.emu_flush()
+        e = rel(y.numpy(), dense.dense_K(X, "gaussian", 0.8) @ v + 0.1 * v)
+        check("krr_failures memory apply", e <= 1e-6, f"{e:.2e}")
+    _raw.emu_fail(1, 8)                          # and its own copies: 6
+    st, msg = _status(_krr)
+    _raw.emu_fail(1, 0)
+    check("krr_failures copy", st == -6 and "factor of cluster" in str(msg), f"status {st}: {msg}")
+    X = to_dev(wl.unit_ball(90, 3, 31), torch.float64)
+    n0 = _raw.emu_launches()
+    st, _ = _status(lambda: hdf.Factor(X, "gaussian", 1e-3, 1e-6, precision=hdf.HDF_FP64))
+    n1 = _raw.emu_launches()
+    sk, msg = _status(lambda: hdf.KRR(X, to_dev(np.zeros(90, np.int32), torch.int32), 1, "gaussian", 1e-3, 1e-6, 0.1))
+    n2 = _raw.emu_launches()
+    check("krr_failures infeasible", st == sk == -4 and n2 - n1 < 2 * (n1 - n0),
+          f"status {st}, {sk}; {n1 - n0} launches of a build, {n2 - n1} of the construction")
+
+
+CASES = {"krr_failures": case_krr_failures, "krr_lanes": case_krr_lanes, "own_device": case_own_device, "adjoint_map": case_adjoint_map, "krr_create": case_krr_create}
 
 if __name__ == "__main__":
     rc._install()
