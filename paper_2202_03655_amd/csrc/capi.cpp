@@ -77,15 +77,29 @@ void trim(int dev) {
     }
   }
 }
+// hipMalloc on the current device; short of memory, after the device's cached blocks are released
+hipError_t fresh(void** p, size_t b) {
+  hipError_t e = hipMalloc(p, b);
+  int dev = 0;
+  if (e == hipErrorOutOfMemory && HDF_ALLOC_CACHE && hipGetDevice(&dev) == hipSuccess) {
+    (void)hipGetLastError();
+    trim(dev);
+    e = hipMalloc(p, b);
+  }
+  if (e != hipSuccess) {
+    (void)hipGetLastError();
+    *p = nullptr;
+  }
+  return e;
+}
 hipError_t alloc(void** p, size_t b, size_t* got, int* dev_out) {
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return e;
   if (!HDF_ALLOC_CACHE) {
-    e = hipMalloc(p, b);
+    e = fresh(p, b);
     *got = e == hipSuccess ? b : 0;
     *dev_out = dev;
-    if (e != hipSuccess) *p = nullptr;
     return e;
   }
   const size_t want = size_class(b);
@@ -101,17 +115,8 @@ hipError_t alloc(void** p, size_t b, size_t* got, int* dev_out) {
       return hipSuccess;
     }
   }
-  e = hipMalloc(p, want);
-  if (e == hipErrorOutOfMemory) {
-    (void)hipGetLastError();
-    trim(dev);
-    e = hipMalloc(p, want);
-  }
-  if (e != hipSuccess) {
-    (void)hipGetLastError();
-    *p = nullptr;
-    return e;
-  }
+  e = fresh(p, want);
+  if (e != hipSuccess) return e;
   *got = want;
   *dev_out = dev;
   return hipSuccess;
@@ -189,6 +194,7 @@ hipError_t wait_device(int dev) {
   const hipError_t back = hipSetDevice(cur);
   return e != hipSuccess ? e : back;
 }
+hipError_t device_alloc(void** p, size_t b) { return pool::fresh(p, b); }
 hipError_t pool_alloc(void** p, size_t b, size_t* got, int* dev) { return pool::alloc(p, b, got, dev); }
 void pool_release(void* p, size_t bytes, int dev) { pool::release(p, bytes, dev); }
 }  // namespace hdf

@@ -22,6 +22,8 @@ void set_product_timing(hdf_handle h, bool on);
 hipError_t wait_device(int dev);
 // The library's caching device allocator: a block of at least b bytes, its size and device; a block is
 // given back only when no enqueued work can use it.
+// device_alloc is hipMalloc on the current device, tried again without the cache where memory is short.
+hipError_t device_alloc(void** p, size_t b);
 hipError_t pool_alloc(void** p, size_t b, size_t* got, int* dev);
 void pool_release(void* p, size_t bytes, int dev);
 // Products of several stored binary64 factors with one right-hand side each: the entries
