@@ -1680,14 +1680,18 @@ static hdf_status pass1_narrow(hdf_handle h, int side, const void* V, int64_t m,
 // Wavefronts below which the narrow pass 2 splits the harmonic rows, and at which its shares aim.
 constexpr int64_t kNarrowWaves = 4096;
 
+// Harmonic rows per share of the narrow pass 2, 0 for no split; `most` bytes are there for the shares.
+static int narrow_share_rows(hdf_handle h, int64_t m, int64_t most) {
+  const int64_t step = 64 * 16 / h->felem(), waves = (h->N + step - 1) / step;
+  if (waves >= kNarrowWaves / 2) return 0;
+  int64_t want = std::min<int64_t>((kNarrowWaves + waves - 1) / waves, (h->H + 7) / 8);
+  want = std::min<int64_t>(want, most / (int64_t)(h->N * m * h->felem()));
+  return want > 1 ? (int)((h->H + want - 1) / want) : 0;
+}
+
 // Pass 2 of a narrow product.
 static hdf_status pass2_narrow(hdf_handle h, int64_t m, void* KV, int64_t ldkv, hipStream_t s) {
-  const int64_t step = 64 * 16 / h->felem(), waves = (h->N + step - 1) / step;
-  int z_rows = 0;
-  if (waves < kNarrowWaves / 2) {
-    const int64_t want = std::min<int64_t>((kNarrowWaves + waves - 1) / waves, (h->H + 7) / 8);
-    if (want > 1) z_rows = (int)((h->H + want - 1) / want);
-  }
+  const int z_rows = narrow_share_rows(h, m, INT64_MAX);
   if (z_rows > 0) HIPCHK(h->ws_n.ensure((size_t)((h->H + z_rows - 1) / z_rows) * h->N * m * h->felem()));
   HIPCHK(hdf::launch_narrow_n(h->phi.p, h->ldN, h->q.p, h->ldN, (const hdf::DegDev*)h->degs_dev.p,
                               (int)h->degs.size(), h->ws_Wd.p, KV, ldkv, h->N, (int)m, (int)h->H, z_rows, h->ws_n.p,
@@ -1858,8 +1862,10 @@ hdf_status hdf_matvec_noalloc(hdf_handle h, const void* V, int64_t m, int64_t ld
                                 side ? h->ldN2 : h->ldN, (const hdf::DegDev*)h->degs_dev.p, nd, items, n_splits,
                                 split_len, V, ldv, n1, (int)m, h->r, (const double*)h->lam_row.p, base, nullptr, 1,
                                 (double*)((char*)base + wn_bytes), h->fprec, h->dtype, s));
+    // the partials are summed: their memory takes the shares of pass 2
+    const int z_rows = narrow_share_rows(h, m, (int64_t)hdf::kScratchBytes - wn_bytes);
     HIPCHK(hdf::launch_narrow_n(h->phi.p, h->ldN, h->q.p, h->ldN, (const hdf::DegDev*)h->degs_dev.p, nd, base, KV, ldkv,
-                                h->N, (int)m, (int)h->H, 0, nullptr, h->fprec, h->dtype, s));
+                                h->N, (int)m, (int)h->H, z_rows, (char*)base + wn_bytes, h->fprec, h->dtype, s));
     return HDF_OK;
   }
   tile_splits(n1, h->n_tgroups[cpl], per_split, &n_splits, &split_len);

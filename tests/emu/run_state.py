@@ -141,7 +141,28 @@ def case_krr_failures():
           f"status {st}, {sk}; {n1 - n0} launches of a build, {n2 - n1} of the construction")
 
 
-CASES = {"krr_failures": case_krr_failures, "krr_lanes": case_krr_lanes, "own_device": case_own_device, "adjoint_map": case_adjoint_map, "krr_create": case_krr_create}
+def case_noalloc_shares():
+    """hdf_matvec_noalloc splits pass 2 of few points and few right-hand sides as hdf_matvec does, the shares in its
+    fixed scratch (one launch more than without a split), and both give the same bits."""
+    n = 700
+    f = hdf.Factor(to_dev(wl.unit_ball(n, 4, 36), torch.float64), "gaussian", 1.0, 1e-4, precision=hdf.HDF_FP64)
+    for m in (1, 4):
+        V, out = to_dev(wl.rhs(n, m, 37), torch.float64), rc.dev_empty((n, m), torch.float64)
+        counts = []
+        def noalloc():
+            assert hdf.lib().hdf_matvec_noalloc(f._h, V.data_ptr(), m, m, out.data_ptr(), m, None) == 0
+            return out
+        for run in (lambda: f.matvec(V), noalloc):
+            _raw.emu_flush()
+            before = _raw.emu_launches()
+            ref = run()
+            _raw.emu_flush()
+            counts.append((_raw.emu_launches() - before, ref.numpy().copy()))
+        check(f"noalloc_shares m={m}", counts[0][0] == counts[1][0] and np.array_equal(counts[0][1], counts[1][1]),
+              f"{counts[0][0]} and {counts[1][0]} launches")
+
+
+CASES = {"noalloc_shares": case_noalloc_shares, "krr_failures": case_krr_failures, "krr_lanes": case_krr_lanes, "own_device": case_own_device, "adjoint_map": case_adjoint_map, "krr_create": case_krr_create}
 
 if __name__ == "__main__":
     rc._install()

@@ -33,6 +33,7 @@ def _run(lib, case):
     assert r.returncode == 0 and "ok  " in r.stdout and "FAIL" not in r.stdout, r.stdout[-4000:] + r.stderr[-4000:]
 
 
-@pytest.mark.parametrize("case", ["krr_create", "adjoint_map", "own_device", "krr_lanes", "krr_failures"])
+@pytest.mark.parametrize("case", ["krr_create", "adjoint_map", "own_device", "krr_lanes", "krr_failures",
+                                  "noalloc_shares"])
 def test_state_after_calls(emu_lib, case):
     _run(emu_lib, case)
