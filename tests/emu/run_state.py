@@ -162,7 +162,23 @@ def case_noalloc_shares():
               f"{counts[0][0]} and {counts[1][0]} launches")
 
 
-CASES = {"noalloc_shares": case_noalloc_shares, "krr_failures": case_krr_failures, "krr_lanes": case_krr_lanes, "own_device": case_own_device, "adjoint_map": case_adjoint_map, "krr_create": case_krr_create}
+def case_narrow_splits():
+    """Pass 1 of a narrow product of a thousand binary32 points runs in two splits (one launch more, their sum)."""
+    for n, launches in ((511, 3), (1100, 4)):
+        X = wl.unit_ball(n, 3, 38).astype(np.float32)
+        f = hdf.Factor(to_dev(X, torch.float32), "gaussian", 1.0, 1e-3, precision=hdf.HDF_MIXED)
+        V = wl.rhs(n, 4, 39).astype(np.float32)
+        Vd = to_dev(V, torch.float32)
+        _raw.emu_flush()
+        before = _raw.emu_launches()
+        y = f.matvec(Vd)
+        _raw.emu_flush()
+        count = _raw.emu_launches() - before
+        e = rel(y.numpy().astype(np.float64), rc.ohdf.matvec(rc.ohdf.build(X.astype(np.float64), "gaussian", 1.0, 1e-3), V))
+        check(f"narrow_splits n={n}", count == launches and e <= 1e-5, f"{count} launches, {e:.2e}")
+
+
+CASES = {"narrow_splits": case_narrow_splits, "noalloc_shares": case_noalloc_shares, "krr_failures": case_krr_failures, "krr_lanes": case_krr_lanes, "own_device": case_own_device, "adjoint_map": case_adjoint_map, "krr_create": case_krr_create}
 
 if __name__ == "__main__":
     rc._install()
