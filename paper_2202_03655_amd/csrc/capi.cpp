@@ -265,6 +265,7 @@ struct hdf_factor {
   std::vector<std::vector<char>> host_keep;
   // host copies of the pass-1 tables: they outlive their asynchronous uploads
   // matvec / adjoint workspace
+  bool products_reserved = false;                 // see reserve_products
   DevBuf ws_part, ws_Wd, ws_Wb, ws_n, bw_GV, bw_GW, bw_VW;
   DevBuf cphi, cq;                                // matrix-free chunk scratch
   // adjoint (dF/dX by contractions): the loop-order row table, q' = dq/d(rho^2) rows and their
@@ -1488,10 +1489,11 @@ static const hdf::MvtGroup* tile_groups(hdf_handle h, int cpl) {
 }
 
 // Splits of the tile-major pass 1 over n points: about 1024 workgroups (of G groups each; two run
-// at once on a CU), splits a multiple of 128 points, partial records capped at about 96 MB.
+// at once on a CU), splits a multiple of 128 points, partial records capped at kPartialBytes.
+constexpr int64_t kPartialBytes = 96000000;
 static void tile_splits(int64_t n, int n_groups, size_t per_split, int* n_splits, int64_t* split_len) {
   int64_t ns = std::max<int64_t>(1, 1024 / std::max(1, n_groups));
-  ns = std::min<int64_t>(ns, std::max<int64_t>(1, (int64_t)(96e6 / (double)per_split)));
+  ns = std::min<int64_t>(ns, std::max<int64_t>(1, kPartialBytes / (int64_t)per_split));
   ns = std::min<int64_t>(ns, (n + 127) / 128);
   ns = std::max<int64_t>(ns, 1);
   int64_t len = (n + ns - 1) / ns;
@@ -1657,7 +1659,7 @@ static hdf_status pass1_narrow(hdf_handle h, int side, const void* V, int64_t m,
   const int64_t per_split = h->r * m * (int64_t)sizeof(double);
   int n_splits;
   int64_t split_len;
-  hdf::narrow_splits(n, items, h->fprec, per_split, (int64_t)96e6, &n_splits, &split_len);
+  hdf::narrow_splits(n, items, h->fprec, per_split, kPartialBytes, &n_splits, &split_len);
   if (n_splits > 1) HIPCHK(h->ws_part.ensure((size_t)per_split * n_splits));
   if (out.W) HIPCHK(out.W->ensure((size_t)h->r * m16 * sizeof(double)));
   if (out.Wn) HIPCHK(out.Wn->ensure((size_t)h->r * m * h->felem()));
@@ -1696,6 +1698,34 @@ static hdf_status pass2_narrow(hdf_handle h, int64_t m, void* KV, int64_t ldkv, 
   HIPCHK(hdf::launch_narrow_n(h->phi.p, h->ldN, h->q.p, h->ldN, (const hdf::DegDev*)h->degs_dev.p,
                               (int)h->degs.size(), h->ws_Wd.p, KV, ldkv, h->N, (int)m, (int)h->H, z_rows, h->ws_n.p,
                               h->fprec, h->dtype, s));
+  return HDF_OK;
+}
+
+// The work buffers of a stored factor's products of up to 16 right-hand sides, those of the narrow passes and
+// of the matrix-core passes together: a program that has made one product makes any other of these without an
+// allocation (under graph capture, say), as if one kind of pass served them all.  The shares of a matrix-core
+// pass 2 of few points are allocated by it.
+static hdf_status reserve_products(hdf_handle h) {
+  if (h->products_reserved) return HDF_OK;
+  const int64_t n1 = h->cross ? h->N2 : h->N;
+  const size_t per16 = (size_t)h->r * 16 * sizeof(double);
+  int n_splits;
+  int64_t split_len;
+  tile_splits(n1, h->n_tgroups[1], per16, &n_splits, &split_len);
+  size_t part = per16 * n_splits, shares = 0;
+  for (int m = 1; m <= hdf::kNwMax; ++m) {
+    const int items = hdf::narrow_items(h->degs.data(), (int)h->degs.size(), h->fprec, m);
+    const int64_t per = h->r * m * (int64_t)sizeof(double);
+    hdf::narrow_splits(n1, items, h->fprec, per, kPartialBytes, &n_splits, &split_len);
+    part = std::max(part, (size_t)per * n_splits);
+    const int z_rows = narrow_share_rows(h, m, INT64_MAX);
+    if (z_rows > 0) shares = std::max(shares, (size_t)((h->H + z_rows - 1) / z_rows) * h->N * m * h->felem());
+  }
+  HIPCHK(h->ws_part.ensure(part));
+  HIPCHK(h->ws_Wd.ensure((size_t)h->r * hdf::kNwMax * h->felem()));
+  HIPCHK(h->ws_Wb.ensure((size_t)h->n_wblocks * 16 * 16 * h->felem()));
+  if (shares > 0) HIPCHK(h->ws_n.ensure(shares));
+  h->products_reserved = true;
   return HDF_OK;
 }
 
@@ -1746,7 +1776,7 @@ static hdf_status pass2(hdf_handle h, const void* phi, const void* q, int64_t ld
   }
   if (z_blocks > 0) {
     const int64_t nz = (h->n_wblocks + z_blocks - 1) / z_blocks;
-    HIPCHK(h->ws_n.ensure((size_t)nz * n * m * h->felem()));
+    HIPCHK(h->ws_n.ensure((size_t)nz * n * m16 * h->felem()));   // of every m up to m16
   }
   HIPCHK(hdf::launch_matvec_n(phi, ld, q, ld, (const hdf::DegDev*)h->degs_dev.p, (int)h->degs.size(), h->ws_Wb.p,
                               h->n_wblocks, m16, KV, ldkv, n, (int)m, h->fprec, h->dtype, z_blocks, h->ws_n.p, s));
@@ -1763,6 +1793,10 @@ static hdf_status matvec_impl(hdf_handle h, const void* V, int64_t m, int64_t ld
   }
   const int m16 = (int)((m + 15) / 16 * 16);
   const bool timed = h->time_products;
+  if (h->storage == HDF_STORE_FACTOR) {
+    const hdf_status rst = reserve_products(h);
+    if (rst != HDF_OK) return rst;
+  }
   PassOut po;
   if (narrow(h, m)) po.Wn = &h->ws_Wd;
   else if (h->mf_fused) po.Wd = &h->ws_Wd;
@@ -2394,7 +2428,7 @@ hdf_status batch_create(const std::vector<hdf_handle>& factors, const std::vecto
     f.lam = (const double*)h->lam_row.p;
     f.n_items = narrow_items(h->degs.data(), f.n_deg, 0, 1);
     // the launches of all factors together aim at what one factor's aim at alone
-    narrow_splits(f.n, f.n_items * live, 0, f.rank * 8, (int64_t)96e6 / live, &f.n_splits, &f.split_len);
+    narrow_splits(f.n, f.n_items * live, 0, f.rank * 8, kPartialBytes / live, &f.n_splits, &f.split_len);
     const int64_t waves = (f.n + 127) / 128;
     const int64_t want = std::min<int64_t>(std::max<int64_t>(1, kNarrowWaves / (waves * live)), (h->H + 7) / 8);
     f.z_rows = (int)((h->H + want - 1) / want);

@@ -441,7 +441,9 @@ static std::map<uintptr_t, std::pair<void*, size_t>> g_guarded;
 static int g_fail[2] = {0, 0};
 static bool fail_now(int what) { return g_fail[what] > 0 && --g_fail[what] == 0; }
 void emu_fail(int what, int n) { emu::Lock lock; g_fail[what] = n; }
+static long long g_mallocs = 0;
 hipError_t hipMalloc(void** p, size_t b) { emu::Lock lock;
+  ++g_mallocs;
   if (fail_now(0)) return hipErrorOutOfMemory;
   void* m = nullptr;
   static const bool guard = getenv("EMU_GUARD") != nullptr;
@@ -549,6 +551,7 @@ hipError_t hipGetLastError() { emu::Lock lock; hipError_t e = emu::g_last; emu::
 const char* hipGetErrorString(hipError_t e) { return e ? "emulated error" : "no error"; }
 void emu_flush() { emu::Lock lock; emu::flush(); }
 // operations enqueued and not yet run: what a caller would find pending on its streams
+long long emu_mallocs() { emu::Lock lock; return g_mallocs; }
 long long emu_frees() { emu::Lock lock; return g_frees; }
 long long emu_pending() { emu::Lock lock; return (long long)emu::q.size(); }
 void emu_register(void* p, size_t n) { emu::Lock lock; emu::user_regions[(uintptr_t)p] = n; }

@@ -15,7 +15,7 @@ import torch
 import run_cases as rc
 from run_cases import _raw, check, dense, hdf, rel, to_dev, wl
 
-for _f in ("emu_pending", "emu_frees", "emu_waits", "emu_launching_threads", "emu_launches"):
+for _f in ("emu_pending", "emu_mallocs", "emu_frees", "emu_waits", "emu_launching_threads", "emu_launches"):
     getattr(_raw, _f).restype = ctypes.c_longlong
 
 
@@ -178,7 +178,24 @@ def case_narrow_splits():
         check(f"narrow_splits n={n}", count == launches and e <= 1e-5, f"{count} launches, {e:.2e}")
 
 
-CASES = {"narrow_splits": case_narrow_splits, "noalloc_shares": case_noalloc_shares, "krr_failures": case_krr_failures, "krr_lanes": case_krr_lanes, "own_device": case_own_device, "adjoint_map": case_adjoint_map, "krr_create": case_krr_create}
+def case_product_buffers():
+    """After one product of a stored factor, others allocate nothing: any of up to 16 right-hand sides with many points,
+    those of no more right-hand sides with few (whose pass 2 is split), and those of the same 16 columns."""
+    few, many = range(1, 17), (1, 2, 3, 4, 5, 16)
+    for n, tol, first, then in ((700, 1e-4, 16, few), (700, 1e-4, 8, range(1, 9)), (700, 1e-4, 4, range(1, 5)),
+                                (66_000, 0.3, 1, many), (66_000, 0.3, 5, many), (50_000, 0.3, 20, (32, 17, 16, 3))):
+        f = _ball_factor(1.0, tol, n)
+        V = wl.rhs(n, max(first, *then), 40)
+        f.matvec(to_dev(V[:, :first], torch.float64))
+        before = _raw.emu_mallocs()
+        for m in then:
+            f.matvec(to_dev(V[:, :m], torch.float64))
+        more = _raw.emu_mallocs() - before
+        check(f"product_buffers n={n} first {first}", more == 0, f"{more} allocations by the products of {list(then)}")
+        _raw.emu_flush()
+
+
+CASES = {"product_buffers": case_product_buffers, "narrow_splits": case_narrow_splits, "noalloc_shares": case_noalloc_shares, "krr_failures": case_krr_failures, "krr_lanes": case_krr_lanes, "own_device": case_own_device, "adjoint_map": case_adjoint_map, "krr_create": case_krr_create}
 
 if __name__ == "__main__":
     rc._install()
