@@ -2046,9 +2046,11 @@ static hdf_status adjoint_dx(hdf_handle h, const double* gv, const double* gw, i
   const int c2s = nw ? m2 : (m2 + 15) / 16 * 16, css = (md2 + 15) / 16 * 16;
   const int64_t c2_rows = nw ? h->r : h->n_wblocks * 16;
   HIPCHK(h->adj_c2.ensure((size_t)c2_rows * c2s * fel));
-  HIPCHK(h->adj_cs.ensure((size_t)std::max<int64_t>(h->shift_blocks, 1) * 16 * css * fel));
   HIPCHK(h->adj_kv2.ensure((size_t)h->N * m2 * fel));
-  HIPCHK(h->adj_kvs.ensure((size_t)h->N * md2 * fel));
+  if (Kh >= 1) {
+    HIPCHK(h->adj_cs.ensure((size_t)h->shift_blocks * 16 * css * fel));
+    HIPCHK(h->adj_kvs.ensure((size_t)h->N * md2 * fel));
+  }
   if (!h->ev_adj[0])
     for (auto& e : h->ev_adj) HIPCHK(hipEventCreate(&e));
   HIPCHK(hipEventRecord(h->ev_adj[0], s));
@@ -2066,14 +2068,12 @@ static hdf_status adjoint_dx(hdf_handle h, const double* gv, const double* gw, i
     HIPCHK(hdf::launch_matvec_n(h->phi.p, h->ldN, h->dq.p, h->ldN, (const hdf::DegDev*)h->degs_dev.p,
                                 (int)h->degs.size(), h->adj_c2.p, h->n_wblocks, c2s, h->adj_kv2.p, m2, h->N, m2,
                                 h->fprec, io, 0, nullptr, s));
-  if (Kh >= 1) {
+  if (Kh >= 1)
     HIPCHK(hdf::launch_matvec_n(h->phi.p, h->ldN, h->q.p, h->ldN, (const hdf::DegDev*)h->adj_degs.p, Kh, h->adj_cs.p,
                                 h->shift_blocks, css, h->adj_kvs.p, md2, h->N, md2, h->fprec, io, 0, nullptr, s));
-  } else {
-    HIPCHK(hipMemset2DAsync(h->adj_kvs.p, md2 * fel, 0, md2 * fel, h->N, s));   // degree 0 only: no derivative
-  }
   HIPCHK(hdf::launch_adj_combine(h->x_soa.p, h->dtype, h->ldN, h->N, d, (const hdf::GeoDev*)h->geo_dev.p,
-                                 h->adj_kvs.p, md2, h->adj_kv2.p, m2, Wm, Vm, ld, m, dX, lddx, h->fprec, s));
+                                 Kh >= 1 ? h->adj_kvs.p : nullptr, md2, h->adj_kv2.p, m2, Wm, Vm, ld, m, dX, lddx,
+                                 h->fprec, s));
   HIPCHK(hipEventRecord(h->ev_adj[1], s));
   h->adj_timed = true;
   return HDF_OK;

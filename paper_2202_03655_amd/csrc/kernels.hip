@@ -1087,7 +1087,7 @@ hipError_t launch_radial(const void* x_soa, int dtype, int64_t ldx, int64_t n, i
 
 // dX[i][j] = (1/R) [ sum_c w_ic KS[i][j 2m + c] + v_ic KS[i][j 2m + m + c]
 //                    + 2 xt_ij (sum_c w_ic K2[i][c] + v_ic K2[i][m + c]) ]
-// KS: n x ldks (the shifted-factor products, 2m columns per direction), K2: n x ldk2.
+// KS: n x ldks (the shifted-factor products, 2m columns per direction; null: zeros), K2: n x ldk2.
 template <typename Tin, typename T, typename TIO>
 __global__ void __launch_bounds__(256) k_adj_combine(const Tin* __restrict__ x_soa, int64_t ldx, int64_t n, int d,
                                                       const GeoDev* __restrict__ geo, const T* __restrict__ KS,
@@ -1102,8 +1102,9 @@ __global__ void __launch_bounds__(256) k_adj_combine(const Tin* __restrict__ x_s
     s2 += (double)Wm[i * ld + c] * (double)K2[i * ldk2 + c] + (double)Vm[i * ld + c] * (double)K2[i * ldk2 + m + c];
   for (int j = 0; j < d; ++j) {
     double sj = 0.0;
-    const T* ks = KS + i * ldks + (int64_t)j * 2 * m;
-    for (int c = 0; c < m; ++c) sj += (double)Wm[i * ld + c] * (double)ks[c] + (double)Vm[i * ld + c] * (double)ks[m + c];
+    const T* ks = KS ? KS + i * ldks + (int64_t)j * 2 * m : nullptr;
+    for (int c = 0; c < m; ++c)
+      sj += (double)Wm[i * ld + c] * (ks ? (double)ks[c] : 0.0) + (double)Vm[i * ld + c] * (ks ? (double)ks[m + c] : 0.0);
     const double xt = ((double)x_soa[(int64_t)j * ldx + i] - geo->c[j]) / Reff;
     dX[i * lddx + j] = (TIO)((sj + 2.0 * xt * s2) / Reff);
   }

@@ -201,7 +201,7 @@ hipError_t launch_adj_coefficients(const double* gv, const double* gw, int64_t g
 // coef[q_off[row] + a] T_a(t_i), a < q_len[row] (rows padded: the launch
 // writes up to the next multiple of 2 or 4 points past n).  launch_adj_combine
 // forms dX[i][j] = (1/R) [sum_c w_ic KS[i][2mj + c] + v_ic KS[i][2mj + m + c]
-// + 2 xt_ij (sum_c w_ic K2[i][c] + v_ic K2[i][m + c])].  prec: factor type
+// + 2 xt_ij (sum_c w_ic K2[i][c] + v_ic K2[i][m + c])], KS zeros if NULL.  prec: factor type
 // (1 binary32, 0 binary64); dtype: points, W, V and dX (0 float32, 1 float64).
 hipError_t launch_radial(const void* x_soa, int dtype, int64_t ldx, int64_t n, int d, const GeoDev* geo,
                          double u0, double u1, const int32_t* q_len, const int32_t* q_off, const void* coef,

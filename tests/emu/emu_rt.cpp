@@ -495,14 +495,16 @@ hipError_t hipMemcpy2DAsync(void* dst, size_t dp, const void* src, size_t sp, si
   });
   return hipSuccess;
 }
-hipError_t hipMemset2DAsync(void* dst, size_t pitch, int v, size_t w, size_t h, hipStream_t s) { emu::Lock lock;
+static long long g_memsets = 0;
+long long emu_memsets() { emu::Lock lock; return g_memsets; }
+hipError_t hipMemset2DAsync(void* dst, size_t pitch, int v, size_t w, size_t h, hipStream_t s) { emu::Lock lock; ++g_memsets;
   if (h) emu::check_range(dst, pitch * (h - 1) + w, true, "memset2D");
   emu::enqueue(s, [=]() {
     for (size_t r = 0; r < h; ++r) memset((char*)dst + r * pitch, v, w);
   });
   return hipSuccess;
 }
-hipError_t hipMemsetAsync(void* dst, int v, size_t b, hipStream_t s) { emu::Lock lock;
+hipError_t hipMemsetAsync(void* dst, int v, size_t b, hipStream_t s) { emu::Lock lock; ++g_memsets;
   emu::check_range(dst, b, true, "memset");
   emu::enqueue(s, [=]() { memset(dst, v, b); });
   return hipSuccess;

@@ -15,7 +15,7 @@ import torch
 import run_cases as rc
 from run_cases import _raw, check, dense, hdf, rel, to_dev, wl
 
-for _f in ("emu_pending", "emu_mallocs", "emu_frees", "emu_waits", "emu_launching_threads", "emu_launches"):
+for _f in ("emu_pending", "emu_mallocs", "emu_frees", "emu_waits", "emu_launching_threads", "emu_launches", "emu_memsets"):
     getattr(_raw, _f).restype = ctypes.c_longlong
 
 
@@ -195,7 +195,23 @@ def case_product_buffers():
         _raw.emu_flush()
 
 
-CASES = {"product_buffers": case_product_buffers, "narrow_splits": case_narrow_splits, "noalloc_shares": case_noalloc_shares, "krr_failures": case_krr_failures, "krr_lanes": case_krr_lanes, "own_device": case_own_device, "adjoint_map": case_adjoint_map, "krr_create": case_krr_create}
+def case_adjoint_degree0():
+    """dF/dX of a factor of degree 0 alone: no memset nodes in what may be captured, and the oracle's gradient."""
+    n = 40
+    X = wl.unit_ball(n, 3, 41)
+    f = hdf.Factor(to_dev(X, torch.float64), "gaussian", 50.0, 0.5, precision=hdf.HDF_FP64)
+    W, V = wl.rhs(n, 3, 42), wl.rhs(n, 3, 43)
+    _raw.emu_flush()
+    before = _raw.emu_memsets()
+    g = f.backward(to_dev(W, torch.float64), to_dev(V, torch.float64), need_l=False)[1]
+    _raw.emu_flush()
+    sets = _raw.emu_memsets() - before
+    st = rc.ohdf.build(X, "gaussian", 50.0, 0.5)
+    e = rel(g.numpy(), rc.ohdf.grad_x(st, W, V))
+    check("adjoint_degree0", _degree(f) == 0 and sets == 0 and e <= 1e-10, f"s_k {f.info()['s_k']}, {sets} memsets, {e:.2e}")
+
+
+CASES = {"adjoint_degree0": case_adjoint_degree0, "product_buffers": case_product_buffers, "narrow_splits": case_narrow_splits, "noalloc_shares": case_noalloc_shares, "krr_failures": case_krr_failures, "krr_lanes": case_krr_lanes, "own_device": case_own_device, "adjoint_map": case_adjoint_map, "krr_create": case_krr_create}
 
 if __name__ == "__main__":
     rc._install()
