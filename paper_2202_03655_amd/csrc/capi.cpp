@@ -254,7 +254,7 @@ struct hdf_factor {
   // tables of the factor evaluation (in build_tabs) and of the products (in prod_tabs), each
   // set uploaded in one copy
   DevBuf build_tabs, prod_tabs;
-  DevView col_of, chain, q_len, q_off, q_coef, leaves, degs_dev, lam_row, blk_src, tile_tabs, degs_by_k;
+  DevView col_of, chain, q_len, q_off, q_coef, leaves, degs_dev, lam_row, blk_src, tile_tabs;
   // tile-major pass 1 (m16 <= 64): wave items and their workgroup groups for each cpl = m16 / 16
   // in 1..4, built with the factor; tile_tabs holds all wave items, then all groups, then the
   // rank-row table
@@ -263,7 +263,6 @@ struct hdf_factor {
   size_t rr_base = 0;                             // byte offset of the rank-row table in tile_tabs
   // host copies of uploaded build tables: they outlive their asynchronous uploads
   std::vector<std::vector<char>> host_keep;
-  // host copies of the pass-1 tables: they outlive their asynchronous uploads
   // matvec / adjoint workspace
   bool products_reserved = false;                 // see reserve_products
   DevBuf ws_part, ws_Wd, ws_Wb, ws_n, bw_GV, bw_GW, bw_VW;
@@ -274,7 +273,7 @@ struct hdf_factor {
   std::vector<int32_t> col_of_host;
   DevBuf dq, dq_coef, adj_degs, adj_c2, adj_cs, adj_kv2, adj_kvs;
   std::vector<hdf::DegDev> adj_degs_host;
-  int64_t r_shift = 0, shift_blocks = 0;
+  int64_t shift_blocks = 0;
   std::vector<char> dq_coef_host;                 // outlives its upload
   std::shared_ptr<struct AdjMap> adj_map;
   hdf::BuildTables tables{};
@@ -350,10 +349,6 @@ void loop_order_columns(int d, int K, const std::unordered_map<uint64_t, int>& c
 
 }  // namespace
 
-// Kept degrees, harmonic tables, memory budget and the factor evaluation,
-// common to the symmetric and the general (X != Y) build.  A general factor
-// evaluates its Y side too, with the Y-side radial coefficients; its diagonal
-// is the identity (sqrt of the singular values is folded into both sides).
 // Wave items of the tile-major pass 1 for cpl = m16 / 16 (1..4): one per 16 harmonics of a kept
 // degree and range of its radial functions (nl * nct accumulator tiles at most), then groups of up
 // to kMvtWavesPerGroup items whose radial rows span at most kMvtMaxNq rows.
@@ -714,6 +709,10 @@ static bool mf_tables(hdf_factor* f, const std::vector<int32_t>& col_of, std::ve
   return true;
 }
 
+// Kept degrees, harmonic tables, memory budget and the factor evaluation,
+// common to the symmetric and the general (X != Y) build.  A general factor
+// evaluates its Y side too, with the Y-side radial coefficients; its diagonal
+// is the identity (sqrt of the singular values is folded into both sides).
 static hdf_status finish_build(hdf_factor* f, double t0, hipStream_t s) {
   struct FinishTimer {
     hdf_factor* f;
@@ -950,15 +949,11 @@ static hdf_status finish_build(hdf_factor* f, double t0, hipStream_t s) {
         for (int h0 = 0; h0 < dg.nh; h0 += 16)
           for (int l = 0; l < dg.s; ++l)
             for (int hh = h0; hh < h0 + 16; ++hh) src.push_back(hh < dg.nh ? dg.roff + hh * dg.s + l : -1);
-      std::vector<hdf::DegDev> dbk(K + 1);
-      for (int k = 0; k <= K; ++k) { dbk[k] = hdf::DegDev{}; }
-      for (size_t di = 0; di < f->degs.size(); ++di) dbk[f->kept_k[di]] = f->degs[di];
       Batch bp;
       bp.add(f->degs_dev, f->degs.data(), f->degs.size() * sizeof(hdf::DegDev));
       bp.add(f->tile_tabs, tabs.data(), tabs.size());
       bp.add(f->lam_row, lr.data(), lr.size() * 8);
       bp.add(f->blk_src, src.data(), src.size() * 4);
-      bp.add(f->degs_by_k, dbk.data(), dbk.size() * sizeof(hdf::DegDev));
       HIPCHK(upload_batch(f->prod_tabs, bp));
       return HDF_OK;
     };
@@ -1440,8 +1435,6 @@ hdf_status hdf_build_cross(const void* x, int64_t nx, int64_t ldx, const void* y
 }
 
 // ------------------------------------------------------------------ matvec
-// Pass 1 (W = U^T V, binary64) and the scaled copy Wd = D W for pass 2.
-// side 0: the factor's (X) rows; side 1: the Y rows of a general factor.
 // Matrix-free factor: evaluate the harmonics and radial functions of points [c0, c0 + nc) into the
 // chunk scratch.
 static hdf_status eval_chunk(hdf_handle h, int64_t c0, int64_t nc, hipStream_t s) {
@@ -1729,6 +1722,8 @@ static hdf_status reserve_products(hdf_handle h) {
   return HDF_OK;
 }
 
+// Pass 1: the wanted sums W = U^T V and scaled copies D W.  side 0: the factor's (X) rows; side 1: the Y rows
+// of a general factor.
 static hdf_status pass1(hdf_handle h, int side, const void* V, int64_t m, int64_t ldv, int m16, const PassOut& out,
                         hipStream_t s, bool timed) {
   if (h->storage == HDF_STORE_NONE)
@@ -2008,7 +2003,6 @@ static hdf_status adjoint_dx(hdf_handle h, const double* gv, const double* gw, i
       roff += (int64_t)d1.nh * dg.s;
       boff += (int64_t)(d1.nh + 15) / 16 * dg.s;
     }
-    h->r_shift = roff;
     h->shift_blocks = boff;
     HIPCHK(h->adj_degs.ensure(h->adj_degs_host.size() * sizeof(hdf::DegDev)));
     HIPCHK(hipMemcpyAsync(h->adj_degs.p, h->adj_degs_host.data(), h->adj_degs_host.size() * sizeof(hdf::DegDev),

@@ -255,13 +255,6 @@ __global__ __launch_bounds__(256) void k_kmv_finish(const double* __restrict__ p
   }
 }
 
-__global__ __launch_bounds__(256) void k_pack_rows(const double* __restrict__ x, int64_t n, int d, int64_t ld,
-                                                   double* __restrict__ out) {
-  const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (e >= n * d) return;
-  out[e] = x[(e / d) * ld + e % d];
-}
-
 __global__ __launch_bounds__(256) void k_gather(const double* __restrict__ v, const int32_t* __restrict__ perm,
                                                 int64_t n, double* __restrict__ out) {
   const int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x;
@@ -758,11 +751,6 @@ int kmv_finish_blocks(int64_t n) { return (int)std::max<int64_t>(1, (n + 63) / 6
 hipError_t launch_kmv_finish(const double* part, int splits, int64_t n, const double* base, const double* v,
                              double lam, double* out, double* part_dot, hipStream_t s) {
   k_kmv_finish<<<(unsigned)kmv_finish_blocks(n), 256, 0, s>>>(part, splits, n, base, v, lam, out, part_dot);
-  return hipGetLastError();
-}
-
-hipError_t launch_pack_rows(const double* x, int64_t n, int d, int64_t ld, double* out, hipStream_t s) {
-  k_pack_rows<<<blocks_for(n * d), 256, 0, s>>>(x, n, d, ld, out);
   return hipGetLastError();
 }
 

@@ -46,8 +46,6 @@ hipError_t launch_kmv(const double* x, int64_t ldx, int64_t nx, const double* y,
 int kmv_finish_blocks(int64_t n);
 hipError_t launch_kmv_finish(const double* part, int splits, int64_t n, const double* base, const double* v,
                              double lam, double* out, double* part_dot, hipStream_t s);
-// contiguous n x d copy of a strided array
-hipError_t launch_pack_rows(const double* x, int64_t n, int d, int64_t ld, double* out, hipStream_t s);
 
 // vectors
 hipError_t launch_gather(const double* v, const int32_t* perm, int64_t n, double* out, hipStream_t s);
