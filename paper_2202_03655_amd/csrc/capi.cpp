@@ -1144,6 +1144,7 @@ hdf_status hdf_build_ex(const void* points, int dtype, int64_t n, int d, int64_t
   f->tau = hdf::tau_threshold(tol, f->nu, n, d, f->p);
   const double t_cores = now_ms() - t_overlap;
   HIPCHK(hipStreamSynchronize(s));
+  f->part.release();                              // the records are summed; the factor needs none of them
   f->t_plan += t_cores;
   f->t_gram = now_ms() - t0 - t_cores;
 
@@ -1325,6 +1326,7 @@ hdf_status hdf_build_cross(const void* x, int64_t nx, int64_t ldx, const void* y
   f->tau0 = f->tau;
   const double t_cores = now_ms() - t_overlap;
   HIPCHK(hipStreamSynchronize(s));
+  f->part.release();                              // the records are summed; the factor needs none of them
   f->t_plan += t_cores;
   f->t_gram = now_ms() - t0 - t_cores;
 

@@ -553,6 +553,12 @@ hipError_t hipGetLastError() { emu::Lock lock; hipError_t e = emu::g_last; emu::
 const char* hipGetErrorString(hipError_t e) { return e ? "emulated error" : "no error"; }
 void emu_flush() { emu::Lock lock; emu::flush(); }
 // operations enqueued and not yet run: what a caller would find pending on its streams
+long long emu_live() {
+  emu::Lock lock;
+  long long n = 0;
+  for (auto& a : emu::allocs) n += (long long)a.second;
+  return n;
+}
 long long emu_mallocs() { emu::Lock lock; return g_mallocs; }
 long long emu_frees() { emu::Lock lock; return g_frees; }
 long long emu_pending() { emu::Lock lock; return (long long)emu::q.size(); }

@@ -15,7 +15,7 @@ import torch
 import run_cases as rc
 from run_cases import _raw, check, dense, hdf, rel, to_dev, wl
 
-for _f in ("emu_pending", "emu_mallocs", "emu_frees", "emu_waits", "emu_launching_threads", "emu_launches", "emu_memsets"):
+for _f in ("emu_pending", "emu_mallocs", "emu_frees", "emu_waits", "emu_launching_threads", "emu_launches", "emu_memsets", "emu_live"):
     getattr(_raw, _f).restype = ctypes.c_longlong
 
 
@@ -211,7 +211,21 @@ def case_adjoint_degree0():
     check("adjoint_degree0", _degree(f) == 0 and sets == 0 and e <= 1e-10, f"s_k {f.info()['s_k']}, {sets} memsets, {e:.2e}")
 
 
-CASES = {"adjoint_degree0": case_adjoint_degree0, "product_buffers": case_product_buffers, "narrow_splits": case_narrow_splits, "noalloc_shares": case_noalloc_shares, "krr_failures": case_krr_failures, "krr_lanes": case_krr_lanes, "own_device": case_own_device, "adjoint_map": case_adjoint_map, "krr_create": case_krr_create}
+def case_factor_memory():
+    """A built factor holds its rows, the points and tables, not the records of the Gram pass (1.3 MB for these points)."""
+    n = 5000
+    X, Y = (to_dev(wl.unit_ball(m, 3, 44), torch.float64) for m in (n, 300))
+    for what in ("symmetric", "general"):
+        before = _raw.emu_live()
+        f = hdf.Factor(X, "gaussian", 1.0, 1e-4, precision=hdf.HDF_FP64) if what == "symmetric" else \
+            hdf.CrossFactor(Y, X, "gaussian", 1.0, 1e-4, precision=hdf.HDF_FP64)
+        _raw.emu_flush()
+        rest = _raw.emu_live() - before - f.info()["factor_bytes"]
+        check(f"factor_memory {what}", rest <= 600_000, f"{rest} bytes beside the rows")
+        del f
+
+
+CASES = {"factor_memory": case_factor_memory, "adjoint_degree0": case_adjoint_degree0, "product_buffers": case_product_buffers, "narrow_splits": case_narrow_splits, "noalloc_shares": case_noalloc_shares, "krr_failures": case_krr_failures, "krr_lanes": case_krr_lanes, "own_device": case_own_device, "adjoint_map": case_adjoint_map, "krr_create": case_krr_create}
 
 if __name__ == "__main__":
     rc._install()

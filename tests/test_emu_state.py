@@ -34,6 +34,7 @@ def _run(lib, case):
 
 
 @pytest.mark.parametrize("case", ["krr_create", "adjoint_map", "own_device", "krr_lanes", "krr_failures",
-                                  "noalloc_shares", "narrow_splits", "product_buffers", "adjoint_degree0"])
+                                  "noalloc_shares", "narrow_splits", "product_buffers", "adjoint_degree0",
+                                  "factor_memory"])
 def test_state_after_calls(emu_lib, case):
     _run(emu_lib, case)
