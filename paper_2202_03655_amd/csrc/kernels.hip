@@ -1521,7 +1521,7 @@ __global__ void __launch_bounds__(256) k_mv_reduce(const double* __restrict__ pa
 // With z_blocks > 0 (few points) blockIdx.z takes the blocks [z z_blocks, (z + 1) z_blocks) only,
 // whatever degree and radial function they are, and writes its share of KV to part[z][n][m];
 // k_mv_n_sum adds the shares in z order.
-// 64 columns: binary32, 1e6 points, rank 1413 3.06 -> 1.88 ms (96 TFLOP/s, matrix cores busy 80 %);
+// 64 columns: binary32, 1e6 points, rank 1413 3.06 -> 1.88 ms (96 TFLOP/s);
 // binary64, 5e5 points, rank 1463 4.43 -> 2.08 ms (45 TFLOP/s; two column tiles per wavefront 2.22).
 // 16 columns: binary64, 250,007 points 0.73 -> 0.52 ms; binary32, 1e6 points 0.79 -> 0.78 ms (memory).
 // Wavefronts per SIMD that the registers are held to (accumulators: 16 NCT registers in binary32,
@@ -1776,7 +1776,10 @@ __global__ void __launch_bounds__(256) k_mv_n_sum(const T* __restrict__ part, in
 // against 0.36; pass 2 0.59, 0.44 and 0.18 against 0.76, 0.51 and 0.30; with eight columns pass 2 takes
 // 0.75, 0.50 and 0.27, no longer worth a second layout of D W, and pass 1 is bound by its arithmetic.
 // One right-hand side: both passes 0.77 + 0.78 -> 0.63 + 0.58 ms, 0.66 + 0.73 -> 0.45 + 0.41, 0.32 + 0.34
-// -> 0.17 + 0.17.
+// -> 0.17 + 0.17.  Few points, whole products against the matrix-core passes of before (seven clouds, d = 3..8,
+// both types, geometric means for one and four columns): 2,000 points 1.41 and 1.18 times as fast, 12,007 1.72
+// and 1.35, 60,000 1.95 and 1.52; without allocation 3.1 and 2.6, 3.1 and 2.3, 2.5 and 1.9.  The least of
+// 448 is four columns of 2,000 to 4,000 binary32 points in d = 7 and 8, as fast within the runs' 2 us.
 //
 // Pass 1: a wavefront takes RB harmonics of one degree, up to four of its radial functions and a range
 // of points; every lane keeps its own sums of PPL points a step (one 16-byte load per row), formed with

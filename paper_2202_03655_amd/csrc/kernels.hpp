@@ -198,8 +198,8 @@ hipError_t launch_adj_coefficients(const double* gv, const double* gw, int64_t g
 
 // Adjoint by contractions (see hdf_backward).  launch_radial evaluates S
 // Chebyshev series of t(rho^2) at every point: out[row][i] = scale * sum_a
-// coef[q_off[row] + a] T_a(t_i), a < q_len[row] (rows padded: the launch
-// writes up to the next multiple of 2 or 4 points past n).  launch_adj_combine
+// coef[q_off[row] + a] T_a(t_i), a < q_len[row], zeros past n (rows as
+// long as launch_build's).  launch_adj_combine
 // forms dX[i][j] = (1/R) [sum_c w_ic KS[i][2mj + c] + v_ic KS[i][2mj + m + c]
 // + 2 xt_ij (sum_c w_ic K2[i][c] + v_ic K2[i][m + c])], KS zeros if NULL.  prec: factor type
 // (1 binary32, 0 binary64); dtype: points, W, V and dX (0 float32, 1 float64).
@@ -261,7 +261,9 @@ MfLayout mf_layout(int64_t n_loop, int S, int64_t n_rows, int64_t n_qcoef, int64
 // registers).  Ranks beyond a workgroup's slots take several slot groups, each of which evaluates the
 // factor again.  The plain binary32 kernels run where two buffers of the harmonics exceed LDS, so one
 // workgroup has a CU and half the wavefronts per SIMD: they take the registers for half as many again.
-// 1e6 points in d = 5 of rank 2142, 16 columns: 7.9 ms with 16 and 64 (two groups a pass), 4.6 so.
+// Products with 16 and 64 before, and so: 1e6 points in d = 5 of rank 2142 x 16 columns 7.9 and 4.6 ms; 200,003
+// of rank 2212 x 16 1.68 and 1.01, x 64 6.5 and 3.8, of rank 3618 x 16 2.68 and 1.97; in d = 4 of rank 2666 x 16
+// 1.48 and 1.20; 20,011 of rank 3048, where the number of groups stays, 0.258 both.
 constexpr int mf_slots(bool f32, bool spec, int pass) { return (f32 && !spec ? 3 : 2) * (pass == 1 ? 8 : 32); }
 // A wavefront's slot list is padded to whole blocks (pass 1: padding slots have out0 = -1; pass 2:
 // nv = 0) so that the kernels test the list length once per block.

@@ -305,7 +305,7 @@ hdf_status hdf_krr_create(const double* points, int64_t n, int d, int64_t ld, co
     // The build of a small cluster is a serial chain of short kernels, host planning and
     // synchronisations that leaves the device idle: the builds run on the threads of a pool kept for
     // such work, each on a stream of its own and with its own loops on its thread (30 clusters of 460
-    // points: the whole construction and solve 21.9 ms with the builds one after the other, 10.8 ms so).
+    // points: a whole fit 21.9 ms with the builds one after the other, 11.4 ms so).
     // While another construction has the pool they run one after the other on the caller's stream, as
     // does a build that finds no memory here (its neighbours hold scratch of their own).  Any other failure
     // is the construction's, the one of the lowest cluster as when they run one after the other; clusters
