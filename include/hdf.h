@@ -224,7 +224,9 @@ hdf_status hdf_build_cross(const void* x, int64_t nx, int64_t ldx, const void* y
                            double tol, hdf_precision prec, void* hip_stream, hdf_handle* out);
 
 /* KV = U D U^T V (Sec. 3.6, two passes over the factor, no host sync); for a
- * handle from hdf_build_cross, KV = U (V_y^T V) with V of ny rows.
+ * handle from hdf_build_cross, KV = U (V_y^T V) with V of ny rows.  The first
+ * product of a stored factor allocates the work space of all with up to 16
+ * right-hand sides.
  *   V   device, n x m (ldv >= m), KV device, n x m (ldkv >= m); same dtype as
  *       the points; 1 <= m <= HDF_MAX_RHS.  V and KV must not overlap. */
 hdf_status hdf_matvec(hdf_handle h, const void* V, int64_t m, int64_t ldv,
@@ -235,7 +237,7 @@ hdf_status hdf_matvec(hdf_handle h, const void* V, int64_t m, int64_t ldv,
  * arguments and result as hdf_matvec, with 1 <= m <= 64 and a stored factor
  * (HDF_STORE_FACTOR; else HDF_E_ARG).  It calls no hipMalloc / hipFree and no
  * allocating routine, copies nothing from the host and records no events:
- * its work buffers (split partials, U^T V, D U^T V) live in a fixed 32 MiB
+ * its work buffers (D U^T V, split partials, shares) live in a fixed 32 MiB
  * array per GPU inside the library, held until the process ends.  A factor
  * whose rank r needs more than that (at least 20 r m16 bytes with m16 =
  * 16 ceil(m / 16) for a binary32 factor, 24 r m16 for binary64) is rejected
@@ -256,7 +258,8 @@ hdf_status hdf_matvec_noalloc(hdf_handle h, const void* V, int64_t m, int64_t ld
  *            (NULL: not computed); same dtype as the points.
  * One blocking synchronisation when dF/dl is asked (U^T V and U^T W come to
  * the host), one more the first time that dF/dX is asked for a dimension and
- * largest degree (the derivative maps of its harmonics go to the device).  dF/dX needs a stored factor
+ * largest degree (the derivative maps of its harmonics go to the device, which
+ * keeps the last eight).  dF/dX needs a stored factor
  * (HDF_STORE_FACTOR) whose kept degrees are 0..K; otherwise HDF_E_ARG before
  * any device work.  It is formed from the stored factor: the stored harmonic
  * rows are solid harmonics, homogeneous harmonic polynomials of the scaled
@@ -382,8 +385,9 @@ hdf_status hdf_kernel_matvec(const double* x, int64_t nx, int64_t ldx, const dou
  *   labels  device int32, n, each in [0, k); 1 <= k <= HDF_MAX_CLUSTERS.
  *   tol     tolerance of every diagonal-block factor (hdf_build).
  *   lambda  regularisation, > 0.
- * Blocking: labels are read back, and each block factor synchronises as
- * hdf_build does.  HDF_E_ARG for a label out of range or a cluster larger
+ * Blocking: labels are read back, the block factors are built on streams of
+ * the library (or on hip_stream, synchronising as hdf_build does), and the
+ * system is complete when the call returns: it may be used on any stream.  HDF_E_ARG for a label out of range or a cluster larger
  * than 16384 points; HDF_E_INFEASIBLE when a block factor is, or when a
  * preconditioner block is not numerically positive definite. */
 hdf_status hdf_krr_create(const double* points, int64_t n, int d, int64_t ld, const int32_t* labels,
